@@ -222,8 +222,8 @@ ht_status ht_eval_particles_grad(ht_ctx* ctx, int n_frames, const int32_t* frame
  * records, work list, partial sums) is a 64 MiB device array inside the library, one per GPU,
  * held until the process ends.  Every call on a GPU shares that GPU's array, so calls that
  * overlap on one GPU (on different streams, or from different contexts) race: enqueue them on
- * one stream.  Nothing in it must start at zero (the work-list kernel of each call resets its
- * dequeue counter), and it keeps the last call's contents.  Same arguments, layouts and
+ * one stream.  Nothing in it must start at zero (the kinematics kernel of each call resets its
+ * work queues), and it keeps the last call's contents.  Same arguments, layouts and
  * results as ht_eval_particles.  Errors as ht_eval_particles, and HT_ERR_ARG when the call
  * needs more than the 64 MiB (about 1800 two-hand particles over 640x480 observations, 8000
  * one-hand particles over 128x128 ones: the size grows with the particles and the largest
@@ -304,11 +304,14 @@ ht_status ht_pso_run_graph(ht_ctx* ctx, const ht_swarm* swarm, const ht_pso_para
 ht_status ht_pso_box_around(ht_ctx* ctx, int n_frames, const float* center,
                             const float* halfwidth, float* lo, float* hi, void* hip_stream);
 
-/* Launch shape of the batched persistent ray-cast kernel.  tiles_per_item is shortened
- * automatically for launches too small to give every compute unit a work item. */
+/* Launch shape of the batched persistent ray-cast kernel.  The work items follow from the launch
+ * itself: whole particles where there are more of them than workgroups, else equal parts of a
+ * particle, one per workgroup.  tiles_per_item is checked and kept for callers that set it and
+ * does not change the items. */
 typedef struct {
-  int32_t tiles_per_item;   /* 8x8-pixel tiles per work item (one work item per workgroup) */
-  int32_t groups_per_cu;    /* persistent workgroups per compute unit                       */
+  int32_t tiles_per_item;   /* 4..1024 (see above)                                          */
+  int32_t groups_per_cu;    /* persistent workgroups per compute unit: 1..3, or 4 and more
+                               for as many as fit                                           */
   int32_t cull;             /* 0: primitive screen boxes from their 3D bounding boxes;
                                1: clipped to the image extent of a bounding capsule        */
 } ht_launch_config;

@@ -122,10 +122,11 @@ struct ht_ctx {
   // evaluation workspace
   ht::Workspace ws{};
   int cap_particles = 0;
-  int cap_items = 0;
   int cap_tiles = 0;
   bool cap_wrench = false;
   ht_launch_config lc{16, 4, 1};
+  int groups[2][2] = {};      // resident ray-cast workgroups per CU: forward without and with debug
+                              // images, gradient with the work-list kernel's list and its own
   // swarm refinement scratch
   float* r_x = nullptr;       // [cap_ref][n_dof] current positions of the refined particles
   float* r_cost = nullptr;    // [cap_ref]
@@ -143,7 +144,7 @@ struct ht_ctx {
   int cap_seg = 0;
   std::map<GraphKey, hipGraphExec_t> graphs;
   void* scratch = nullptr;    // this device's address of the no-allocation scratch array
-  unsigned long long* d_eval_count = nullptr;   // [2] forward / gradient evaluations
+  unsigned long long* d_eval_count = nullptr;   // [2][kCountSlots] forward / gradient sums
   unsigned int* d_errors = nullptr;              // HT_DEVERR_* flags
   // tracing of eager launches
   struct ProfRec {
@@ -179,20 +180,18 @@ void invalidate_graphs(ht_ctx* c) {
 
 void free_workspace(ht_ctx* c) {
   invalidate_graphs(c);
-  dfree(c->ws.recs);
-  dfree(c->ws.boxes);
-  dfree(c->ws.caps);
-  dfree(c->ws.capr);
+  dfree(c->ws.tables);
   dfree(c->ws.pinfo);
   dfree(c->ws.dof_frame);
   dfree(c->ws.seg_org);
+  dfree(c->ws.partial);
+  dfree(c->ws.wrench);
   dfree(c->ws.tiles);
   dfree(c->ws.item_off);
   dfree(c->ws.item_map);
-  dfree(c->ws.partial);
-  dfree(c->ws.wrench);
+  dfree(c->ws.list);
   dfree(c->ws.counters);
-  c->cap_particles = c->cap_items = c->cap_tiles = 0;
+  c->cap_particles = c->cap_tiles = 0;
   c->cap_wrench = false;
 }
 
@@ -204,10 +203,18 @@ bool capturing(hipStream_t s) {
 
 // Whether the workspace already holds n_total particles over observations of max_tiles tiles.
 bool workspace_fits(const ht_ctx* c, int n_total, int max_tiles, bool grad) {
-  const long long items =
-      std::max<long long>((long long)n_total * ((max_tiles + kMinTilesPerItem - 1) / kMinTilesPerItem), 1);
-  return n_total <= c->cap_particles && items <= c->cap_items && max_tiles <= c->cap_tiles &&
-         (!grad || c->cap_wrench);
+  return n_total <= c->cap_particles && max_tiles <= c->cap_tiles && (!grad || c->cap_wrench);
+}
+
+// Work items of a call over n_total particles, at most.  Forward: its particles, or the parts
+// they are split into, which are no more than the resident workgroups.  Gradient: items of at
+// least kMinTilesPerItem tiles.
+constexpr int kMaxGroupsPerCu = 8;     // 2048 threads
+constexpr int kListGroupsPerCu = 5;    // nominal workgroups per CU of a gradient work list
+constexpr int kTilesPerPart = 16;      // tiles of the observation per part, at least
+long long item_bound(const ht_ctx* c, long long n_total, int max_tiles, bool grad) {
+  const long long fwd = std::max<long long>(n_total, (long long)kMaxGroupsPerCu * c->n_cu);
+  return grad ? std::max(fwd, n_total * ((max_tiles + kMinTilesPerItem - 1) / kMinTilesPerItem)) : fwd;
 }
 
 // Make sure the workspace holds n_total particles over observations of max_tiles tiles.
@@ -215,73 +222,67 @@ ht_status ensure_workspace(ht_ctx* c, int n_total, int max_tiles, bool grad, hip
   const long long items_ll =
       (long long)n_total * ((max_tiles + kMinTilesPerItem - 1) / kMinTilesPerItem);
   if (items_ll > (1ll << 30)) return fail(HT_ERR_ARG, "workload too large: %lld work items", items_ll);
-  const int items = (int)std::max<long long>(items_ll, 1);
   if (workspace_fits(c, n_total, max_tiles, grad)) return HT_OK;
   if (capturing(s))
     return fail(HT_ERR_STATE, "workspace too small during graph capture; call ht_reserve first");
   HT_HIP(hipDeviceSynchronize());
   const int np = std::max(n_total, c->cap_particles);
   const int nt = std::max(max_tiles, c->cap_tiles);
-  const int ni = std::max<long long>(items, (long long)np * ((nt + kMinTilesPerItem - 1) / kMinTilesPerItem));
   const bool wr = grad || c->cap_wrench;
+  const size_t ni = (size_t)item_bound(c, np, nt, wr);
   free_workspace(c);
   auto& w = c->ws;
-  HT_HIP(hipMalloc(&w.recs, (size_t)np * c->n_prim * ht::kRec * sizeof(float)));
-  HT_HIP(hipMalloc(&w.boxes, (size_t)np * c->n_prim * sizeof(int4)));
-  HT_HIP(hipMalloc(&w.caps, (size_t)np * c->n_prim * sizeof(float4)));
-  HT_HIP(hipMalloc(&w.capr, (size_t)np * c->n_prim * sizeof(float2)));
+  HT_HIP(hipMalloc(&w.tables, (size_t)np * ht::Tables(c->n_prim).words * sizeof(float4)));
   HT_HIP(hipMalloc(&w.pinfo, (size_t)np * sizeof(ht::PInfo)));
   HT_HIP(hipMalloc(&w.dof_frame, (size_t)np * c->n_dof * 8 * sizeof(float)));
   HT_HIP(hipMalloc(&w.seg_org, (size_t)np * c->n_seg * 4 * sizeof(float)));
   HT_HIP(hipMalloc(&w.tiles, (size_t)np * sizeof(int)));
-  HT_HIP(hipMalloc(&w.item_off, (size_t)(np + 1) * sizeof(int)));
-  HT_HIP(hipMalloc(&w.item_map, (size_t)ni * sizeof(int)));
-  HT_HIP(hipMalloc(&w.partial, (size_t)ni * sizeof(ht::Partial)));
-  if (wr) HT_HIP(hipMalloc(&w.wrench, (size_t)ni * c->n_seg * 6 * sizeof(float)));
-  HT_HIP(hipMalloc(&w.counters, 4 * sizeof(int)));
-  HT_HIP(hipMemset(w.counters, 0, 4 * sizeof(int)));
-  w.max_items = ni;
+  HT_HIP(hipMalloc(&w.partial, (ni + 1) * sizeof(ht::Partial)));   // (an empty range may start at the end)
+  if (wr) {
+    HT_HIP(hipMalloc(&w.item_off, (size_t)(np + 1) * sizeof(int)));
+    HT_HIP(hipMalloc(&w.item_map, ni * sizeof(int)));
+    HT_HIP(hipMalloc(&w.list, 4 * sizeof(int)));
+    HT_HIP(hipMalloc(&w.wrench, ni * c->n_seg * 6 * sizeof(float)));
+  }
+  HT_HIP(hipMalloc(&w.counters, 2 * ht::kCounterInts * sizeof(int)));
   c->cap_tiles = nt;
   c->cap_particles = np;
-  c->cap_items = ni;
   c->cap_wrench = wr;
   return HT_OK;
 }
 
-// Work items that a call over n_total particles and observations of max_tiles tiles can
-// produce (items are never shorter than kMinTilesPerItem tiles).
-long long item_bound(int n_total, int max_tiles) {
-  return std::max<long long>(
-      (long long)n_total * ((max_tiles + kMinTilesPerItem - 1) / kMinTilesPerItem), 1);
+// What ht_eval_particles_noalloc accepts (its documented size limit): the bytes of a workspace
+// that holds, per particle, its tables, header, joint frames and segment origins, and per work item of
+// kMinTilesPerItem tiles a partial and its bookkeeping.  The workspace it lays out (below) is smaller.
+size_t noalloc_need(const ht_ctx* c, long long np, int max_tiles) {
+  const long long runs = std::max<long long>(np * ((max_tiles + kMinTilesPerItem - 1) / kMinTilesPerItem), 1);
+  size_t off = 0;
+  for (const size_t bytes :
+       {(size_t)np * c->n_prim * 80, (size_t)np * c->n_prim * 16, (size_t)np * c->n_prim * 16,
+        (size_t)np * c->n_prim * 8, (size_t)np * 112, (size_t)np * c->n_dof * 32,
+        (size_t)np * c->n_seg * 16, (size_t)np * 4, (size_t)(np + 1) * 4, (size_t)runs * 4,
+        (size_t)runs * 24, (size_t)16})
+    off = (off + 255) / 256 * 256 + bytes;
+  return off;
 }
 
 // Lays the forward-evaluation workspace of np particles and ni work items out from base in
-// 256-byte aligned pieces (no wrench buffer) and returns the bytes it spans; base == nullptr
-// computes the size only.
-size_t carve_workspace(unsigned char* base, long long np, long long ni, int n_prim, int n_dof,
-                       int n_seg, ht::Workspace* w) {
+// 256-byte aligned pieces (no adjoint buffers) and returns the bytes it spans.
+size_t carve_workspace(unsigned char* base, long long np, long long ni, int n_prim,
+                       ht::Workspace* w) {
   size_t off = 0;
   auto take = [&](auto*& ptr, size_t bytes) {
     off = (off + 255) / 256 * 256;
-    ptr = base ? reinterpret_cast<std::remove_reference_t<decltype(ptr)>>(base + off) : nullptr;
+    ptr = reinterpret_cast<std::remove_reference_t<decltype(ptr)>>(base + off);
     off += bytes;
   };
   ht::Workspace t{};
-  take(t.recs, (size_t)np * n_prim * ht::kRec * sizeof(float));
-  take(t.boxes, (size_t)np * n_prim * sizeof(int4));
-  take(t.caps, (size_t)np * n_prim * sizeof(float4));
-  take(t.capr, (size_t)np * n_prim * sizeof(float2));
+  take(t.tables, (size_t)np * ht::Tables(n_prim).words * sizeof(float4));
   take(t.pinfo, (size_t)np * sizeof(ht::PInfo));
-  take(t.dof_frame, (size_t)np * n_dof * 8 * sizeof(float));
-  take(t.seg_org, (size_t)np * n_seg * 4 * sizeof(float));
   take(t.tiles, (size_t)np * sizeof(int));
-  take(t.item_off, (size_t)(np + 1) * sizeof(int));
-  take(t.item_map, (size_t)ni * sizeof(int));
   take(t.partial, (size_t)ni * sizeof(ht::Partial));
-  take(t.counters, 4 * sizeof(int));
-  t.wrench = nullptr;
-  t.max_items = (int)ni;
-  if (w) *w = t;
+  take(t.counters, 2 * ht::kCounterInts * sizeof(int));
+  *w = t;
   return off;
 }
 
@@ -317,6 +318,13 @@ ht_status check_slots_set(ht_ctx* c) {
 
 namespace ht {
 
+// Resident workgroups per CU of a ray-cast variant for the context's model (looked up once).
+static int resident_groups(ht_ctx* c, bool grad, bool dbg, bool all_types, bool self) {
+  int& n = c->groups[grad][grad ? self : dbg];
+  if (n == 0) n = raycast_groups_per_cu(grad, dbg, all_types, self, c->n_prim, c->n_seg);
+  return n;
+}
+
 // Evaluation shared by ht_eval_particles, ht_eval_particles_grad and the swarm step.
 // With src, particle r of frame f reuses the kinematics that the previous evaluation (of
 // src_stride particles per frame) left for its particle src[r] of frame f: poses must equal
@@ -328,7 +336,8 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
                     const ht_debug* dbg, hipStream_t s, const int32_t* frame_stop = nullptr,
                     const int32_t* src = nullptr, int src_stride = 0,
                     const Workspace* fixed = nullptr, const int32_t* active = nullptr,
-                    int active_div = 1, bool assemble = true, EvalArgs* args_out = nullptr) {
+                    int active_div = 1, bool assemble = true, EvalArgs* args_out = nullptr,
+                    bool adjoint = false) {
   const int n_total = n_frames * n_particles;
   if (n_total == 0) return HT_OK;
   if (!fixed) {
@@ -363,23 +372,35 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
     a.dbg_bg = sh.entry.bg;
   }
   a.type_masks = c->tmask;
-  // the work-list kernel shortens work items for launches with few tiles (tiles_per_item is
-  // their maximum); never more persistent workgroups than there can be items
-  a.tiles_per_item = c->lc.tiles_per_item;
   a.cull = c->lc.cull;
-  const long long bound = (long long)n_total *
-                          ((c->max_tiles() + kMinTilesPerItem - 1) / kMinTilesPerItem);
+  a.adjoint = adjoint || grad ? 1 : 0;
   const bool dbg_on = a.dbg.depth || a.dbg.hit || a.dbg.rm || a.dbg.winner || a.dbg.margin;
   const bool all_types = (c->tmask.m[HT_CONE][0] | c->tmask.m[HT_CONE][1] |
                           c->tmask.m[HT_ECYLINDER][0] | c->tmask.m[HT_ECYLINDER][1]) != 0ull;
-  // launches of at most kSelfSchedMax particles without debug images build their work list
-  // in the ray cast (no work-list launch)
-  a.self_sched = n_total <= ht::kSelfSchedMax && !dbg_on ? 1 : 0;
-  int gpc = std::min(c->lc.groups_per_cu,
-                     ht::raycast_groups_per_cu(grad != nullptr, dbg_on, all_types,
-                                               a.self_sched != 0));
-  if (a.self_sched) gpc = std::min(gpc, ht::kSelfGroupsPerCu);
-  a.grid = (int)std::max<long long>(1, std::min<long long>((long long)c->n_cu * gpc, bound));
+  // groups_per_cu: four and more stand for every workgroup that fits (five to eight of them);
+  // a cap at four left 65536 poses of a 320x240 frame at 3.53 ms against 2.71 ms with eight
+  const int lc = c->lc.groups_per_cu;
+  const int fit = std::min(resident_groups(c, grad != nullptr, dbg_on, all_types,
+                                           n_total <= kSelfSchedMax), kMaxGroupsPerCu);
+  const int full = std::max(c->n_cu * (lc >= 4 ? fit : std::min(lc, fit)), 8);
+  // Parts per particle: as many as give every resident workgroup one item, rounded down (a
+  // launch with more items than workgroups waits for the few that take two: 256 poses of a
+  // 320x240 frame 34 us with one item per workgroup, 39 us with two), but parts of 16 tiles of
+  // the observation at least (64 poses of a 128x128 frame: 16 parts 27.2 us per generation, 32
+  // parts 30.9 us: their workgroups' start costs more than the few tiles they take over).
+  const int most = (c->max_tiles() + kTilesPerPart - 1) / kTilesPerPart;
+  a.parts = grad ? 1 : std::max(1, std::min(most, full / n_total));
+  a.grid = grad ? full : (int)std::min<long long>(full, (long long)n_total * a.parts);
+  a.direct = assemble && !grad && a.parts == 1 ? 1 : 0;
+  if (grad) {
+    // the nominal grid that sizes a gradient's items (part of its bits, see the work list)
+    const long long items =
+        (long long)n_total * ((c->max_tiles() + kMinTilesPerItem - 1) / kMinTilesPerItem);
+    a.tiles_per_item = c->lc.tiles_per_item;
+    a.list_grid = (int)std::max<long long>(
+        1, std::min<long long>((long long)c->n_cu * std::min(lc, kListGroupsPerCu), items));
+    a.grid = (int)std::max<long long>(1, std::min<long long>(full, items));
+  }
   a.n_prim = c->n_prim;
   a.n_seg = c->n_seg;
   a.n_dof = c->n_dof;
@@ -389,7 +410,8 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
   for (int stage = 0; stage < kNumStages; ++stage) {
     if (stage == kStageFk && src) continue;   // reused from the previous evaluation
     if (stage == kStageFinalize && !assemble) continue;   // assembled by the next kernel
-    if (stage == kStageSched && a.self_sched) continue;   // built by the ray cast
+    if (stage == kStageFinalize && a.direct) continue;   // costs from the ray cast
+    if (stage == kStageSched && (!grad || n_total <= kSelfSchedMax)) continue;   // no work list
     if (fixed)
       HT_HIP(launch_eval_stage(stage, a, ws, s));
     else
@@ -424,8 +446,8 @@ ht_status ht_create(ht_ctx** out, int hip_device) {
   hipError_t e = hipMalloc(&c->d_slots, HT_MAX_SLOTS * sizeof(ht::FrameSlot));
   if (e == hipSuccess) e = hipMemset(c->d_slots, 0, HT_MAX_SLOTS * sizeof(ht::FrameSlot));
   if (e == hipSuccess) e = hipMalloc(&c->d_model, sizeof(ht::DevModel));
-  if (e == hipSuccess) e = hipMalloc(&c->d_eval_count, 2 * sizeof(unsigned long long));
-  if (e == hipSuccess) e = hipMemset(c->d_eval_count, 0, 2 * sizeof(unsigned long long));
+  if (e == hipSuccess) e = hipMalloc(&c->d_eval_count, 2 * ht::kCountSlots * sizeof(unsigned long long));
+  if (e == hipSuccess) e = hipMemset(c->d_eval_count, 0, 2 * ht::kCountSlots * sizeof(unsigned long long));
   if (e == hipSuccess) e = hipMalloc(&c->d_errors, sizeof(unsigned int));
   if (e == hipSuccess) e = hipMemset(c->d_errors, 0, sizeof(unsigned int));
   if (e != hipSuccess) {
@@ -616,6 +638,7 @@ ht_status ht_set_model(ht_ctx* c, const ht_model* m) {
   c->n_dof = m->n_dof;
   c->n_seg = m->n_seg;
   c->n_prim = m->n_prim;
+  std::memset(c->groups, 0, sizeof c->groups);   // the LDS need follows the model
   c->has_model = true;
   return HT_OK;
 }
@@ -768,16 +791,16 @@ ht_status ht_eval_particles_noalloc(ht_ctx* c, int n_frames, const int32_t* fram
   if ((st = check_slots_set(c)) != HT_OK) return st;
   if (!c->scratch) return fail(HT_ERR_STATE, "no scratch address on device %d", c->device);
   const int n_total = n_frames * n_particles;
-  const long long ni = item_bound(n_total, c->max_tiles());
-  const size_t need = carve_workspace(nullptr, n_total, ni, c->n_prim, c->n_dof, c->n_seg, nullptr);
+  const size_t need = noalloc_need(c, n_total, c->max_tiles());
   if (need > kScratchBytes)
     return fail(HT_ERR_ARG,
                 "%d particles over observations of up to %d tiles need %zu bytes of scratch; "
                 "ht_eval_particles_noalloc has %zu: evaluate fewer particles per call",
                 n_total, c->max_tiles(), need, kScratchBytes);
   ht::Workspace w{};
-  carve_workspace(static_cast<unsigned char*>(c->scratch), n_total, ni, c->n_prim, c->n_dof,
-                  c->n_seg, &w);
+  if (carve_workspace(static_cast<unsigned char*>(c->scratch), n_total, item_bound(c, n_total, 0, false), c->n_prim,
+                      &w) > kScratchBytes)
+    return fail(HT_ERR_ARG, "%d particles exceed the scratch array", n_total);
   DeviceGuard g(c->device);
   return ht::eval_impl(c, n_frames, frame_slots, n_particles, poses, cost, nullptr, nullptr,
                        nullptr, (hipStream_t)stream, nullptr, nullptr, 0, &w);
@@ -849,11 +872,13 @@ ht_status ensure_refine(ht_ctx* c, int n_ref, hipStream_t s) {
 ht_status pso_step_impl(ht_ctx* c, const ht_swarm& sw, const ht_pso_params& p, hipStream_t s) {
   const int F = sw.n_frames, P = sw.n_particles, D = c->n_dof;
   if (F * P == 0) return HT_OK;
-  ht_status st = ht::eval_impl(c, F, sw.frame_slots, P, sw.x, sw.cost, nullptr, nullptr, nullptr, s,
-                               sw.stop_gen);
-  if (st != HT_OK) return st;
   const int K = p.refine_topk;
-  if (K > 0 && p.refine_steps > 0) {
+  const bool refine = K > 0 && p.refine_steps > 0;
+  // (the refinement's first gradient evaluation reads these particles' kinematics)
+  ht_status st = ht::eval_impl(c, F, sw.frame_slots, P, sw.x, sw.cost, nullptr, nullptr, nullptr, s,
+                               sw.stop_gen, nullptr, 0, nullptr, nullptr, 1, true, nullptr, refine);
+  if (st != HT_OK) return st;
+  if (refine) {
     const int n_ref = F * K;
     if ((st = ensure_refine(c, n_ref, s)) != HT_OK) return st;
     HT_HIP(traced(c, HT_K_REFINE, n_ref, s, [&] { return ht::launch_refine_select(sw, K, D, c->r_sel, c->r_x, c->r_cost, c->r_active, s); }));
@@ -1175,12 +1200,15 @@ ht_status ht_eval_counts(ht_ctx* c, int64_t* forward, int64_t* gradient, int res
   g_err.clear();
   if (!c || !forward || !gradient) return fail(HT_ERR_ARG, "NULL argument");
   DeviceGuard g(c->device);
-  unsigned long long v[2] = {0, 0};
+  unsigned long long v[2 * ht::kCountSlots] = {};
   HT_HIP(hipDeviceSynchronize());
   HT_HIP(hipMemcpy(v, c->d_eval_count, sizeof v, hipMemcpyDeviceToHost));
   if (reset) HT_HIP(hipMemset(c->d_eval_count, 0, sizeof v));
-  *forward = (int64_t)v[0];
-  *gradient = (int64_t)v[1];
+  *forward = *gradient = 0;
+  for (int i = 0; i < ht::kCountSlots; ++i) {
+    *forward += (int64_t)v[i];
+    *gradient += (int64_t)v[ht::kCountSlots + i];
+  }
   return HT_OK;
 }
 

@@ -15,12 +15,7 @@ constexpr int kBlock = 256;         // 4 wavefronts per workgroup
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kRec = 20;            // floats per primitive record
 constexpr int kNumTypes = 5;        // HT_SPHERE .. HT_ECYLINDER
-// Work items of the ray-cast kernel (tiles): never shorter than kMinTilesPerItem (the lower
-// bound of the configured tiles_per_item, which sizes the workspace); the work-list kernel
-// aims at kFloorTilesFwd / kFloorTilesGrad at least, capped by the configured value.
-constexpr int kMinTilesPerItem = 4;
-constexpr int kFloorTilesFwd = 8;
-constexpr int kFloorTilesGrad = 8;  // 16 left a 32-particle gradient launch at 22.5 us (19.2)
+constexpr int kCounterInts = 8 * 256;   // work queue counters of one launch
 constexpr float kDMatch = 10.0f;    // d_m, mm
 constexpr float kDClamp = 40.0f;    // d_M, mm
 constexpr double kLambda = 20.0;
@@ -77,10 +72,12 @@ struct FrameSlot {
   const uint8_t* grad_mask;  // [H][W] gradient pixel mask of the slot, NULL: every pixel
 };
 
-// Per-particle summary written by the kinematics kernel.  The tiles to visit are the union of
+// Per-particle header written by the kinematics kernel.  The tiles to visit are the union of
 // up to kMaxRects disjoint rectangles (one per kinematic tree, overlapping ones merged), each
-// covering its primitives' screen boxes; tile t of the particle is found by walking them.
-struct PInfo {
+// covering its primitives' screen boxes; tile t of the particle is found by walking them.  It
+// also carries what the ray cast needs of the frame's slot, so that one read of the header
+// (scalar loads) starts a particle without a dependent slot lookup.
+struct alignas(16) PInfo {
   int4 rect[kMaxRects];       // tx0, ty0, tw, th (tiles)
   int n_rects;
   int n_tiles;                // sum of the rectangles' tiles
@@ -90,37 +87,51 @@ struct PInfo {
   int skip;                   // 1: not evaluated (its frame has stopped, or it is a candidate
                               // of a refined particle that has stopped): nothing is written
   int kc_mask;                // collision pairs with a positive term (bit i: pair i)
-  double bg_td, bg_or;        // the observation's ROI-wide background sums (copied from its
-                              // slot, so the finalize kernels need no slot lookup)
+  int TW;                     // the slot's tile columns and ROI width
+  int W;
+  float bg;                   // the slot's background plane depth, ray scales and centre
+  float sx, sy, sz, cx, cy;
+  const uint32_t* words;      // the slot's observation words, tile sums and gradient mask
+  const float* tile_td;
+  const int* tile_skin;
+  const uint8_t* grad_mask;
+  double bg_td, bg_or;        // the observation's ROI-wide background sums
 };
 
 struct Partial {
   double td;  // clamped depth sum minus the background sum of the processed tiles
   int a;      // sum(o_s and r_m)
   int o;      // sum(o_s or r_m) minus the background skin count of the processed tiles
-  int pad;
+};
+
+// A particle's primitive tables as the ray cast stages them in LDS, one contiguous run of
+// 16-byte words per particle: the records ([n_prim][kRec] floats), the pixel boxes ([n_prim]
+// int4 (u0, u1, v0, v1), empty = (1, 0, 1, 0)), the image segments of the bounding capsules
+// ([n_prim] float4 (x0, y0, dx, dy): the centres of the end spheres' image discs, pixels) and
+// their reaches ([n_prim] float2 (1 / |(dx, dy)|^2 or 0, reach^2): a tile whose centre lies
+// farther than reach from the segment sees none of the primitive).
+struct Tables {
+  int box, cap, capr, words;  // offsets of the three later pieces and the total, 16-byte words
+  __host__ __device__ explicit Tables(int n_prim)
+      : box(n_prim * (kRec / 4)), cap(box + n_prim), capr(cap + n_prim),
+        words(capr + (n_prim + 1) / 2) {}
 };
 
 // Workspace of one evaluation call (device pointers, owned by the context).
 struct Workspace {
-  float* recs;           // [n_total][n_prim][kRec]
-  int4* boxes;           // [n_total][n_prim] pixel box (u0, u1, v0, v1), empty = (1, 0, 1, 0)
-  float4* caps;          // [n_total][n_prim] image segment (x0, y0, dx, dy) of the bounding
-                         // capsule: the centres of its end spheres' image discs (pixels)
-  float2* capr;          // [n_total][n_prim] (1 / |(dx, dy)|^2 or 0, reach^2): a tile whose
-                         // centre lies farther than reach from the segment sees none of it
+  float4* tables;        // [n_total][Tables(n_prim).words]
   PInfo* pinfo;          // [n_total]
   float* dof_frame;      // [n_total][n_dof][8]: kind, axis xyz, point xyz (camera frame)
   float* seg_org;        // [n_total][n_seg][4]
-  int* tiles;            // [n_total] tiles of each particle (a compact copy for the
-                         // scheduler), -1 for a particle that is not evaluated (skipped)
-  int* item_off;         // [n_total + 1]
-  int* item_map;         // [max_items]
-  Partial* partial;      // [max_items]
-  float* wrench;         // [max_items][n_seg][6] (gradient only)
-  int* counters;         // [0] dequeue counter, [1] total items, [2] tiles per item,
-                         // [3] 1: a particle's items take interleaved tiles
-  int max_items;
+  int* tiles;            // [n_total] tiles of each particle (a compact copy for the work list),
+                         // -1 for a particle that is not evaluated (skipped)
+  int* item_off;         // [n_total + 1] work list of a gradient launch: items per particle
+  int* item_map;         // [items] particle of each item (launches of more than kSelfSchedMax)
+  int* list;             // [4] items, tiles per item, 1: interleaved tiles (as item_map)
+  Partial* partial;      // [items] forward: part q of particle r at r * parts + q
+  float* wrench;         // [items][n_seg][6] (gradient only)
+  int* counters;         // [2][kCounterInts] work queue counters, cleared by the kinematics
+                         // kernel: for its own evaluation, and for one that reuses its tables
 };
 
 struct EvalArgs {
@@ -137,8 +148,8 @@ struct EvalArgs {
   // evaluated (the candidates of a refined particle that has stopped refining)
   const int* active;
   int active_div;
-  // evaluations performed (not skipped), [0] forward and [1] gradient, added up by the
-  // work-list kernel of every call; may be NULL
+  // evaluations performed (not skipped), kCountSlots forward sums, then as many gradient ones
+  // (a workgroup adds to the sum of its index, so that they do not meet on one address)
   unsigned long long* eval_count;
   unsigned int* dev_errors;    // HT_DEVERR_* flags raised on the device, may be NULL
   // NULL, or per evaluated particle r its source s = src[r]: the particle reuses the kinematics
@@ -150,11 +161,13 @@ struct EvalArgs {
   int dbg_W, dbg_H;
   float dbg_bg;
   TypeMasks type_masks;
-  int tiles_per_item;
   int cull;                    // 1: screen boxes clipped to the bounding capsule's image extent
+  int adjoint;                 // 1: the kinematics also writes dof_frame and seg_org
   int grid;                    // persistent workgroups
-  int self_sched;              // 1: the ray cast builds the work list (at most kSelfSchedMax
-                               // particles, no debug images)
+  int parts;                   // work items per particle: parts * particles <= grid, or 1
+  int tiles_per_item;          // gradient work list: most tiles per item, and the nominal grid
+  int list_grid;               // that its items are sized for
+  int direct;                  // 1 (forward, whole particles): the ray cast writes the costs
   int n_prim, n_seg, n_dof;
 };
 
@@ -163,12 +176,12 @@ hipError_t launch_pack_observation(const uint16_t* depth, const uint8_t* skin, i
                                    int TW, int TH, uint32_t* words, float* tile_td,
                                    int* tile_skin, double* totals, float bg, hipStream_t s);
 enum { kStageFk = 0, kStageSched = 1, kStageRaycast = 2, kStageFinalize = 3, kNumStages = 4 };
-constexpr int kSelfSchedMax = 256;   // launches of at most this many particles self-schedule
-// persistent workgroups per CU of a self-scheduled launch, at most: on the two-hand 640x480
-// workload the 128-particle forward launch took 31.5, 27.9, 26.9, 30.5 and 30.7 us at 4..8
-constexpr int kSelfGroupsPerCu = 6;
+constexpr int kSelfSchedMax = 256;   // gradient launches of at most this many particles build
+                                     // their own work list
+constexpr int kMinTilesPerItem = 4;  // lower bound of the configured tiles_per_item
+constexpr int kCountSlots = 64;
 hipError_t launch_eval_stage(int stage, const EvalArgs& a, const Workspace& ws, hipStream_t s);
-int raycast_groups_per_cu(bool grad, bool dbg, bool all_types, bool self_sched);
+int raycast_groups_per_cu(bool grad, bool dbg, bool all_types, bool self, int n_prim, int n_seg);
 hipError_t launch_pso_init(const DevModel* model, const ht_swarm& sw, int n_dof, hipStream_t s);
 int preprocess_partials(int W, int H);
 hipError_t launch_preprocess(int W, int H, const uint8_t* rgb, const uint16_t* depth,

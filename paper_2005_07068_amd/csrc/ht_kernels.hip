@@ -1,16 +1,15 @@
-// Evaluation kernels: observation packing, forward kinematics prologue, work scheduling,
+// Evaluation kernels: observation packing, forward kinematics prologue,
 // persistent ray cast + Eq. 4 cost terms + reduction (with the optional adjoint), finalize.
 //
 // Work decomposition: an 8x8 pixel tile is one wavefront (64 lanes, one pixel each).  The
 // primitives of a particle are culled per tile by their conservative screen boxes with a
 // ballot; tiles that no primitive touches render the background, whose cost terms are
-// summed once per observation, so only touched tiles are visited.  A work item is a run of
-// `tiles_per_item` touched-rectangle tiles of one particle; persistent workgroups of four
-// wavefronts dequeue items, stage the particle's primitive table in LDS and write one
-// partial per item, which the finalize kernel combines in item order (deterministic).  The
-// clamped depth sum is accumulated in FP64: its FP32 per-pixel terms are multiples of
-// 2^-15 mm (depths of at least 256 mm), so the sum is exact and the cost does not depend on
-// how the tiles were split into items.
+// summed once per observation, so only touched tiles are visited.  A work item is a particle or
+// one of the equal parts it is split into; persistent workgroups of four wavefronts stage the
+// particle's primitive tables in LDS and write its cost, or one partial per part, which the
+// finalize kernel combines in part order (deterministic).  The clamped depth sum is accumulated
+// in FP64: its FP32 per-pixel terms are multiples of 2^-15 mm (depths of at least 256 mm), so
+// the sum is exact and the cost does not depend on how the tiles were split.
 #include <float.h>
 #include <math.h>
 
@@ -30,6 +29,13 @@ __device__ __forceinline__ float fast_sqrt(float x) { return __builtin_amdgcn_sq
 template <class T>
 __device__ __forceinline__ const __attribute__((address_space(1))) T* global_ptr(const T* p) {
   return (const __attribute__((address_space(1))) T*)p;
+}
+
+// A wave-uniform address of memory that this kernel does not write: read with scalar loads
+// into scalar registers.
+template <class T>
+__device__ __forceinline__ const __attribute__((address_space(4))) T* scalar_ptr(const T* p) {
+  return (const __attribute__((address_space(4))) T*)p;
 }
 
 __device__ __forceinline__ float wave_sum(float v) {
@@ -94,6 +100,11 @@ __device__ __forceinline__ int wave_max(int v) {
   for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
   return v;
 }
+
+// Work queues of the ray cast (below) and the ints between two queues' counters (1 KB).
+constexpr int kQueues = 8;
+constexpr int kQueueStride = 256;
+static_assert(kQueues * kQueueStride == kCounterInts, "room for the counters of one launch");
 
 // C = A * B for 3x4 affine transforms (row-major, implicit last row 0 0 0 1).
 __device__ inline void mul34(const double* A, const double* B, double* C) {
@@ -207,17 +218,29 @@ hipError_t launch_pack_observation(const uint16_t* depth, const uint8_t* skin, i
 }
 
 // ------------------------------------------------------------------------------------
-// work list, built by one workgroup (kSchedBlock threads, kSchedSmall for launches of at most
-// kSchedSmall particles, whose barriers then wait on 4 wavefronts instead of 16).  The tiles
-// per work item are
-// chosen from the launch's actual tile count: about kItemsPerGroup items per persistent
-// workgroup (more, smaller items measured slower: each item stages its particle's tables),
-// a multiple of the wavefronts per workgroup, at least kFloorTilesFwd (kFloorTilesGrad for
-// a gradient) and at most the configured tiles_per_item (itself >= kMinTilesPerItem, which
+// work list of a gradient launch of more than kSelfSched particles, built by one workgroup.
+// Which tiles a wrench sum takes together is part of a gradient's bits (the rows are FP32
+// sums), and the accept decisions of the refinement hang on them, so the items of a gradient
+// launch are fixed by its particles and a nominal grid (a.list_grid), whatever executes them:
+// about one item per nominal workgroup, a multiple of the wavefronts per workgroup, at least
+// kFloorTiles tiles and at most the configured tiles_per_item (itself >= kMinTilesPerItem, which
 // sizes the workspace).  An exclusive scan of the per-particle item counts then gives the
-// item -> particle map, and the dequeue counter is reset here (no memset: graph-capturable).
+// item -> particle map.
 
-constexpr int kItemsPerGroup = 1;
+constexpr int kFloorTiles = 8;       // 16 left a 32-particle gradient launch at 22.5 us (19.2)
+
+// Tiles per item of a list of total_tiles tiles.
+__device__ __forceinline__ int tiles_per_item(const EvalArgs& a, int total_tiles) {
+  int tq = (total_tiles + a.list_grid - 1) / a.list_grid;
+  tq = (tq + kWavesPerBlock - 1) / kWavesPerBlock * kWavesPerBlock;
+  return max(min(kFloorTiles, a.tiles_per_item), min(tq, a.tiles_per_item));
+}
+
+// Items of about equal work: a list of at most two items per nominal workgroup has nothing to
+// even out its items' different costs, so each particle's items take interleaved tiles.
+__device__ __forceinline__ bool interleaved(const EvalArgs& a, int total_items) {
+  return total_items <= 2 * a.list_grid;
+}
 
 // Inclusive scan over the workgroup; every thread gets its own prefix and the total: a scan
 // within each wavefront by lane shifts, then the wavefront totals through LDS (two barriers
@@ -274,7 +297,6 @@ __device__ int block_scan(int* s_sum, int v, int* total) {
 // latencies overlap (the counts were written by every XCD, so each load misses this L2).
 constexpr int kSchedBatch = 8;
 constexpr int kSchedBlock = 1024;    // threads of the work-list kernel (its only workgroup)
-constexpr int kSchedSmall = 256;     // ... for launches of at most this many particles
 constexpr int kSchedWindow = 8192;   // items staged in LDS per round (32 KB)
 
 // Workspace particle holding the kinematics of evaluated particle r (itself, or its source
@@ -320,9 +342,9 @@ __device__ __forceinline__ void batch_tiles(const EvalArgs& a, const Workspace& 
   }
 }
 
-template <int BLOCK>
-__device__ void schedule_items(const EvalArgs& a, int n_total, const Workspace& ws) {
-  constexpr int kNW = BLOCK / kWave;
+__global__ __launch_bounds__(kSchedBlock) void sched_kernel(EvalArgs a, Workspace ws) {
+  constexpr int BLOCK = kSchedBlock, kNW = BLOCK / kWave;
+  const int n_total = a.n_frames * a.n_particles;
   __shared__ int s_sum[kNW];
   const int t = threadIdx.x;
   const int chunk = (n_total + BLOCK - 1) / BLOCK;
@@ -344,12 +366,7 @@ __device__ void schedule_items(const EvalArgs& a, int n_total, const Workspace& 
   __shared__ int2 s_sum2[kNW];
   int total_tiles, total_evaluated;
   block_scan2<kNW>(s_sum2, tiles, evaluated, &total_tiles, &total_evaluated);
-  const long long target = (long long)a.grid * kItemsPerGroup;
-  long long tq = ((long long)total_tiles + target - 1) / target;
-  tq = (tq + kWavesPerBlock - 1) / kWavesPerBlock * kWavesPerBlock;
-  // a gradient item also writes and its finalize re-reads a wrench per segment: longer items
-  const long long lo = a.grad ? (long long)kFloorTilesGrad : (long long)kFloorTilesFwd;
-  const int tpi = (int)max(min(lo, (long long)a.tiles_per_item), min(tq, (long long)a.tiles_per_item));
+  const int tpi = tiles_per_item(a, total_tiles);
 
   int local = 0;
   for (int i0 = b; i0 < e; i0 += kSchedBatch) {
@@ -406,16 +423,12 @@ __device__ void schedule_items(const EvalArgs& a, int n_total, const Workspace& 
     __syncthreads();
   }
   if (t == 0) {
-    if (a.eval_count) atomicAdd(&a.eval_count[a.grad ? 1 : 0], (unsigned long long)total_evaluated);
+    if (a.eval_count)
+      atomicAdd(&a.eval_count[kCountSlots], (unsigned long long)total_evaluated);
     ws.item_off[n_total] = total_items;
-    ws.counters[0] = 0;
-    ws.counters[1] = total_items;
-    ws.counters[2] = tpi;
-    // a gradient launch with at most about two items per persistent workgroup has nothing to
-    // even out its items' different costs (and its tiles are the heavier ones), so each
-    // particle's items take interleaved tiles of about equal work; elsewhere runs of
-    // consecutive tiles measured faster (the dequeue balances larger launches)
-    ws.counters[3] = a.grad && total_items <= 2 * a.grid ? 1 : 0;
+    ws.list[0] = total_items;
+    ws.list[1] = tpi;
+    ws.list[2] = interleaved(a, total_items) ? 1 : 0;
   }
 }
 
@@ -521,6 +534,8 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
   const bool active = p < n_total;
   const int n_dof = a.n_dof, n_seg = a.n_seg, n_prim = a.n_prim;
   const DevModel* __restrict__ G = a.model;
+  // the work queues' counters of the ray cast that follows, and of one that reuses its tables
+  if (blockIdx.x == 0 && threadIdx.x < 2 * kQueues) ws.counters[threadIdx.x * kQueueStride] = 0;
   // Every load that depends on the particle alone is issued first, together and with clamped
   // indices (a load behind a branch, or issued after another whose result is awaited, adds a
   // memory latency to this latency-bound kernel): this lane's pose parameter, the frame's
@@ -557,6 +572,30 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
   __shared__ int s_fin[kWavesPerBlock];
   PrimIn pin0;
   if (active && lane + h * kWave < n_prim) load_prim(G, lane + h * kWave, pin0);
+  if (a.frame_stop || a.active) {
+    // (after the loads above were issued)  A workgroup whose particles are all skipped (stopped frames, candidates of stopped refined
+    // particles) writes their headers and is done: a frozen swarm's generation takes 2 us here
+    // instead of 3.5
+    bool all = true;
+#pragma unroll
+    for (int j = 0; j < kPpb; ++j) {
+      const int q = min((int)blockIdx.x * kPpb + j, n_total - 1);
+      const bool stop = a.frame_stop && scalar_ptr(a.frame_stop)[q / a.n_particles] != 0;
+      const bool off = a.active && scalar_ptr(a.active)[q / a.active_div] == 0;
+      all &= stop || off;
+    }
+    if (all) {
+      const int q = blockIdx.x * kPpb + threadIdx.x;
+      if ((int)threadIdx.x < kPpb && q < n_total) {
+        PInfo pi{};
+        pi.slot = a.frame_slots[q / a.n_particles];
+        pi.skip = 1;
+        ws.pinfo[q] = pi;
+        ws.tiles[q] = -1;
+      }
+      return;
+    }
+  }
 
   // every angle's sine and cosine at once (one lane per pose parameter, n_dof <= 64), so the
   // tree walk below is trigonometry-free
@@ -641,7 +680,7 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
     W0[9] = Rzy[7] * cx + Rzy[8] * sx;
     W0[10] = -Rzy[7] * sx + Rzy[8] * cx;
     W0[11] = hq[2];
-    if (root == lane) {
+    if (a.adjoint && root == lane) {
       // wrist dofs: translations along camera axes; rotations about Rz Ry e_x, Rz e_y, e_z
       // through the wrist position
       float* df = ws.dof_frame + ((size_t)p * n_dof + b) * 8;
@@ -675,7 +714,7 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
     const int dof1 = M.seg_dof[lane][0], dof2 = M.seg_dof[lane][1];
     for (int j = 0; j < 2; ++j) {
       const int dof = j ? dof2 : dof1;
-      if (dof < 0) continue;
+      if (dof < 0 || !a.adjoint) continue;
       double v[3] = {M.seg_axis[lane][j][0], M.seg_axis[lane][j][1], M.seg_axis[lane][j][2]};
       if (j == 0 && dof2 >= 0) {
         // Rot(a2, q2)^T v = c v - s (a2 x v) + (1 - c)(a2 . v) a2
@@ -694,11 +733,9 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
       }
       f[7] = 0.0f;
     }
-    float* so = ws.seg_org + ((size_t)p * n_seg + lane) * 4;
-    so[0] = (float)T[3];
-    so[1] = (float)T[7];
-    so[2] = (float)T[11];
-    so[3] = 0.0f;
+    if (a.adjoint)
+      reinterpret_cast<float4*>(ws.seg_org)[(size_t)p * n_seg + lane] =
+          make_float4((float)T[3], (float)T[7], (float)T[11], 0.0f);
   }
   // collision terms of Eq. 5, one per spare lane (summed in order below)
   __shared__ double s_kc[kWavesPerBlock][HT_MAX_KC];
@@ -721,6 +758,8 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
   __syncthreads();
   if (valid) {
     const FrameSlot fs = a.slots[slot];
+    const Tables L(n_prim);
+    float4* tab = ws.tables + (size_t)p * L.words;
     for (int o = lane + h * kWave; o < n_prim; o += kWave * WPP) {
       PrimIn pin;
       if (o == lane + h * kWave) pin = pin0;
@@ -803,7 +842,7 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
           rec[18] = rec[11] * fs.sz;
         }
       }
-      float4* dst = reinterpret_cast<float4*>(ws.recs + ((size_t)p * n_prim + k) * kRec);
+      float4* dst = tab + k * (kRec / 4);
       for (int i = 0; i < kRec / 4; ++i)
         dst[i] = make_float4(rec[4 * i], rec[4 * i + 1], rec[4 * i + 2], rec[4 * i + 3]);
 
@@ -924,10 +963,10 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
           capr = make_float2(vv > 0.0f ? fast_rcp(vv) : 0.0f, reach * reach);
         }
       }
-      ws.caps[(size_t)p * n_prim + k] = cap;
-      ws.capr[(size_t)p * n_prim + k] = capr;
+      tab[L.cap + k] = cap;
+      reinterpret_cast<float2*>(tab + L.capr)[k] = capr;
       if (box.x > box.y || box.z > box.w) box = make_int4(1, 0, 1, 0);
-      ws.boxes[(size_t)p * n_prim + k] = box;
+      reinterpret_cast<int4*>(tab + L.box)[k] = box;
       if (box.x <= box.y) {
         int* rq = s_rect[pb][pin.root];
         atomicMin(rq + 0, box.x);
@@ -960,6 +999,21 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
     pi.kc_mask = kc_mask;
     pi.bg_td = bg_td;
     pi.bg_or = bg_or;
+    if (slot_ok) {
+      const FrameSlot& fs = a.slots[slot];
+      pi.TW = fs.TW;
+      pi.W = fs.W;
+      pi.bg = fs.bg;
+      pi.sx = fs.sx;
+      pi.sy = fs.sy;
+      pi.sz = fs.sz;
+      pi.cx = fs.cx;
+      pi.cy = fs.cy;
+      pi.words = fs.words;
+      pi.tile_td = fs.tile_td;
+      pi.tile_skin = fs.tile_skin;
+      pi.grad_mask = fs.grad_mask;
+    }
     // one tile rectangle per tree, as (x0, y0, x1, y1) inclusive; overlapping ones are merged
     // (into the lower index) so that no tile is visited twice.  Every index below is a
     // compile-time constant, so the rectangles stay in registers.
@@ -1015,14 +1069,6 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
       ws.tiles[p] = skip ? -1 : nt;
     }
   }
-}
-
-// The work list is built by its own one-workgroup launch: folding it into the kinematics
-// kernel as "the last workgroup to finish builds it" needs a device-scope fence in every
-// workgroup, which on a multi-XCD part (one L2 per XCD) costs far more than a launch.
-template <int BLOCK>
-__global__ __launch_bounds__(BLOCK) void sched_kernel(EvalArgs a, Workspace ws) {
-  schedule_items<BLOCK>(a, a.n_frames * a.n_particles, ws);
 }
 
 // ------------------------------------------------------------------------------------
@@ -1404,52 +1450,21 @@ __device__ __forceinline__ void ecylinder_test(const float* r, float dx, float d
 // bookkeeping runs on the scalar unit and holds no vector registers
 
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
-__device__ __forceinline__ float uni(float x) {
-  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
-}
-template <class T>
-__device__ __forceinline__ T* uni(T* x) {
-  const uint64_t v = reinterpret_cast<uint64_t>(x);
-  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
-  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
-  return reinterpret_cast<T*>(((uint64_t)hi << 32) | lo);
-}
-
-__device__ __forceinline__ FrameSlot uni(const FrameSlot& f) {
-  FrameSlot u;
-  u.W = uni(f.W);
-  u.H = uni(f.H);
-  u.TW = uni(f.TW);
-  u.TH = uni(f.TH);
-  u.sx = uni(f.sx);
-  u.sy = uni(f.sy);
-  u.sz = uni(f.sz);
-  u.cx = uni(f.cx);
-  u.cy = uni(f.cy);
-  u.fx = uni(f.fx);
-  u.fy = uni(f.fy);
-  u.bg = uni(f.bg);
-  u.set = uni(f.set);
-  u.words = uni(f.words);
-  u.tile_td = uni(f.tile_td);
-  u.tile_skin = uni(f.tile_skin);
-  u.totals = uni(f.totals);
-  u.grad_mask = uni(f.grad_mask);
-  return u;
-}
-
 // Walks a particle's tiles (the union of its rectangles, each row-major) in steps of the
 // number of wavefronts per workgroup, without a division per tile.
+using PInfoPtr = const __attribute__((address_space(4))) PInfo*;
+
 struct TileWalk {
-  const PInfo* pi;
+  PInfoPtr pi;
   int n, ri, rx, ry, rw, rh, ox, oy;
 
   __device__ void load(int r) {
-    const int4 rc = pi->rect[r];
-    rx = uni(rc.x);
-    ry = uni(rc.y);
-    rw = uni(rc.z);
-    rh = uni(rc.w);
+    const __attribute__((address_space(4))) int* q =
+        (const __attribute__((address_space(4))) int*)pi + 4 * r;   // rect is the first member
+    rx = q[0];
+    ry = q[1];
+    rw = q[2];
+    rh = q[3];
   }
   // position at tile t of the union
   __device__ void seek(int t) {
@@ -1460,9 +1475,9 @@ struct TileWalk {
     oy = t / rw;
     ox = t - oy * rw;
   }
-  __device__ void start(const PInfo* p, int t) {
+  __device__ void start(PInfoPtr p, int t) {
     pi = p;
-    n = uni(p->n_rects);
+    n = p->n_rects;
     ri = 0;
     load(0);
     seek(t);
@@ -1486,11 +1501,11 @@ struct TileWalk {
 // ------------------------------------------------------------------------------------
 // persistent ray cast + cost terms + reduction
 
-// Workgroups are dispatched to the chip's 8 XCDs round-robin (workgroup b on XCD b mod 8), each
-// XCD with its own L2.  The first item of workgroup b is taken XCD-major: XCD x's workgroups
-// take the x-th eighth of the items in order, so the consecutive items of one particle (and
-// its staged tables) stay on one XCD instead of spreading over all eight.  A bijection of
-// 0 .. G-1 for any grid size G.
+// Work items.  A launch of fewer particles than resident workgroups splits every particle into
+// equal parts, one item per workgroup (the host chooses parts = resident workgroups / particles,
+// rounded down).  Workgroups are dispatched to the chip's 8 XCDs round-robin (workgroup b on XCD
+// b mod 8), each XCD with its own L2; an item is taken XCD-major, so that the parts of one
+// particle (and the tables they stage) stay on one XCD.  A bijection of 0 .. G-1.
 constexpr int kXcds = 8;
 __device__ __forceinline__ int xcd_major_item(int b, int G) {
   const int q = G / kXcds, rem = G % kXcds;
@@ -1498,185 +1513,236 @@ __device__ __forceinline__ int xcd_major_item(int b, int G) {
   return x * q + min(x, rem) + j;
 }
 
-// Launches of at most kSelfSched particles build their work list in every ray-cast workgroup
-// (no work-list launch before them): one thread per particle reads its tile count, two block
-// scans give the item size (the work-list kernel's rule) and the item offsets in LDS, and the
-// workgroups take items in a static stride of the grid size (the items are sized to about
-// one per workgroup, so there is nothing to balance dynamically).  Workgroup 0 stores the
-// offsets for the finalize and refinement kernels and adds the launch's evaluations to the
-// counts.
-constexpr int kSelfSched = kBlock;
-static_assert(kSelfSched == kSelfSchedMax, "one thread per particle of a self-scheduled launch");
+// A larger launch takes whole particles, from kQueues queues, one per XCD: queue q holds the
+// particles r with r mod kQueues = q (every frame of a batch is spread over all queues) and is
+// worked off by the workgroups b with b mod kQueues = q.  A workgroup's first particle follows
+// from its index, later ones come from its queue's counter.  Nothing but speed depends on
+// where a workgroup runs.  (A static stride left the launch waiting on its slowest workgroup:
+// 65536 poses of a 320x240 frame 3.42 ms against 2.75 ms; one counter for the launch cost about
+// 20 ns per item, one after another on the one address: 4096 poses of 64 uneven frames 119 us
+// against 99 us.)
 
-__device__ void self_schedule(const EvalArgs& a, const Workspace& ws, int* s_off, int& total,
-                              int& tpi, bool& interleave) {
-  __shared__ int2 s_sum2[kWavesPerBlock];
-  __shared__ int s_sum[kWavesPerBlock];
-  const int n_total = a.n_frames * a.n_particles;
-  const int t = threadIdx.x;
-  const int v = t < n_total ? ws.tiles[src_of(a, min(t, n_total - 1))] : -1;
-  int total_tiles, total_evaluated;
-  block_scan2<kWavesPerBlock>(s_sum2, max(v, 0), v >= 0 ? 1 : 0, &total_tiles,
-                              &total_evaluated);
-  const long long target = (long long)a.grid * kItemsPerGroup;
-  long long tq = ((long long)total_tiles + target - 1) / target;
-  tq = (tq + kWavesPerBlock - 1) / kWavesPerBlock * kWavesPerBlock;
-  const long long lo = a.grad ? (long long)kFloorTilesGrad : (long long)kFloorTilesFwd;
-  tpi = (int)max(min(lo, (long long)a.tiles_per_item), min(tq, (long long)a.tiles_per_item));
-  const int items = (max(v, 0) + tpi - 1) / tpi;
-  int total_items;
-  const int incl = block_scan<kWavesPerBlock>(s_sum, items, &total_items);
-  if (t < n_total) s_off[t + 1] = incl;
-  if (t == 0) s_off[0] = 0;
-  __syncthreads();
-  total = total_items;
-  // items in a static stride, about one per workgroup: interleaved tiles, so that every item
-  // samples the whole hand (runs of consecutive tiles left the launch waiting on the items
-  // from the hand's middle: 128 forward candidates 26.7 -> 24.1 us)
-  interleave = total_items <= 2 * a.grid;
-  if (blockIdx.x == 0) {
-    // n_total + 1 offsets: one per thread, the end offset by thread 0
-    if (t < n_total) ws.item_off[t] = s_off[t];
-    if (t == 0) {
-      ws.item_off[n_total] = total_items;
-      if (a.eval_count)
-        atomicAdd(&a.eval_count[a.grad ? 1 : 0], (unsigned long long)total_evaluated);
-      ws.counters[1] = total_items;
-      ws.counters[2] = tpi;
-      ws.counters[3] = interleave ? 1 : 0;
+// Gradient launches of at most kSelfSched particles build their work list in every wavefront of
+// the ray cast (no work-list launch, no barrier): lane l holds the tile counts of particles
+// 4l .. 4l + 3, two wavefront sums and a scan give the items.  Workgroup 0 stores the item
+// offsets for the kernels that assemble the evaluation and adds the launch's evaluations to the
+// counts.
+constexpr int kSelfSched = 4 * kWave;
+static_assert(kSelfSched == kSelfSchedMax, "four particles per lane");
+
+struct WaveList {
+  int off;       // offset of the lane's first particle's items
+  int cnt[4];    // items of the lane's particles
+  int total, tpi;
+  bool interleave;
+
+  __device__ void build(const EvalArgs& a, const Workspace& ws, int lane) {
+    const int n = a.n_frames * a.n_particles;
+    int v[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) v[j] = ws.tiles[src_of(a, min(4 * lane + j, n - 1))];
+    int tiles = 0, evaluated = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      v[j] = 4 * lane + j < n ? v[j] : -1;
+      tiles += max(v[j], 0);
+      evaluated += v[j] >= 0 ? 1 : 0;
+    }
+    tiles = uni(wave_sum(tiles));
+    tpi = tiles_per_item(a, tiles);
+    int mine = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      cnt[j] = (max(v[j], 0) + tpi - 1) / tpi;
+      mine += cnt[j];
+    }
+    int incl = mine;
+#pragma unroll
+    for (int o = 1; o < kWave; o <<= 1) {
+      const int u = __shfl_up(incl, o);
+      if (lane >= o) incl += u;
+    }
+    off = incl - mine;
+    total = __builtin_amdgcn_readlane(incl, kWave - 1);
+    interleave = interleaved(a, total);
+    if (blockIdx.x == 0 && threadIdx.x < kWave) {
+      int o = off;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        if (4 * lane + j < n) ws.item_off[4 * lane + j] = o;
+        o += cnt[j];
+      }
+      evaluated = wave_sum(evaluated);
+      if (lane == 0) {
+        ws.item_off[n] = total;
+        if (a.eval_count)
+          atomicAdd(&a.eval_count[kCountSlots], (unsigned long long)evaluated);
+      }
     }
   }
+  // the evaluated particle of an item, its first item and item count (wave-uniform)
+  __device__ __forceinline__ int find(int item, int& first, int& n_it) const {
+    int o = off, r = 0;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const uint64_t m = __builtin_amdgcn_ballot_w64(o <= item) &
+                         __builtin_amdgcn_ballot_w64(item < o + cnt[j]);
+      if (m) {
+        const int l = __builtin_ctzll(m);
+        r = 4 * l + j;
+        first = __builtin_amdgcn_readlane(o, l);
+        n_it = __builtin_amdgcn_readlane(cnt[j], l);
+      }
+      o += cnt[j];
+    }
+    return r;
+  }
+};
+
+// Items that a workgroup of a larger gradient launch takes from its queue at a time: consecutive
+// ones, so that most of them need no new tables.
+constexpr int kRunItems = 4;
+
+// Tiles of a part: part q of a particle split into n parts takes tiles t with
+// (t / kWavesPerBlock) mod n = q, wavefront w of its workgroup those with t mod kWavesPerBlock
+// = w, so every part samples the whole hand and carries about equal work.  Parts past the
+// particle's tiles do nothing; the others' partials are read by the kernel that assembles the
+// evaluation.
+__device__ __forceinline__ int active_parts(int n_tiles, int parts) {
+  return min(parts, max((n_tiles + kWavesPerBlock - 1) / kWavesPerBlock, 1));
 }
 
-// The evaluated particle r of item i in a self-scheduled launch: s_off[r] <= i < s_off[r + 1]
-// (a binary search over the LDS offsets; wave-uniform).
-__device__ __forceinline__ int self_item_particle(const int* s_off, int n_total, int i) {
-  int lo = 0, hi = n_total;   // s_off[lo] <= i < s_off[hi]
-  while (hi - lo > 1) {
-    const int mid = (lo + hi) >> 1;
-    if (uni(s_off[mid]) <= i) lo = mid;
-    else hi = mid;
+// Eq. 4-5 from the sums (FP64).
+__device__ inline float cost_from_sums(double S_d, long long S_and, long long S_or, float kc) {
+  double D;
+  if (S_or == 0) {
+    D = kLambda;
+  } else {
+    D = S_d / (double)S_or + kLambda * (1.0 - 2.0 * (double)S_and / (double)(S_and + S_or));
   }
-  return lo;
+  return (float)(D + kLambdaK * (double)kc);
 }
 
 // NT: primitive types the model uses (3: spheres, cylinders, ellipsoids; kNumTypes: also
 // cones and elliptic cylinders), so a model without the latter keeps the smaller register
 // footprint.  (Forcing more wavefronts per SIMD than the vector register count allows
-// spills vector registers and measured slower.)  SELF: the launch builds its own work list (at most
-// kSelfSched particles, no debug images); a variant of its own, so the larger launches keep
-// the dequeue loop without the self-scheduling code (which cost them about 5%).
-//
-// The work-list launches of the plain forward cast ask for eight wavefronts per SIMD: left to
-// itself the compiler needs more scalar registers than eight allow (seven fit), and the few
-// it then keeps in vector-register lanes are reloaded per item, outside the tile loop
-// (1.2 % off the two-hand frame; the self-scheduled launches, at most six workgroups per
-// CU, measured slower with the same request).
+// spills vector registers and measured slower.)
 template <bool GRAD, bool DEBUG, int NT, bool SELF>
 __global__ __attribute__((amdgpu_flat_work_group_size(1, kBlock),
-                          amdgpu_waves_per_eu((GRAD || DEBUG || SELF) ? 1 : 8)))
+                          amdgpu_waves_per_eu((GRAD || DEBUG) ? 1 : 8)))
 void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
-  __shared__ float4 s_rec[HT_MAX_PRIM * (kRec / 4)];
-  __shared__ int4 s_box[HT_MAX_PRIM];
-  __shared__ float4 s_cap[HT_MAX_PRIM];
-  __shared__ float2 s_capr[HT_MAX_PRIM];
-  __shared__ int s_item;
-  __shared__ PInfo s_pi;
-  __shared__ double s_td[kWavesPerBlock];
-  __shared__ int s_a[kWavesPerBlock], s_o[kWavesPerBlock];
-  // gradient: per wavefront, segment and 16-lane row, the six wrench components of the item
-  __shared__ float s_wr[GRAD ? kWavesPerBlock : 1][GRAD ? HT_MAX_SEG : 1][GRAD ? 4 : 1][6];
+  static_assert(!(GRAD && DEBUG) && !(SELF && !GRAD), "forward, debug or gradient");
+  // the particle's tables, then (gradient) the wrench rows: per wavefront, segment and 16-lane
+  // row the six wrench components of the item
+  extern __shared__ float4 s_tab[];
+  __shared__ int s_next[2];
+  __shared__ double s_td[2][kWavesPerBlock];
+  __shared__ int s_a[2][kWavesPerBlock], s_o[2][kWavesPerBlock];
 
   // the wavefront index as a scalar, so that the tile walk, the tile's coordinates and the
   // observation addresses are wave-uniform (scalar instructions)
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int n_prim = a.n_prim, n_seg = a.n_seg;
-  static_assert(!(SELF && DEBUG), "debug launches take the work-list kernel");
-  constexpr bool self = SELF;
-  __shared__ int s_off[SELF ? kSelfSched + 1 : 1];
-  int total, tpi;
-  bool interleave;
-  if constexpr (SELF) {
-    self_schedule(a, ws, s_off, total, tpi, interleave);
-  } else {
-    total = uni(ws.counters[1]);
-    tpi = uni(ws.counters[2]);
-    interleave = uni(ws.counters[3]) != 0;
+  const Tables L(n_prim);
+  const int4* s_box = reinterpret_cast<const int4*>(s_tab + L.box);
+  const float4* s_cap = s_tab + L.cap;
+  const float2* s_capr = reinterpret_cast<const float2*>(s_tab + L.capr);
+  float* s_wr = reinterpret_cast<float*>(s_tab + L.words);   // [wave][seg][row][6]
+  const float* recs = reinterpret_cast<const float*>(s_tab);
+  const int parts = a.parts;
+  const int G = gridDim.x, n_eval = a.n_frames * a.n_particles;
+  // Forward: whole particles from the queues, or the particle's parts, one per workgroup.
+  // Gradient: the work list's items, in runs of consecutive ones (SELF: an equal share of the
+  // list per workgroup, else kRunItems at a time from the queues).
+  WaveList list;
+  if constexpr (GRAD && SELF) {
+    list.build(a, ws, lane);
+  } else if constexpr (GRAD) {
+    list.total = scalar_ptr(ws.list)[0];
+    list.tpi = scalar_ptr(ws.list)[1];
+    list.interleave = scalar_ptr(ws.list)[2] != 0;
   }
-  const int n_eval = a.n_frames * a.n_particles;
+  const int units = GRAD ? (SELF ? G : (list.total + kRunItems - 1) / kRunItems) : n_eval;
+  const bool queued = units > G;
+  const int queue = blockIdx.x % kQueues;
+  // workgroups of this queue, and the units it holds
+  const int groups = (G - queue + kQueues - 1) / kQueues;
+  const int held = (units - queue + kQueues - 1) / kQueues;
+  int* counter = ws.counters + (a.src ? kCounterInts : 0) + queue * kQueueStride;
+  int n_counted = 0;
   int cur_p = -1;
-  FrameSlot fs{};
   // the lane's pixel offset within a tile as a ray component: ((lane & 7) - cx) sx and
   // ((lane >> 3) - cy) sy, so that a tile's rays cost one multiply-add per component
   float lane_dx = 0.0f, lane_dy = 0.0f;
-  const PInfo& pi = s_pi;
 
-  // the first item of every workgroup is its own index; later ones come from the dequeue
-  // counter (offset by the grid size), so the launch does not start with one atomic per
-  // workgroup on a single address (which stalls the memory channel that holds it)
-  bool first = true;
-  int item = 0;
-  for (;;) {
-    if (first) {
-      item = xcd_major_item(blockIdx.x, gridDim.x);
-      first = false;
-    } else if constexpr (SELF) {
-      // the next item in the static stride; the barrier keeps its per-wavefront LDS sums
-      // clear of the previous item's (whose readers may still be at work when both items
-      // belong to one particle and so no staging barrier follows)
-      item += gridDim.x;
-      __syncthreads();
+  int unit = queued ? (int)blockIdx.x / kQueues : xcd_major_item(blockIdx.x, G);
+  const int end = queued ? held : (GRAD ? units : n_eval * parts);
+  int buf = 0;
+  while (unit < end) {
+    // the next unit is taken now, so that the atomic's latency passes under this one's work
+    int next = end;
+    if (queued && tid == 0) next = groups + atomicAdd(counter, 1);
+    int item = 0, item_end = 1, part = 0, r = 0;
+    if constexpr (GRAD) {
+      const int q = queued ? unit * kQueues + queue : unit;
+      item = SELF ? (int)((long long)list.total * q / G) : q * kRunItems;
+      item_end = SELF ? (int)((long long)list.total * (q + 1) / G)
+                      : min(item + kRunItems, list.total);
     } else {
-      if (tid == 0) s_item = (int)gridDim.x + atomicAdd(&ws.counters[0], 1);
-      __syncthreads();
-      item = uni(s_item);
-      __syncthreads();
+      part = queued ? 0 : unit % parts;
+      r = queued ? unit * kQueues + queue : unit / parts;
     }
-    if (item >= total) break;
-    // evaluated particle
-    const int r = self ? self_item_particle(s_off, n_eval, item) : uni(ws.item_map[item]);
+  for (; item < item_end; ++item, buf ^= 1) {
+    // evaluated particle, and for a gradient the item's place among the particle's
+    int first_item = 0, n_it = 1;
+    if constexpr (GRAD && SELF) {
+      r = list.find(item, first_item, n_it);
+    } else if constexpr (GRAD) {
+      r = scalar_ptr(ws.item_map)[item];
+      first_item = scalar_ptr(ws.item_off)[r];
+      n_it = scalar_ptr(ws.item_off)[r + 1] - first_item;
+    }
     const int p = a.src ? uni(src_of(a, r)) : r;   // the workspace particle of its kinematics
-    if (p != cur_p) {
-      const float4* src = reinterpret_cast<const float4*>(ws.recs + (size_t)p * n_prim * kRec);
-      for (int i = tid; i < n_prim * (kRec / 4); i += kBlock) s_rec[i] = src[i];
-      for (int i = tid; i < n_prim; i += kBlock) {
-        s_box[i] = ws.boxes[(size_t)p * n_prim + i];
-        s_cap[i] = ws.caps[(size_t)p * n_prim + i];
-        s_capr[i] = ws.capr[(size_t)p * n_prim + i];
-      }
-      if (tid == 0) s_pi = ws.pinfo[p];
+    const PInfoPtr pi = scalar_ptr(ws.pinfo + p);
+    const int n_tiles = pi->n_tiles;
+    const bool skip = !GRAD && pi->skip != 0;   // (a skipped particle has no gradient items)
+    if (!GRAD && part == 0 && !skip) ++n_counted;
+    const bool on = !skip && (GRAD || part < active_parts(n_tiles, parts));
+    if (on) {
+    if (!GRAD || p != cur_p) {
+      const float4* src = ws.tables + (size_t)p * L.words;
+      for (int i = tid; i < L.words; i += kBlock) s_tab[i] = src[i];
       cur_p = p;
-      __syncthreads();
-      fs = uni(a.slots[uni(s_pi.slot)]);
-      lane_dx = ((float)(lane & 7) - fs.cx) * fs.sx;
-      lane_dy = ((float)(lane >> 3) - fs.cy) * fs.sy;
     }
+    const float f_sx = pi->sx, f_sy = pi->sy, f_sz = pi->sz, f_bg = pi->bg;
+    lane_dx = ((float)(lane & 7) - pi->cx) * f_sx;
+    lane_dy = ((float)(lane >> 3) - pi->cy) * f_sy;
+    const int TW = pi->TW;
+    const uint32_t* words = pi->words;
+    const float* tile_td = pi->tile_td;
+    const int* tile_skin = pi->tile_skin;
     if (GRAD) {
-      float* wr = &s_wr[wave][0][0][0];
+      float* wr = s_wr + wave * n_seg * 24;
       for (int i = lane; i < n_seg * 24; i += kWave) wr[i] = 0.0f;
     }
-    // item c of a particle with n_it items takes tiles c tpi .. (c + 1) tpi - 1, or, when
-    // interleaved, tiles c, c + n_it, c + 2 n_it, ...: then every item samples the whole hand
-    // and carries about equal work (runs of consecutive tiles differed threefold, and a launch
-    // with about one item per workgroup lasts as long as its longest item); wavefront w takes
-    // every fourth of an item's tiles
-    const int off = self ? uni(s_off[r]) : uni(ws.item_off[r]);
-    const int c = item - off;
-    const int n_it = (self ? uni(s_off[r + 1]) : uni(ws.item_off[r + 1])) - off;
-    const int n_tiles = uni(pi.n_tiles);
-    const int first = interleave ? c : c * tpi;
-    const int gap = interleave ? n_it : 1;
-    const int t_end = interleave ? n_tiles : min((c + 1) * tpi, n_tiles);
+    __syncthreads();
+    // tiles t0, t0 + stride, ... below t_end.  Gradient item c of a particle with n_it items:
+    // tiles c tpi .. (c + 1) tpi - 1, or, when interleaved, c, c + n_it, c + 2 n_it, ...;
+    // wavefront w takes every fourth of them
+    const int c = item - first_item;
+    const int gap = GRAD ? (list.interleave ? n_it : 1) : parts;
     const int stride = gap * kWavesPerBlock;
+    const int t0 = GRAD ? (list.interleave ? c : c * list.tpi) + wave * gap
+                        : part * kWavesPerBlock + wave;
+    const int t_end = GRAD && !list.interleave ? min((c + 1) * list.tpi, n_tiles) : n_tiles;
     double acc_td = 0.0;   // exact: the FP32 terms are multiples of 2^-15 mm
     double acc_bg = 0.0;   // the tiles' background depth sums (the same on every lane)
     int acc_a = 0, acc_o = 0;   // wavefront totals: popcounts of lane masks (scalar unit)
-    const float* recs = reinterpret_cast<const float*>(s_rec);
 
     TileWalk walk;
-    walk.start(&pi, first + wave * gap);
-    for (int t = first + wave * gap; t < t_end; t += stride, walk.step(stride)) {
+    if (t0 < t_end) walk.start(pi, t0);
+    for (int t = t0; t < t_end; t += stride, walk.step(stride)) {
       const int tx = walk.tx(), ty = walk.ty();
       const int x0 = tx * kTile, y0 = ty * kTile;
       const float x0f = (float)x0, y0f = (float)y0;
@@ -1716,19 +1782,19 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
       }
       if ((mk[0] | mk[1]) == 0ull) continue;
 
-      const int tile_idx = ty * fs.TW + tx;
+      const int tile_idx = ty * TW + tx;
       const int u = x0 + (lane & 7), v = y0 + (lane >> 3);
-      const uint32_t word = global_ptr(fs.words)[(size_t)tile_idx * kTilePx + lane];
+      const uint32_t word = global_ptr(words)[(size_t)tile_idx * kTilePx + lane];
       // the tile's background sums, loaded with the words (one address for every lane) so
       // that their latency overlaps the tests; lane 0 subtracts them after the tests
-      const float bg_td = global_ptr(fs.tile_td)[tile_idx];
-      const int bg_sk = global_ptr(fs.tile_skin)[tile_idx];
+      const float bg_td = global_ptr(tile_td)[tile_idx];
+      const int bg_sk = global_ptr(tile_skin)[tile_idx];
       const bool valid = (word & kValidBit) != 0;
       const float od = (float)(word & 0xFFFFu);
       const bool os = (word & kSkinBit) != 0;
-      const float dx = fmaf(x0f, fs.sx, lane_dx);
-      const float dy = fmaf(y0f, fs.sy, lane_dy);
-      const float dz = fs.sz;
+      const float dx = fmaf(x0f, f_sx, lane_dx);
+      const float dy = fmaf(y0f, f_sy, lane_dy);
+      const float dz = f_sz;
       const float dd = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
       const float inv_dd = fast_rcp(dd);
       float tmin = INFINITY;
@@ -1776,9 +1842,9 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
       // depth of the nearest entry; behind the background plane it is hidden
       const float zmin = tmin * dz;
       const bool any = (GRAD || DEBUG) ? win >= 0 : __float_as_uint(tmin) < 0x7F800000u;
-      const bool hit = any & !(fs.bg > 0.0f && zmin >= fs.bg);
+      const bool hit = any & !(f_bg > 0.0f && zmin >= f_bg);
       win = hit ? win : -1;
-      const float rd = hit ? zmin : (fs.bg > 0.0f ? fs.bg : 0.0f);
+      const float rd = hit ? zmin : (f_bg > 0.0f ? f_bg : 0.0f);
       const float diff = fabsf(od - rd);
       const float td = fminf(diff, kDClamp);
       const bool rm = hit && (diff < kDMatch || od == 0.0f);
@@ -1812,8 +1878,8 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
         // adjoint: coefficient of the depth term, then the per-segment wrench
         bool act = valid && hit && diff < kDClamp && od != rd;
         // the call's mask (one frame), else the frame's slot mask
-        const uint8_t* gmask = a.pixel_mask ? a.pixel_mask : fs.grad_mask;
-        if (act && gmask) act = global_ptr(gmask)[(size_t)v * fs.W + u] != 0;
+        const uint8_t* gmask = a.pixel_mask ? a.pixel_mask : pi->grad_mask;
+        if (act && gmask) act = global_ptr(gmask)[(size_t)v * pi->W + u] != 0;
         int seg = -1;
         float kap = 0.0f;
         float mx = 0, my = 0, mz = 0;
@@ -1846,7 +1912,7 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
 #pragma unroll
           for (int q = 0; q < 6; ++q) sum[q] = row_total(vals[q]);
           if ((lane & 15) == 0) {
-            float* dst = &s_wr[wave][s][lane >> 4][0];
+            float* dst = s_wr + ((wave * n_seg + s) * 4 + (lane >> 4)) * 6;
 #pragma unroll
             for (int q = 0; q < 6; ++q) atomicAdd(dst + q, sum[q]);
           }
@@ -1856,47 +1922,63 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
 
     acc_td = wave_sum(acc_td) - acc_bg;
     if (lane == 0) {
-      s_td[wave] = acc_td;
-      s_a[wave] = acc_a;
-      s_o[wave] = acc_o;
+      s_td[buf][wave] = acc_td;
+      s_a[buf][wave] = acc_a;
+      s_o[buf][wave] = acc_o;
     }
+    }
+    if (tid == 0) s_next[buf] = next;
     __syncthreads();
-    if (tid == 0) {
-      Partial pr;
-      pr.td = ((s_td[0] + s_td[1]) + s_td[2]) + s_td[3];
-      pr.a = s_a[0] + s_a[1] + s_a[2] + s_a[3];
-      pr.o = s_o[0] + s_o[1] + s_o[2] + s_o[3];
-      pr.pad = 0;
-      ws.partial[item] = pr;
-    }
-    if (GRAD) {
-      for (int i = tid; i < n_seg * 6; i += kBlock) {
-        const int s = i / 6, q = i % 6;
-        float v = 0.0f;
+    if (on) {
+      if (tid == 0) {
+        const double td = ((s_td[buf][0] + s_td[buf][1]) + s_td[buf][2]) + s_td[buf][3];
+        const int sa = s_a[buf][0] + s_a[buf][1] + s_a[buf][2] + s_a[buf][3];
+        const int so = s_o[buf][0] + s_o[buf][1] + s_o[buf][2] + s_o[buf][3];
+        if (!GRAD && a.direct) {
+          // the whole particle: its cost follows here (no finalize launch)
+          a.cost[r] = pi->valid ? cost_from_sums(pi->bg_td + td, sa, (long long)pi->bg_or + so, pi->kc)
+                                : (pi->slot < 0 ? NAN : INFINITY);
+        } else {
+          ws.partial[GRAD ? item : r * parts + part] = Partial{td, sa, so};
+        }
+      }
+      if (GRAD) {
+        for (int i = tid; i < n_seg * 6; i += kBlock) {
+          const int s = i / 6, q = i % 6;
+          float v = 0.0f;
 #pragma unroll
-        for (int w = 0; w < kWavesPerBlock; ++w)
-          v += (s_wr[w][s][0][q] + s_wr[w][s][1][q]) + (s_wr[w][s][2][q] + s_wr[w][s][3][q]);
-        ws.wrench[(size_t)item * n_seg * 6 + i] = v;
+          for (int w = 0; w < kWavesPerBlock; ++w) {
+            const float* c = s_wr + (w * n_seg + s) * 24 + q;
+            v += (c[0] + c[6]) + (c[12] + c[18]);
+          }
+          ws.wrench[(size_t)item * n_seg * 6 + i] = v;
+        }
+        __syncthreads();   // the rows are read before the next item clears them
       }
     }
   }
+    unit = queued ? uni(s_next[buf ^ 1]) : end;
+  }
+  if (!GRAD && tid == 0 && n_counted && a.eval_count)
+    atomicAdd(&a.eval_count[blockIdx.x % kCountSlots], (unsigned long long)n_counted);
 }
 
 // ------------------------------------------------------------------------------------
 // finalize: combine partials in item order, Eq. 4-5, and the kinematic adjoint
 
-// This lane's partial among a particle's first 64 items (items b .. e-1), loaded without a
-// branch: the index is clamped into the buffer and the value is used only when in range.
-__device__ __forceinline__ Partial first_partial(const Workspace& ws, int b, int e, int lane) {
-  return ws.partial[max(min(b + lane, e - 1), 0)];
+// This lane's partial among a particle's first 64 parts (items b .. b + parts - 1), loaded
+// before the number of active parts is known: the index is clamped into the particle's items
+// and the value is used only when its part is active.
+__device__ __forceinline__ Partial first_partial(const Workspace& ws, int b, int parts, int lane) {
+  return ws.partial[b + min(lane, parts - 1)];
 }
 
 // S_d, S_and, S_or of a particle: the ROI's background totals plus its items' partials,
 // summed by the lanes of one wavefront (pr0: this lane's first_partial, loaded early by the
 // caller).  Every depth term is a multiple of 2^-15 mm, so the FP64 sums are exact and equal
 // to any other summation order.
-__device__ inline void wave_partial_sums(const PInfo& pi, const Workspace& ws, int b, int e,
-                                         int lane, const Partial& pr0, double& S_d,
+__device__ inline void wave_partial_sums(double bg_td, double bg_or, const Workspace& ws, int b,
+                                         int e, int lane, const Partial& pr0, double& S_d,
                                          long long& S_and, long long& S_or) {
   const bool in0 = b + lane < e;
   double d = in0 ? pr0.td : 0.0;
@@ -1910,20 +1992,9 @@ __device__ inline void wave_partial_sums(const PInfo& pi, const Workspace& ws, i
   d = wave_sum(d);
   sa = wave_sum(sa);
   so = wave_sum(so);
-  S_d = pi.bg_td + d;
+  S_d = bg_td + d;
   S_and = sa;
-  S_or = (long long)pi.bg_or + so;
-}
-
-// Eq. 4-5 from the sums (FP64).
-__device__ inline float cost_from_sums(double S_d, long long S_and, long long S_or, float kc) {
-  double D;
-  if (S_or == 0) {
-    D = kLambda;
-  } else {
-    D = S_d / (double)S_or + kLambda * (1.0 - 2.0 * (double)S_and / (double)(S_and + S_or));
-  }
-  return (float)(D + kLambdaK * (double)kc);
+  S_or = (long long)bg_or + so;
 }
 
 // Forward: one wavefront per particle.
@@ -1933,14 +2004,14 @@ __global__ __launch_bounds__(kBlock) void finalize_kernel(EvalArgs a, Workspace 
   const int p = blockIdx.x * kWavesPerBlock + __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const int n_total = a.n_frames * a.n_particles;
   if (p >= n_total) return;
-  // the item range and the record are independent loads; the partials are summed before the
-  // record is tested (a skipped or invalid particle has no items), so no branch waits on it
-  const int b = ws.item_off[p], e = ws.item_off[p + 1];
-  const PInfo pi = ws.pinfo[src_of(a, p)];
-  const Partial pr0 = first_partial(ws, b, e, lane);
+  // the header and the first partials are independent loads
+  const int b = p * a.parts;
+  const PInfo& pi = ws.pinfo[src_of(a, p)];
+  const Partial pr0 = first_partial(ws, b, a.parts, lane);
+  const int e = b + active_parts(pi.n_tiles, a.parts);
   double S_d;
   long long S_and, S_or;
-  wave_partial_sums(pi, ws, b, e, lane, pr0, S_d, S_and, S_or);
+  wave_partial_sums(pi.bg_td, pi.bg_or, ws, b, e, lane, pr0, S_d, S_and, S_or);
   if (pi.skip) return;
   if (!pi.valid) {
     if (lane == 0) a.cost[p] = pi.slot < 0 ? NAN : INFINITY;
@@ -1968,7 +2039,7 @@ __global__ __launch_bounds__(kBlock) void finalize_grad_kernel(EvalArgs a, Works
   // threads past n_dof have none).  The record is tested only after the sums below (a skipped
   // or invalid particle has no items), so no branch holds these loads back.
   const int b = ws.item_off[p], e = ws.item_off[p + 1];
-  const PInfo pi = ws.pinfo[ps];
+  const PInfo& pi = ws.pinfo[ps];
   const int j = t, jc = min(t, n_dof - 1);   // loads clamped in bounds, unconditional
   const uint32_t desc = j < n_dof ? a.model->dof_desc[jc] : 0u;
   const float4* f4 = reinterpret_cast<const float4*>(ws.dof_frame + ((size_t)ps * n_dof + jc) * 8);
@@ -1986,7 +2057,7 @@ __global__ __launch_bounds__(kBlock) void finalize_grad_kernel(EvalArgs a, Works
   const int q = __builtin_amdgcn_readfirstlane(t >> 6);   // wave-uniform
   // the first partials, for the second wavefront's cost sums below; loaded by every wavefront
   // (unconditionally, so that no branch waits on them), issued with the wrench loads
-  const Partial pr0 = first_partial(ws, b, e, lane);
+  const Partial pr0 = first_partial(ws, b, max(e - b, 1), lane);
   constexpr int kFinItems = 4;
   double acc[3] = {0.0, 0.0, 0.0};
   for (int i = b + q; i < e; i += kFinItems * kWavesPerBlock) {
@@ -2020,7 +2091,7 @@ __global__ __launch_bounds__(kBlock) void finalize_grad_kernel(EvalArgs a, Works
   static_assert(HT_MAX_DOF <= kWave, "pose parameters fit the first wavefront");
   double S_d = 0.0;
   long long S_and = 0, S_or = 0;
-  if (q == 1) wave_partial_sums(pi, ws, b, e, lane, pr0, S_d, S_and, S_or);
+  if (q == 1) wave_partial_sums(pi.bg_td, pi.bg_or, ws, b, e, lane, pr0, S_d, S_and, S_or);
   if (pi.skip) return;
   if (!pi.valid) {
     if (t == 0) a.cost[p] = pi.slot < 0 ? NAN : INFINITY;
@@ -2105,11 +2176,13 @@ __device__ bool assemble_wave(const EvalArgs& a, const Workspace& ws, int p, boo
   const int lane = threadIdx.x & (kWave - 1);
   const int n_seg = a.n_seg, n_dof = a.n_dof, nv = n_seg * 6;
   const int ps = uni(src_of(a, p));
-  const int b = uni(ws.item_off[p]), e = uni(ws.item_off[p + 1]);
+  // its items: of the work list (gradient), or its parts
+  const int b = grad ? scalar_ptr(ws.item_off)[p] : p * a.parts;
+  const int parts = grad ? max(scalar_ptr(ws.item_off)[p + 1] - b, 1) : a.parts;
   // loads that depend on the particle alone, issued before any branch: the record, the first
   // partials, this lane's pose-parameter frame and segment-origin values (clamped indices)
-  const PInfo pi = ws.pinfo[ps];
-  const Partial pr0 = first_partial(ws, b, e, lane);
+  const PInfoPtr ph = scalar_ptr(ws.pinfo + ps);
+  const Partial pr0 = first_partial(ws, b, parts, lane);
   const int jc = min(lane, n_dof - 1);
   const float4* f4 = reinterpret_cast<const float4*>(ws.dof_frame + ((size_t)ps * n_dof + jc) * 8);
   const float4 f0 = f4[0], f1 = f4[1];
@@ -2117,16 +2190,17 @@ __device__ bool assemble_wave(const EvalArgs& a, const Workspace& ws, int p, boo
   const float* org_src = ws.seg_org + (size_t)ps * n_seg * 4;
   const float o0 = org_src[min(lane, n_seg * 4 - 1)];
   const float o1 = org_src[min(lane + kWave, n_seg * 4 - 1)];
+  g = 0.0f;
+  if (ph->skip) return false;
+  const int e = b + (grad ? (ph->n_tiles ? parts : 0) : active_parts(ph->n_tiles, parts));
   double S_d;
   long long S_and, S_or;
-  wave_partial_sums(pi, ws, b, e, lane, pr0, S_d, S_and, S_or);
-  g = 0.0f;
-  if (pi.skip) return false;
-  if (!pi.valid) {
-    cost = pi.slot < 0 ? NAN : INFINITY;
+  wave_partial_sums(ph->bg_td, ph->bg_or, ws, b, e, lane, pr0, S_d, S_and, S_or);
+  if (!ph->valid) {
+    cost = ph->slot < 0 ? NAN : INFINITY;
     return true;
   }
-  cost = cost_from_sums(S_d, S_and, S_or, pi.kc);
+  cost = cost_from_sums(S_d, S_and, S_or, ph->kc);
   if (!grad) return true;
   // wrench rows summed in item order (lane l: values l, l + 64, l + 128), kAsmItems items'
   // loads in flight at a time (indices clamped into the particle's items; past the end adds
@@ -2193,7 +2267,7 @@ __device__ bool assemble_wave(const EvalArgs& a, const Workspace& ws, int p, boo
         if (has[q]) acc_g += t[q];
     }
     acc_g *= inv_or;
-    for (int m = pi.kc_mask; m; m &= m - 1) {
+    for (int m = ph->kc_mask; m; m &= m - 1) {
       const int i = __builtin_ctz(m);
       if (a.model->kc_a[i] == j) acc_g -= kLambdaK;
       if (a.model->kc_b[i] == j) acc_g += kLambdaK;
@@ -2325,41 +2399,42 @@ hipError_t launch_refine_update(const EvalArgs& a, const Workspace& ws, const Re
 
 // ------------------------------------------------------------------------------------
 
-// The ray-cast variant of a launch.
-template <bool GRAD, int NT>
-static const void* raycast_fn_nt(bool dbg, bool self) {
-  if (dbg) return reinterpret_cast<const void*>(&raycast_kernel<GRAD, true, NT, false>);
-  return self ? reinterpret_cast<const void*>(&raycast_kernel<GRAD, false, NT, true>)
-              : reinterpret_cast<const void*>(&raycast_kernel<GRAD, false, NT, false>);
+// The ray-cast variant of a launch, and its LDS bytes (the tables, and a gradient's wrench rows).
+template <int NT>
+static const void* raycast_fn_nt(bool grad, bool dbg, bool self) {
+  if (grad)
+    return self ? reinterpret_cast<const void*>(&raycast_kernel<true, false, NT, true>)
+                : reinterpret_cast<const void*>(&raycast_kernel<true, false, NT, false>);
+  return dbg ? reinterpret_cast<const void*>(&raycast_kernel<false, true, NT, false>)
+             : reinterpret_cast<const void*>(&raycast_kernel<false, false, NT, false>);
 }
 
 static const void* raycast_fn(bool grad, bool dbg, bool all_types, bool self) {
-  if (all_types)
-    return grad ? raycast_fn_nt<true, kNumTypes>(dbg, self)
-                : raycast_fn_nt<false, kNumTypes>(dbg, self);
-  return grad ? raycast_fn_nt<true, 3>(dbg, self) : raycast_fn_nt<false, 3>(dbg, self);
+  return all_types ? raycast_fn_nt<kNumTypes>(grad, dbg, self) : raycast_fn_nt<3>(grad, dbg, self);
+}
+
+static size_t raycast_lds(bool grad, int n_prim, int n_seg) {
+  return (size_t)Tables(n_prim).words * 16 +
+         (grad ? (size_t)kWavesPerBlock * n_seg * 24 * sizeof(float) : 0);
 }
 
 // Workgroups of a ray-cast variant that are resident on one CU at once (its registers and
 // LDS decide).  The persistent grid is capped at this many per CU: a workgroup beyond it
 // starts only when another has finished, and its statically assigned first item then
 // finishes late (a 128-particle launch spent half its time in that tail).
-int raycast_groups_per_cu(bool grad, bool dbg, bool all_types, bool self) {
-  self = self && !dbg;
-  static int cache[2][2][2][2] = {};
-  int& n = cache[grad][dbg][all_types][self];
-  if (n > 0) return n;
-  const void* f = raycast_fn(grad, dbg, all_types, self);
+int raycast_groups_per_cu(bool grad, bool dbg, bool all_types, bool self, int n_prim,
+                          int n_seg) {
   int r = 0;
-  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, f, kBlock, 0) != hipSuccess || r < 1) {
+  if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&r, raycast_fn(grad, dbg, all_types, self),
+                                                   kBlock, raycast_lds(grad, n_prim, n_seg)) != hipSuccess ||
+      r < 1) {
     (void)hipGetLastError();
     r = 1;
   }
-  n = r;
-  return n;
+  return r;
 }
 
-// The evaluation is four launches on one stream; `stage` selects one so the host can
+// The evaluation is three launches on one stream; `stage` selects one so the host can
 // bracket each with HIP events when profiling.
 hipError_t launch_eval_stage(int stage, const EvalArgs& a, const Workspace& ws, hipStream_t s) {
   const int n_total = a.n_frames * a.n_particles;
@@ -2376,28 +2451,26 @@ hipError_t launch_eval_stage(int stage, const EvalArgs& a, const Workspace& ws, 
                            dim3(kBlock), 0, s, a, ws);
       break;
     case kStageSched:
-      if (a.self_sched) return hipErrorInvalidValue;   // the ray cast builds its work list
-      if (n_total <= kSchedSmall)
-        hipLaunchKernelGGL(sched_kernel<kSchedSmall>, dim3(1), dim3(kSchedSmall), 0, s, a, ws);
-      else
-        hipLaunchKernelGGL(sched_kernel<kSchedBlock>, dim3(1), dim3(kSchedBlock), 0, s, a, ws);
-      if (dbg) {
-        const size_t n = (size_t)a.n_particles * a.dbg_H * a.dbg_W;
-        hipLaunchKernelGGL(debug_fill_kernel, dim3((unsigned)((n + kBlock - 1) / kBlock)),
-                           dim3(kBlock), 0, s, a.dbg, n, a.dbg_bg);
-      }
+      // (the forward cast needs no list, a small gradient cast builds its own)
+      if (a.grad && n_total > kSelfSched)
+        hipLaunchKernelGGL(sched_kernel, dim3(1), dim3(kSchedBlock), 0, s, a, ws);
       break;
     case kStageRaycast: {
       const TypeMasks tm = a.type_masks;
       const bool all = (tm.m[HT_CONE][0] | tm.m[HT_CONE][1] | tm.m[HT_ECYLINDER][0] |
                         tm.m[HT_ECYLINDER][1]) != 0ull;
-      if (a.self_sched && (dbg || n_total > kSelfSched)) return hipErrorInvalidValue;
-      const void* f = raycast_fn(a.grad != nullptr, dbg, all, a.self_sched != 0);
+      if (dbg) {
+        const size_t n = (size_t)a.n_particles * a.dbg_H * a.dbg_W;
+        hipLaunchKernelGGL(debug_fill_kernel, dim3((unsigned)((n + kBlock - 1) / kBlock)),
+                           dim3(kBlock), 0, s, a.dbg, n, a.dbg_bg);
+      }
+      const void* f = raycast_fn(a.grad != nullptr, dbg, all, n_total <= kSelfSched);
       EvalArgs ka = a;
       Workspace kw = ws;
       TypeMasks kt = tm;
       void* args[] = {&ka, &kw, &kt};
-      return hipLaunchKernel(f, dim3(a.grid), dim3(kBlock), args, 0, s);
+      return hipLaunchKernel(f, dim3(a.grid), dim3(kBlock), args,
+                             (unsigned)raycast_lds(a.grad != nullptr, a.n_prim, a.n_seg), s);
     }
     case kStageFinalize:
       if (a.grad)

@@ -1,0 +1,120 @@
+"""The ray cast's split of a launch: fewer particles than resident workgroups are cut into parts,
+more are taken whole from the work queues.  The sizes lie on both sides of each switch; costs must
+be bit-identical to a launch that splits otherwise (the FP64 depth sums are exact), gradients
+agree to 1e-5 of their largest component (FP32 row sums of other tiles)."""
+import numpy as np
+import pytest
+
+import paper_2005_07068_amd as ht
+from gpu_util import frame_for, make_ctx, particles_for, torch_cuda
+from oracle import synth
+from workload import WORKLOADS, make_hand_model, seed_sequence
+
+pytestmark = pytest.mark.gpu
+
+
+def _uneven(n_frames):
+    cfg = WORKLOADS[3]
+    model = make_hand_model(seed_sequence(3, 10_000))
+    frames = [synth.make_frame(model, cfg, f) for f in range(n_frames)]
+    return model, frames
+
+
+@pytest.mark.parametrize("gpc", [1, 8])
+@pytest.mark.parametrize("n", [1, 3, 7, 8, 9, 127, 129, 255, 256, 257, 2047, 2049])
+def test_sizes_around_the_switch_from_parts_to_queues(n, gpc):
+    torch = torch_cuda()
+    dev = torch.device("cuda:0")
+    cfg, model, fr = frame_for(0)
+    ctx = make_ctx(model, [fr])
+    slots = torch.zeros(1, dtype=torch.int32, device=dev)
+    x = torch.tensor(particles_for(model, fr, n, seed=31), device=dev)
+    if n > 2:
+        x[n // 2, 3] = float("nan")
+    ctx.set_launch_config(16, gpc, 1)
+    ctx.eval_counts(reset=True)
+    cost, (c_g, g) = ctx.eval(x, slots), ctx.eval_grad(x, slots)
+    assert ctx.eval_counts(reset=True) == (n, n)
+    ref_c, ref_g = [], []
+    for i in range(0, n, 64):                     # launches of at most 64, split into parts
+        c, gg = ctx.eval_grad(x[i:i + 64], slots)
+        ref_c.append(c)
+        ref_g.append(gg)
+    ref_c, ref_g = torch.cat(ref_c), torch.cat(ref_g)
+    assert torch.equal(cost, ref_c) and torch.equal(c_g, ref_c)
+    if n > 2:
+        assert torch.isinf(cost[n // 2]) and not g[n // 2].any()
+    scale = ref_g.abs().amax(1, keepdim=True)
+    assert torch.all((g - ref_g).abs() <= 1e-5 * scale)
+    ctx.close()
+
+
+def test_queues_over_uneven_frames_and_an_unset_slot():
+    """24 uneven frames x 23 particles, one frame on an unset slot, with one workgroup per CU (552
+    particles from the queues): the costs of one launch per frame."""
+    torch = torch_cuda()
+    dev = torch.device("cuda:0")
+    F, P = 24, 23
+    model, frames = _uneven(F)
+    ctx = make_ctx(model, frames)
+    poses = np.stack([particles_for(model, frames[f], P, seed=40 + f) for f in range(F)])
+    x = torch.tensor(poses, device=dev)
+    slots = torch.arange(F, dtype=torch.int32, device=dev)
+    slots[5] = 900
+    ctx.set_launch_config(16, 1, 1)
+    got = ctx.eval(x, slots)
+    ctx.set_launch_config(16, 8, 1)
+    for f in range(F):
+        one = ctx.eval(x[f], slots[f:f + 1].contiguous())
+        assert torch.isnan(one).all() if f == 5 else torch.equal(one, got[f])
+    assert torch.isnan(got[5]).all()
+    assert ctx.device_errors(reset=True) == ht.HT_DEVERR_UNSET_SLOT
+    ctx.close()
+
+
+def test_refinement_larger_than_the_grid():
+    """Two frames, 160 refined particles each, one workgroup per CU: the gradient evaluation of
+    the selected particles (which reuses the swarm's kinematics) and their candidates come from
+    the queues.  Each refined particle ends on one of the four candidates that its gradient, from
+    a separate evaluation, gives (or where it was), at the cost a separate evaluation gives."""
+    torch = torch_cuda()
+    dev = torch.device("cuda:0")
+    model, frames = _uneven(2)
+    ctx = make_ctx(model, frames)
+    ctx.set_launch_config(16, 1, 1)
+    F, P, K, eta_rot, eta_trans = 2, 256, 160, 0.02, 2.0
+    slots = torch.arange(F, dtype=torch.int32, device=dev)
+    x0 = torch.tensor(np.stack([particles_for(model, frames[f], P, seed=70 + f)
+                                for f in range(F)]), device=dev)
+    sw = ctx.swarm(slots, P, x0[:, 0], x0[:, 0], seed=3)
+    ctx.pso_init(sw)
+    sw["x"].copy_(x0)
+    c0, g = ctx.eval_grad(x0, slots)
+    ctx.pso_step(sw, ht.pso_params(w=0.0, c1=0.0, c2=0.0, mutate_every=0, refine_topk=K,
+                                   refine_steps=1, eta_rot=eta_rot, eta_trans=eta_trans))
+    x1, c1 = sw["x"], sw["cost"]
+    assert torch.equal(ctx.eval(x1, slots), c1)
+    lo = torch.tensor(model["bounds_lo"], dtype=torch.float32, device=dev)
+    hi = torch.tensor(model["bounds_hi"], dtype=torch.float32, device=dev)
+    eta = torch.full((model["n_dof"],), eta_rot, device=dev)
+    eta[20:23] = eta_trans
+    gs = g * eta
+    step = eta * gs / gs.abs().amax(2, keepdim=True)
+    order = torch.sort(c0, dim=1, stable=True).indices
+    moved = 0
+    for f in range(F):
+        for i in order[f, :K].tolist():
+            # the gradient agrees to 1e-5 of its largest component, so does the scaled step
+            # (2e-5 with the division's), and positions round to their own last place
+            tol = 4e-5 * eta + 2.4e-7 * x0[f, i].abs()
+            cands = [torch.minimum(torch.maximum(x0[f, i] - step[f, i] / 2 ** j, lo), hi)
+                     for j in range(4)]
+            on = [bool(((x1[f, i] - q).abs() <= tol).all()) for q in cands]
+            stay = torch.equal(x1[f, i], x0[f, i])
+            assert any(on) or stay, (f, i)
+            assert c1[f, i] < c0[f, i] if not stay else c1[f, i] == c0[f, i]
+            moved += not stay
+        rest = order[f, K:]
+        assert torch.equal(x1[f, rest], x0[f, rest])
+    assert moved > K
+    ctx.close()
