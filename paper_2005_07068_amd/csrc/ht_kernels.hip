@@ -1536,7 +1536,8 @@ struct WaveList {
   int total, tpi;
   bool interleave;
 
-  __device__ void build(const EvalArgs& a, const Workspace& ws, int lane) {
+  // (first wavefront: the offsets also go to LDS, for load() after the next barrier)
+  __device__ void build(const EvalArgs& a, const Workspace& ws, int lane, int* s_off) {
     const int n = a.n_frames * a.n_particles;
     int v[4];
 #pragma unroll
@@ -1565,13 +1566,17 @@ struct WaveList {
     off = incl - mine;
     total = __builtin_amdgcn_readlane(incl, kWave - 1);
     interleave = interleaved(a, total);
-    if (blockIdx.x == 0 && threadIdx.x < kWave) {
+    if (threadIdx.x < kWave) {
       int o = off;
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
-        if (4 * lane + j < n) ws.item_off[4 * lane + j] = o;
+        s_off[4 * lane + j] = o;
+        if (blockIdx.x == 0 && 4 * lane + j < n) ws.item_off[4 * lane + j] = o;
         o += cnt[j];
       }
+      if (lane == 0) s_off[kSelfSched] = total;
+    }
+    if (blockIdx.x == 0 && threadIdx.x < kWave) {
       evaluated = wave_sum(evaluated);
       if (lane == 0) {
         ws.item_off[n] = total;
@@ -1579,6 +1584,15 @@ struct WaveList {
           atomicAdd(&a.eval_count[kCountSlots], (unsigned long long)evaluated);
       }
     }
+  }
+  // the lane's part again (the registers are not held over an item's tiles)
+  __device__ __forceinline__ void load(const int* s_off, int lane) {
+    int o[5];
+#pragma unroll
+    for (int j = 0; j < 5; ++j) o[j] = s_off[4 * lane + j];
+    off = o[0];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) cnt[j] = o[j + 1] - o[j];
   }
   // the evaluated particle of an item, its first item and item count (wave-uniform)
   __device__ __forceinline__ int find(int item, int& first, int& n_it) const {
@@ -1598,10 +1612,6 @@ struct WaveList {
     return r;
   }
 };
-
-// Items that a workgroup of a larger gradient launch takes from its queue at a time: consecutive
-// ones, so that most of them need no new tables.
-constexpr int kRunItems = 4;
 
 // Tiles of a part: part q of a particle split into n parts takes tiles t with
 // (t / kWavesPerBlock) mod n = q, wavefront w of its workgroup those with t mod kWavesPerBlock
@@ -1625,11 +1635,14 @@ __device__ inline float cost_from_sums(double S_d, long long S_and, long long S_
 
 // NT: primitive types the model uses (3: spheres, cylinders, ellipsoids; kNumTypes: also
 // cones and elliptic cylinders), so a model without the latter keeps the smaller register
-// footprint.  (Forcing more wavefronts per SIMD than the vector register count allows
-// spills vector registers and measured slower.)
+// footprint.  The forward cast asks for eight wavefronts per SIMD, the gradient cast for six (80
+// vector registers, about ten spilled around the tile loop): six workgroups per CU take a small
+// launch's items, a few more than its nominal grid of five, in one round, where five left the
+// last ones to a second round (two-hand refined generation 338 us, 333 us with six, 336 us with
+// seven).  SELF: the wavefronts build the work list (at most kSelfSched particles).
 template <bool GRAD, bool DEBUG, int NT, bool SELF>
 __global__ __attribute__((amdgpu_flat_work_group_size(1, kBlock),
-                          amdgpu_waves_per_eu((GRAD || DEBUG) ? 1 : 8)))
+                          amdgpu_waves_per_eu(GRAD ? 6 : DEBUG ? 1 : 8)))
 void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
   static_assert(!(GRAD && DEBUG) && !(SELF && !GRAD), "forward, debug or gradient");
   // the particle's tables, then (gradient) the wrench rows: per wavefront, segment and 16-lane
@@ -1653,17 +1666,17 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
   const int parts = a.parts;
   const int G = gridDim.x, n_eval = a.n_frames * a.n_particles;
   // Forward: whole particles from the queues, or the particle's parts, one per workgroup.
-  // Gradient: the work list's items, in runs of consecutive ones (SELF: an equal share of the
-  // list per workgroup, else kRunItems at a time from the queues).
+  // Gradient: the work list's items, one per workgroup or from the queues.
+  __shared__ int s_off[SELF ? kSelfSched + 1 : 1];
   WaveList list;
   if constexpr (GRAD && SELF) {
-    list.build(a, ws, lane);
+    list.build(a, ws, lane, s_off);
   } else if constexpr (GRAD) {
     list.total = scalar_ptr(ws.list)[0];
     list.tpi = scalar_ptr(ws.list)[1];
     list.interleave = scalar_ptr(ws.list)[2] != 0;
   }
-  const int units = GRAD ? (SELF ? G : (list.total + kRunItems - 1) / kRunItems) : n_eval;
+  const int units = GRAD ? list.total : n_eval;
   const bool queued = units > G;
   const int queue = blockIdx.x % kQueues;
   // workgroups of this queue, and the units it holds
@@ -1671,37 +1684,32 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
   const int held = (units - queue + kQueues - 1) / kQueues;
   int* counter = ws.counters + (a.src ? kCounterInts : 0) + queue * kQueueStride;
   int n_counted = 0;
-  int cur_p = -1;
   // the lane's pixel offset within a tile as a ray component: ((lane & 7) - cx) sx and
   // ((lane >> 3) - cy) sy, so that a tile's rays cost one multiply-add per component
   float lane_dx = 0.0f, lane_dy = 0.0f;
 
-  int unit = queued ? (int)blockIdx.x / kQueues : xcd_major_item(blockIdx.x, G);
-  const int end = queued ? held : (GRAD ? units : n_eval * parts);
-  int buf = 0;
-  while (unit < end) {
+  // (a gradient launch can have fewer items than workgroups: the first ones take them)
+  const int end = queued ? held : GRAD ? units : n_eval * parts;
+  int unit = queued ? (int)blockIdx.x / kQueues
+                    : ((int)blockIdx.x < end ? xcd_major_item(blockIdx.x, end) : end);
+  for (int round = 0; unit < end; ++round) {
+    const int buf = round & 1;
     // the next unit is taken now, so that the atomic's latency passes under this one's work
     int next = end;
     if (queued && tid == 0) next = groups + atomicAdd(counter, 1);
-    int item = 0, item_end = 1, part = 0, r = 0;
-    if constexpr (GRAD) {
-      const int q = queued ? unit * kQueues + queue : unit;
-      item = SELF ? (int)((long long)list.total * q / G) : q * kRunItems;
-      item_end = SELF ? (int)((long long)list.total * (q + 1) / G)
-                      : min(item + kRunItems, list.total);
-    } else {
-      part = queued ? 0 : unit % parts;
-      r = queued ? unit * kQueues + queue : unit / parts;
-    }
-  for (; item < item_end; ++item, buf ^= 1) {
-    // evaluated particle, and for a gradient the item's place among the particle's
-    int first_item = 0, n_it = 1;
+    // evaluated particle; forward: its part; gradient: the item's place among the particle's
+    const int item = queued ? unit * kQueues + queue : unit;
+    int r, part = 0, first_item = 0, n_it = 1;
     if constexpr (GRAD && SELF) {
+      if (round) list.load(s_off, lane);
       r = list.find(item, first_item, n_it);
     } else if constexpr (GRAD) {
       r = scalar_ptr(ws.item_map)[item];
       first_item = scalar_ptr(ws.item_off)[r];
       n_it = scalar_ptr(ws.item_off)[r + 1] - first_item;
+    } else {
+      r = item / parts;
+      part = item - r * parts;
     }
     const int p = a.src ? uni(src_of(a, r)) : r;   // the workspace particle of its kinematics
     const PInfoPtr pi = scalar_ptr(ws.pinfo + p);
@@ -1710,11 +1718,8 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
     if (!GRAD && part == 0 && !skip) ++n_counted;
     const bool on = !skip && (GRAD || part < active_parts(n_tiles, parts));
     if (on) {
-    if (!GRAD || p != cur_p) {
-      const float4* src = ws.tables + (size_t)p * L.words;
-      for (int i = tid; i < L.words; i += kBlock) s_tab[i] = src[i];
-      cur_p = p;
-    }
+    const float4* src = ws.tables + (size_t)p * L.words;
+    for (int i = tid; i < L.words; i += kBlock) s_tab[i] = src[i];
     const float f_sx = pi->sx, f_sy = pi->sy, f_sz = pi->sz, f_bg = pi->bg;
     lane_dx = ((float)(lane & 7) - pi->cx) * f_sx;
     lane_dy = ((float)(lane >> 3) - pi->cy) * f_sy;
@@ -1939,7 +1944,7 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
           a.cost[r] = pi->valid ? cost_from_sums(pi->bg_td + td, sa, (long long)pi->bg_or + so, pi->kc)
                                 : (pi->slot < 0 ? NAN : INFINITY);
         } else {
-          ws.partial[GRAD ? item : r * parts + part] = Partial{td, sa, so};
+          ws.partial[item] = Partial{td, sa, so};
         }
       }
       if (GRAD) {
@@ -1956,8 +1961,7 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
         __syncthreads();   // the rows are read before the next item clears them
       }
     }
-  }
-    unit = queued ? uni(s_next[buf ^ 1]) : end;
+    unit = uni(s_next[buf]);
   }
   if (!GRAD && tid == 0 && n_counted && a.eval_count)
     atomicAdd(&a.eval_count[blockIdx.x % kCountSlots], (unsigned long long)n_counted);
