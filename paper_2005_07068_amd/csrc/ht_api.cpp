@@ -533,6 +533,9 @@ ht_status build_model(const ht_model* m, ht::DevModel& d, ht::TypeMasks& tm) {
     } else {
       d.seg_root_dof[s] = -1;
     }
+    if (par >= 0) std::memcpy(d.seg_path[s], d.seg_path[par], sizeof d.seg_path[s]);
+    d.seg_path[s][d.seg_depth[s]] = (uint8_t)s;
+    d.seg_wrist[s] = par < 0 ? d.seg_root_dof[s] : d.seg_wrist[par];
     for (int i = 0; i < 12; ++i) d.seg_off[s][i] = m->seg_offset[s * 12 + i];
     for (int j = 0; j < 2; ++j) {
       const int dof = m->seg_joint_dof[s * 2 + j];

@@ -33,7 +33,9 @@ struct DevModel {
   int n_roots;                           // independent kinematic trees (hands), <= kMaxRects
   int seg_parent[HT_MAX_SEG];
   int seg_root_dof[HT_MAX_SEG];
-  int seg_depth[HT_MAX_SEG];
+  int seg_depth[HT_MAX_SEG];             // segments above it (root: 0)
+  int seg_wrist[HT_MAX_SEG];             // first wrist dof of its tree
+  uint8_t seg_path[HT_MAX_SEG][HT_MAX_SEG];   // root .. the segment itself (seg_depth + 1)
   int seg_dof[HT_MAX_SEG][2];
   double seg_off[HT_MAX_SEG][12];        // row-major 3x4
   double seg_axis[HT_MAX_SEG][2][3];

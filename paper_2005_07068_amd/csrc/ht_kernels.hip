@@ -120,25 +120,6 @@ __device__ inline void mul34(const double* A, const double* B, double* C) {
   }
 }
 
-// T <- T * Rot(axis, angle) (Rodrigues) given sin and cos of the angle; rotation part only.
-__device__ inline void post_rotate(double* T, const double* a, double s, double c) {
-  const double C = 1.0 - c;
-  const double R[9] = {c + a[0] * a[0] * C, a[0] * a[1] * C - a[2] * s, a[0] * a[2] * C + a[1] * s,
-                       a[1] * a[0] * C + a[2] * s, c + a[1] * a[1] * C, a[1] * a[2] * C - a[0] * s,
-                       a[2] * a[0] * C - a[1] * s, a[2] * a[1] * C + a[0] * s, c + a[2] * a[2] * C};
-  double out[9];
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j)
-      out[i * 3 + j] = T[i * 4 + 0] * R[0 * 3 + j] + T[i * 4 + 1] * R[1 * 3 + j] +
-                       T[i * 4 + 2] * R[2 * 3 + j];
-#pragma unroll
-  for (int i = 0; i < 3; ++i)
-#pragma unroll
-    for (int j = 0; j < 3; ++j) T[i * 4 + j] = out[i * 3 + j];
-}
-
 __device__ __forceinline__ void split(double x, float& hi, float& lo) {
   hi = (float)x;
   lo = (float)(x - (double)hi);
@@ -441,14 +422,16 @@ __global__ __launch_bounds__(kSchedBlock) void sched_kernel(EvalArgs a, Workspac
 // geometry takes the hardware reciprocal and square root (errors of about 1e-7 relative,
 // 1e-4 pixel at most, far inside the pads; the quotients' range-safe sequences made the
 // primitive set-up a long chain of latencies).
-__device__ bool capsule_extent(const double* q0, const double* q1, double r,
-                               const FrameSlot& fs, float* e) {
+using FrameSlotRef = const __attribute__((address_space(4))) FrameSlot&;
+__device__ __forceinline__ bool capsule_extent(const float* q0, const float* q1, float rr,
+                                               FrameSlotRef fs, float* e) {
   float amin = INFINITY, amax = -INFINITY, bmin = INFINITY, bmax = -INFINITY;
-  const float rr = (float)r;
+  bool ok = true;
+#pragma unroll
   for (int j = 0; j < 2; ++j) {
-    const double* q = j ? q1 : q0;
-    const float X = (float)q[0], Y = (float)q[1], Z = (float)q[2];
-    if (!(Z > 1.001f * rr + 1.0f)) return false;
+    const float* q = j ? q1 : q0;
+    const float X = q[0], Y = q[1], Z = q[2];
+    ok &= Z > 1.001f * rr + 1.0f;
     const float den = (Z - rr) * (Z + rr);
     const float inv = fast_rcp(den);
     const float hx = rr * fast_sqrt(fmaf(X, X, den)), hy = rr * fast_sqrt(fmaf(Y, Y, den));
@@ -462,7 +445,7 @@ __device__ bool capsule_extent(const double* q0, const double* q1, double r,
   e[1] = fmaf(fs.fx, amax, fs.cx) + 0.25f;
   e[2] = fmaf(fs.fy, bmin, fs.cy) - 0.25f;
   e[3] = fmaf(fs.fy, bmax, fs.cy) + 0.25f;
-  return true;
+  return ok;
 }
 
 // Bounding disc of the image of a sphere (centre q, radius r, q.z > r): the image is an
@@ -470,9 +453,9 @@ __device__ bool capsule_extent(const double* q0, const double* q1, double r,
 // radii tan(theta - alpha) .. tan(theta + alpha), theta being the angle of q from the optical
 // axis and sin(alpha) = r / |q|.  Its centre and semi-major axis, in pixels (the larger focal
 // length for the radius), give a disc that contains it.
-__device__ void sphere_image_disc(const double* q, double r, const FrameSlot& fs, float* D,
-                                  float& rho) {
-  const float X = (float)q[0], Y = (float)q[1], Z = (float)q[2], R = (float)r;
+__device__ __forceinline__ void sphere_image_disc(const float* q, float R, FrameSlotRef fs, float* D,
+                                                  float& rho) {
+  const float X = q[0], Y = q[1], Z = q[2];
   const float rad = fast_sqrt(fmaf(X, X, Y * Y));
   const float inv_n = __builtin_amdgcn_rsqf(fmaf(rad, rad, Z * Z));
   const float st = rad * inv_n, ct = Z * inv_n, sa = R * inv_n;
@@ -514,20 +497,20 @@ __device__ __forceinline__ void load_prim(const DevModel* __restrict__ G, int o,
   }
 }
 
-// WPP wavefronts per particle: 1, or 2 for models of more than 64 primitives, whose set-up then
-// takes one round on each of the two wavefronts instead of two rounds on one (the second
-// wavefront waits for the first one's trigonometry and chains at the barriers, and sets up
-// primitives 64..127; the first writes the record).
+constexpr int kFkSpread = 256;   // launches of at most this many particles: WPP = 4
+
+// WPP wavefronts per particle (the host's choice, see launch_eval_stage): the rows of the
+// transforms and the primitives are spread over them.
 template <int WPP>
-__global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws) {
-  __shared__ double s_T[kWavesPerBlock][HT_MAX_SEG][12];
-  __shared__ double s_h[kWavesPerBlock][HT_MAX_DOF];
-  __shared__ double s_sin[kWavesPerBlock][HT_MAX_DOF], s_cos[kWavesPerBlock][HT_MAX_DOF];
+__global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a, Workspace ws) {
+  constexpr int kPpb = kWavesPerBlock / WPP;     // particles per workgroup
+  __shared__ double s_T[kPpb][HT_MAX_SEG][12];
+  __shared__ double s_h[kPpb][HT_MAX_DOF];
+  __shared__ double s_sin[kPpb][HT_MAX_DOF], s_cos[kPpb][HT_MAX_DOF];
   // the wavefront index as a scalar, so that everything per particle below is wave-uniform
   // (scalar instructions and branches)
   const int lane = threadIdx.x & (kWave - 1);
   const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  constexpr int kPpb = kWavesPerBlock / WPP;     // particles per workgroup
   const int pb = w / WPP, h = w % WPP;           // particle in the workgroup, its wavefront
   const int n_total = a.n_frames * a.n_particles;
   const int p = blockIdx.x * kPpb + pb;
@@ -543,10 +526,10 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
   const int pc = min(p, n_total - 1);
   const int f = pc / a.n_particles;
   const float x_lane = a.poses[(size_t)pc * n_dof + min(lane, n_dof - 1)];
-  const int slot_raw = a.frame_slots[f];
-  const int stop_raw = a.frame_stop ? a.frame_stop[f] : 0;
-  const int act_raw = a.active ? a.active[pc / a.active_div] : 1;
-  const int kc_i = max(lane - (kWave - HT_MAX_KC), 0);
+  const int slot_raw = scalar_ptr(a.frame_slots)[f];
+  const int stop_raw = a.frame_stop ? scalar_ptr(a.frame_stop)[f] : 0;
+  const int act_raw = a.active ? scalar_ptr(a.active)[pc / a.active_div] : 1;
+  const int kc_i = min(lane, HT_MAX_KC - 1);
   const int kc_a = G->kc_a[kc_i], kc_b = G->kc_b[kc_i];
   // the kinematic tables (everything before the primitive tables), staged by one coalesced
   // copy with all its loads in flight at once: the tree walk would otherwise wait on long
@@ -556,52 +539,61 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
   constexpr int kSegBytes = ((int)offsetof(DevModel, prim_type) + 15) / 16 * 16;
   static_assert(kSegBytes <= (int)sizeof(DevModel), "copy stays inside the model");
   __shared__ __align__(16) unsigned char s_model[kSegBytes];
-  {
-    constexpr int kN = kSegBytes / 16, kIt = (kN + kBlock - 1) / kBlock;
-    const uint4* src4 = reinterpret_cast<const uint4*>(a.model);
-    uint4* dst4 = reinterpret_cast<uint4*>(s_model);
-    uint4 v[kIt];
+  constexpr int kN = kSegBytes / 16, kIt = (kN + kBlock - 1) / kBlock;
+  uint4 stage[kIt];
 #pragma unroll
-    for (int j = 0; j < kIt; ++j) v[j] = src4[min((int)threadIdx.x + j * kBlock, kN - 1)];
-#pragma unroll
-    for (int j = 0; j < kIt; ++j)
-      if ((int)threadIdx.x + j * kBlock < kN) dst4[threadIdx.x + j * kBlock] = v[j];
-  }
-  // only the members before prim_type may be read through M
-  const DevModel& M = *reinterpret_cast<const DevModel*>(s_model);
-  __shared__ int s_fin[kWavesPerBlock];
-  PrimIn pin0;
-  if (active && lane + h * kWave < n_prim) load_prim(G, lane + h * kWave, pin0);
+  for (int j = 0; j < kIt; ++j)
+    stage[j] = reinterpret_cast<const uint4*>(a.model)[min((int)threadIdx.x + j * kBlock, kN - 1)];
+  const int slot = active ? slot_raw : -1;
+  const bool in_range = slot >= 0 && slot < HT_MAX_SLOTS;
+  FrameSlotRef fs = scalar_ptr(a.slots)[in_range ? slot : 0];
+  const bool slot_ok = in_range && fs.set;
+  if (active && !slot_ok && h == 0 && lane == 0 && a.dev_errors)
+    atomicOr(a.dev_errors, HT_DEVERR_UNSET_SLOT);
+  // a particle of a stopped frame (tracking stop rule), or a candidate of a refined particle
+  // that has stopped refining, is neither cast nor written
+  const bool skip = active && (stop_raw != 0 || act_raw == 0);
+
+  // A workgroup whose particles are all skipped writes their headers and is done (a frozen
+  // swarm's generation 1.6 us here, 3.5 us with the rest of the kernel).
   if (a.frame_stop || a.active) {
-    // (after the loads above were issued)  A workgroup whose particles are all skipped (stopped frames, candidates of stopped refined
-    // particles) writes their headers and is done: a frozen swarm's generation takes 2 us here
-    // instead of 3.5
     bool all = true;
 #pragma unroll
     for (int j = 0; j < kPpb; ++j) {
       const int q = min((int)blockIdx.x * kPpb + j, n_total - 1);
-      const bool stop = a.frame_stop && scalar_ptr(a.frame_stop)[q / a.n_particles] != 0;
-      const bool off = a.active && scalar_ptr(a.active)[q / a.active_div] == 0;
-      all &= stop || off;
+      all &= (a.frame_stop && scalar_ptr(a.frame_stop)[q / a.n_particles] != 0) ||
+             (a.active && scalar_ptr(a.active)[q / a.active_div] == 0);
     }
     if (all) {
-      const int q = blockIdx.x * kPpb + threadIdx.x;
-      if ((int)threadIdx.x < kPpb && q < n_total) {
+      if (active && h == 0 && lane == 0) {
         PInfo pi{};
-        pi.slot = a.frame_slots[q / a.n_particles];
+        pi.slot = slot_ok ? slot : -1;
         pi.skip = 1;
-        ws.pinfo[q] = pi;
-        ws.tiles[q] = -1;
+        ws.pinfo[p] = pi;
+        ws.tiles[p] = -1;
       }
       return;
     }
   }
 
+#pragma unroll
+  for (int j = 0; j < kIt; ++j)
+    if ((int)threadIdx.x + j * kBlock < kN)
+      reinterpret_cast<uint4*>(s_model)[threadIdx.x + j * kBlock] = stage[j];
+  // only the members before prim_type may be read through M
+  const DevModel& M = *reinterpret_cast<const DevModel*>(s_model);
+  __shared__ int s_fin[kPpb];
+  // this wavefront's primitives (slots of the type order): its share, in a row, so that its
+  // lanes take few of the set-up paths
+  const int o_per = (n_prim + WPP - 1) / WPP;
+  const int o_end = min((h + 1) * o_per, n_prim);
+  PrimIn pin;
+  if (active && h * o_per + lane < o_end) load_prim(G, h * o_per + lane, pin);
   // every angle's sine and cosine at once (one lane per pose parameter, n_dof <= 64), so the
   // tree walk below is trigonometry-free
   static_assert(HT_MAX_DOF <= kWave, "one lane per pose parameter");
   bool finite = true;
-  if (active && h == 0 && lane < n_dof) {
+  if (active && !skip && h == 0 && lane < n_dof) {
     const float x = x_lane;
     s_h[pb][lane] = (double)x;
     finite = isfinite(x);
@@ -612,158 +604,168 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
   }
   finite = __ballot(!finite) == 0ull;
   if (h == 0 && lane == 0) s_fin[pb] = finite ? 1 : 0;
-  const int slot = active ? slot_raw : -1;
-  const bool slot_ok = active && slot >= 0 && slot < HT_MAX_SLOTS && a.slots[slot].set;
-  if (active && !slot_ok && h == 0 && lane == 0 && a.dev_errors)
-    atomicOr(a.dev_errors, HT_DEVERR_UNSET_SLOT);
-  // a particle of a stopped frame (tracking stop rule), or a candidate of a refined particle
-  // that has stopped refining, is neither cast nor written
-  const bool skip = active && (stop_raw != 0 || act_raw == 0);
   __syncthreads();
   // the first wavefront's finiteness test, for every wavefront of the particle
   if (WPP > 1) finite = __builtin_amdgcn_readfirstlane(s_fin[pb]) != 0;
   const bool valid = slot_ok && finite && !skip;
-  // the slot's background sums, needed only by the record written at the end: loaded after
-  // the barrier as global loads (which no barrier waits for), so that their two dependent
-  // latencies overlap the tree walk
+  // the slot's background sums, needed only by the record written at the end (scalar loads, two
+  // dependent latencies under the tree walk)
   double bg_td = 0.0, bg_or = 0.0;
   if (slot_ok && h == 0) {
-    const double* tot = a.slots[slot].totals;
-    bg_td = global_ptr(tot)[0];
-    bg_or = global_ptr(tot)[1];
+    const double* tot = fs.totals;
+    bg_td = scalar_ptr(tot)[0];
+    bg_or = scalar_ptr(tot)[1];
   }
 
-  // segment transforms, T_s = W L_root ... L_parent(s) L_s with L_s = Off_s Rot(a1, q1)
-  // Rot(a2, q2) and W the wrist of s's tree: every lane forms its own L_s once and stages it
-  // in LDS, then multiplies its ancestors' staged transforms right to left (the tree is
-  // shallow: palm and three phalanges), so no joint rotation is computed twice.
-  __shared__ double s_L[kWavesPerBlock][HT_MAX_SEG][12];
-  const bool seg_lane = valid && h == 0 && lane < n_seg;
-  if (seg_lane) {
-    double Lm[12];
-    for (int i = 0; i < 12; ++i) Lm[i] = M.seg_off[lane][i];
+  // Segment transforms, T_s = W L_root ... L_parent(s) L_s with L_s = Off_s Rot(a1, q1)
+  // Rot(a2, q2) and W the wrist of s's tree, one lane per row of a transform: a row of a product
+  // needs that row of the left factor alone, so a lane forms its row of L_s (a row vector times
+  // a rotation is c v + (1 - c)(v.a) a + s (v x a): 21 operations a joint, where the 3x3
+  // product takes 60), stages it in LDS, and after one barrier carries its row of the wrist
+  // down the path from the root (12 multiply-adds a segment).  48 of a hand's lanes work where
+  // one lane per segment kept 16 busy with three times the operations each.
+  __shared__ double s_L[kPpb][HT_MAX_SEG][12];
+  const int n_rows = valid ? 3 * n_seg : 0;
+#pragma unroll 1
+  for (int q = lane + h * kWave; q < n_rows; q += kWave * WPP) {
+    const int s = q / 3, i = q - 3 * s;
+    const double* off = M.seg_off[s] + 4 * i;
+    double v[3] = {off[0], off[1], off[2]};
+    const double t = off[3];
+#pragma unroll
     for (int j = 0; j < 2; ++j) {
-      const int dof = M.seg_dof[lane][j];
-      if (dof >= 0) post_rotate(Lm, M.seg_axis[lane][j], s_sin[pb][dof], s_cos[pb][dof]);
+      const int dof = M.seg_dof[s][j];
+      if (dof < 0) continue;
+      const double* x = M.seg_axis[s][j];
+      const double sn = s_sin[pb][dof], cs = s_cos[pb][dof];
+      const double d = (1.0 - cs) * (v[0] * x[0] + v[1] * x[1] + v[2] * x[2]);
+      const double c0 = v[1] * x[2] - v[2] * x[1], c1 = v[2] * x[0] - v[0] * x[2],
+                   c2 = v[0] * x[1] - v[1] * x[0];
+      v[0] = cs * v[0] + d * x[0] + sn * c0;
+      v[1] = cs * v[1] + d * x[1] + sn * c1;
+      v[2] = cs * v[2] + d * x[2] + sn * c2;
     }
-    for (int i = 0; i < 12; ++i) s_L[pb][lane][i] = Lm[i];
+    double* o = s_L[pb][s] + 4 * i;
+    o[0] = v[0];
+    o[1] = v[1];
+    o[2] = v[2];
+    o[3] = t;
   }
   __syncthreads();
-  if (seg_lane) {
-    double P[12];
-    for (int i = 0; i < 12; ++i) P[i] = s_L[pb][lane][i];
-    int q = M.seg_parent[lane], root = lane;
-    while (q >= 0) {
-      double Q[12];
-      mul34(s_L[pb][q], P, Q);
-      for (int i = 0; i < 12; ++i) P[i] = Q[i];
-      root = q;
-      q = M.seg_parent[q];
-    }
-    // wrist: Trans(x, y, z) Rz(tz) Ry(ty) Rx(tx)
-    const int b = M.seg_root_dof[root];
-    const double* hq = &s_h[pb][b];
+#pragma unroll 1
+  for (int q = lane + h * kWave; q < n_rows; q += kWave * WPP) {
+    const int s = q / 3, i = q - 3 * s;
+    // row i of the wrist: Trans(x, y, z) Rz(tz) Ry(ty) Rx(tx)
+    const int b = M.seg_wrist[s];
+    const double hq = s_h[pb][b + i];
     const double sx = s_sin[pb][b + 3], cx = s_cos[pb][b + 3];
     const double sy = s_sin[pb][b + 4], cy = s_cos[pb][b + 4];
     const double sz = s_sin[pb][b + 5], cz = s_cos[pb][b + 5];
-    const double Rzy[9] = {cz * cy, -sz, cz * sy, sz * cy, cz, sz * sy, -sy, 0.0, cy};
-    double W0[12];
-    W0[0] = Rzy[0];
-    W0[1] = Rzy[1] * cx + Rzy[2] * sx;
-    W0[2] = -Rzy[1] * sx + Rzy[2] * cx;
-    W0[3] = hq[0];
-    W0[4] = Rzy[3];
-    W0[5] = Rzy[4] * cx + Rzy[5] * sx;
-    W0[6] = -Rzy[4] * sx + Rzy[5] * cx;
-    W0[7] = hq[1];
-    W0[8] = Rzy[6];
-    W0[9] = Rzy[7] * cx + Rzy[8] * sx;
-    W0[10] = -Rzy[7] * sx + Rzy[8] * cx;
-    W0[11] = hq[2];
-    if (a.adjoint && root == lane) {
-      // wrist dofs: translations along camera axes; rotations about Rz Ry e_x, Rz e_y, e_z
-      // through the wrist position
+    const double z = i == 0 ? cz : sz;
+    const double r0 = i == 2 ? -sy : z * cy, r1 = i == 0 ? -sz : (i == 1 ? cz : 0.0),
+                 r2 = i == 2 ? cy : z * sy;
+    double v[3] = {r0, r1 * cx + r2 * sx, r2 * cx - r1 * sx};
+    double t = hq;
+    const int depth = M.seg_depth[s];
+    if (a.adjoint && depth == 0) {
+      // wrist dofs, component i: translations along camera axes; rotations about Rz Ry e_x,
+      // Rz e_y, e_z through the wrist position
       float* df = ws.dof_frame + ((size_t)p * n_dof + b) * 8;
-      for (int i = 0; i < 3; ++i) {
-        float* f = df + i * 8;
-        f[0] = 1.0f;
-        f[1] = i == 0;
-        f[2] = i == 1;
-        f[3] = i == 2;
-        f[4] = f[5] = f[6] = f[7] = 0.0f;
-      }
-      const double ax[3][3] = {{W0[0], W0[4], W0[8]}, {-sz, cz, 0.0}, {0.0, 0.0, 1.0}};
-      for (int i = 0; i < 3; ++i) {
-        float* f = df + (3 + i) * 8;
-        f[0] = 0.0f;
-        f[1] = (float)ax[i][0];
-        f[2] = (float)ax[i][1];
-        f[3] = (float)ax[i][2];
-        f[4] = (float)hq[0];
-        f[5] = (float)hq[1];
-        f[6] = (float)hq[2];
-        f[7] = 0.0f;
+      const double ax[3] = {v[0], i == 0 ? -sz : (i == 1 ? cz : 0.0), i == 2 ? 1.0 : 0.0};
+#pragma unroll
+      for (int j = 0; j < 3; ++j) {
+        float* f = df + j * 8;
+        f[1 + i] = i == j;
+        f[4 + i] = 0.0f;
+        float* g = f + 24;
+        g[1 + i] = (float)ax[j];
+        g[4 + i] = (float)hq;
+        if (i == 0) {
+          f[0] = 1.0f;
+          f[7] = g[0] = g[7] = 0.0f;
+        }
       }
     }
-    double T[12];
-    mul34(W0, P, T);
-    for (int i = 0; i < 12; ++i) s_T[pb][lane][i] = T[i];
-    // joint axes in the camera frame: the second joint's axis is R_s a2; the first's is
-    // R_s Rot(a2, q2)^T a1 (each rotation leaves its own axis fixed); both pass through the
-    // segment origin
-    const int dof1 = M.seg_dof[lane][0], dof2 = M.seg_dof[lane][1];
-    for (int j = 0; j < 2; ++j) {
-      const int dof = j ? dof2 : dof1;
-      if (dof < 0 || !a.adjoint) continue;
-      double v[3] = {M.seg_axis[lane][j][0], M.seg_axis[lane][j][1], M.seg_axis[lane][j][2]};
-      if (j == 0 && dof2 >= 0) {
-        // Rot(a2, q2)^T v = c v - s (a2 x v) + (1 - c)(a2 . v) a2
-        const double* a2 = M.seg_axis[lane][1];
-        const double sn = s_sin[pb][dof2], cs = s_cos[pb][dof2];
-        const double dt = (1.0 - cs) * (a2[0] * v[0] + a2[1] * v[1] + a2[2] * v[2]);
-        const double cr[3] = {a2[1] * v[2] - a2[2] * v[1], a2[2] * v[0] - a2[0] * v[2],
-                              a2[0] * v[1] - a2[1] * v[0]};
-        for (int i = 0; i < 3; ++i) v[i] = cs * v[i] - sn * cr[i] + dt * a2[i];
+    // (four path entries per LDS read)
+#pragma unroll 1
+    for (int d0 = 0; d0 <= depth; d0 += 4) {
+      const uint32_t path = *reinterpret_cast<const uint32_t*>(&M.seg_path[s][d0]);
+#pragma unroll
+      for (int d = 0; d < 4; ++d) {
+        const double* l = s_L[pb][(path >> (8 * d)) & 255u];
+        const bool on = d0 + d <= depth;
+        const double x = v[0], y = v[1], u = v[2];
+        const double n0 = x * l[0] + y * l[4] + u * l[8];
+        const double n1 = x * l[1] + y * l[5] + u * l[9];
+        const double n2 = x * l[2] + y * l[6] + u * l[10];
+        const double nt = x * l[3] + y * l[7] + u * l[11] + t;
+        v[0] = on ? n0 : x;
+        v[1] = on ? n1 : y;
+        v[2] = on ? n2 : u;
+        t = on ? nt : t;
       }
-      float* f = ws.dof_frame + ((size_t)p * n_dof + dof) * 8;
-      f[0] = 0.0f;
-      for (int i = 0; i < 3; ++i) {
-        f[1 + i] = (float)(T[i * 4 + 0] * v[0] + T[i * 4 + 1] * v[1] + T[i * 4 + 2] * v[2]);
-        f[4 + i] = (float)T[i * 4 + 3];
-      }
-      f[7] = 0.0f;
     }
-    if (a.adjoint)
-      reinterpret_cast<float4*>(ws.seg_org)[(size_t)p * n_seg + lane] =
-          make_float4((float)T[3], (float)T[7], (float)T[11], 0.0f);
+    double* o = s_T[pb][s] + 4 * i;
+    o[0] = v[0];
+    o[1] = v[1];
+    o[2] = v[2];
+    o[3] = t;
+    if (a.adjoint) {
+      // joint axes in the camera frame, component i: the second joint's axis is R_s a2; the
+      // first's is R_s Rot(a2, q2)^T a1 (each rotation leaves its own axis fixed); both pass
+      // through the segment origin
+      const int dof2 = M.seg_dof[s][1];
+#pragma unroll
+      for (int j = 0; j < 2; ++j) {
+        const int dof = M.seg_dof[s][j];
+        if (dof < 0) continue;
+        const double* a1 = M.seg_axis[s][j];
+        double x[3] = {a1[0], a1[1], a1[2]};
+        if (j == 0 && dof2 >= 0) {
+          // Rot(a2, q2)^T x = c x - s (a2 x x) + (1 - c)(a2 . x) a2
+          const double* a2 = M.seg_axis[s][1];
+          const double sn = s_sin[pb][dof2], cs = s_cos[pb][dof2];
+          const double dt = (1.0 - cs) * (a2[0] * x[0] + a2[1] * x[1] + a2[2] * x[2]);
+          const double cr[3] = {a2[1] * x[2] - a2[2] * x[1], a2[2] * x[0] - a2[0] * x[2],
+                                a2[0] * x[1] - a2[1] * x[0]};
+          for (int k = 0; k < 3; ++k) x[k] = cs * x[k] - sn * cr[k] + dt * a2[k];
+        }
+        float* f = ws.dof_frame + ((size_t)p * n_dof + dof) * 8;
+        f[1 + i] = (float)(v[0] * x[0] + v[1] * x[1] + v[2] * x[2]);
+        f[4 + i] = (float)t;
+        if (i == 0) f[0] = f[7] = 0.0f;
+      }
+      float* so = ws.seg_org + ((size_t)p * n_seg + s) * 4;
+      so[i] = (float)t;
+      if (i == 0) so[3] = 0.0f;
+    }
   }
-  // collision terms of Eq. 5, one per spare lane (summed in order below)
-  __shared__ double s_kc[kWavesPerBlock][HT_MAX_KC];
-  // (every pair slot is written, zero past the model's pairs, so the record below sums all of
-  // them without a branch per slot)
-  if (valid && h == 0 && lane >= kWave - HT_MAX_KC) {
-    const int i = lane - (kWave - HT_MAX_KC);
-    double v = 0.0;
-    if (i < M.n_kc) v = fmax(-(s_h[pb][kc_a] - s_h[pb][kc_b]), 0.0);
-    s_kc[pb][i] = v;
+  // collision terms of Eq. 5, one per lane; they are differences of FP32 values, so their FP64
+  // sum is exact in any order, and few are positive
+  double kc = 0.0;
+  int kc_mask = 0;
+  if (valid && h == 0) {
+    const double v = lane < M.n_kc ? fmax(-(s_h[pb][kc_a] - s_h[pb][kc_b]), 0.0) : 0.0;
+    kc_mask = (int)__ballot(v > 0.0);
+    for (int m = kc_mask; m; m &= m - 1) {
+      const int l = __builtin_ctz(m);
+      const uint64_t bits = __double_as_longlong(v);
+      kc += __longlong_as_double((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)bits, l) |
+                                 (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(bits >> 32), l) << 32);
+    }
   }
-  __syncthreads();
-
-  // primitive records and screen boxes, in type order (a wave's lanes then take at most two
-  // of the three set-up paths per round); per-tree unions of the primitive boxes (u0, v0 minima; u1, v1 maxima), accumulated with
-  // LDS atomics (cheaper than sixteen wave reductions)
-  __shared__ int s_rect[kWavesPerBlock][kMaxRects][4];
+  __shared__ int s_rect[kPpb][kMaxRects][4];
   if (h == 0 && lane < kMaxRects * 4)
     s_rect[pb][lane >> 2][lane & 3] = (lane & 1) ? INT_MIN : INT_MAX;
   __syncthreads();
+
+  // primitive records and screen boxes, in type order; per-tree unions of the primitive boxes
+  // (u0, v0 minima; u1, v1 maxima), accumulated with LDS atomics (cheaper than sixteen wave
+  // reductions)
   if (valid) {
-    const FrameSlot fs = a.slots[slot];
     const Tables L(n_prim);
     float4* tab = ws.tables + (size_t)p * L.words;
-    for (int o = lane + h * kWave; o < n_prim; o += kWave * WPP) {
-      PrimIn pin;
-      if (o == lane + h * kWave) pin = pin0;
-      else load_prim(G, o, pin);
+    if (h * o_per + lane < o_end) {   // (at most one primitive per lane, see launch_eval_stage)
       const int k = pin.k;
       const int s = pin.seg;
       double F[12];
@@ -846,39 +848,29 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
       for (int i = 0; i < kRec / 4; ++i)
         dst[i] = make_float4(rec[4 * i], rec[4 * i + 1], rec[4 * i + 2], rec[4 * i + 3]);
 
-      // conservative pixel box of an axis-aligned 3D box of the solid, in FP32 (its rounding,
-      // about 1e-4 mm, is covered by a quarter-pixel pad)
-      float lo3[3], hi3[3];
-      {
-        const float cf[3] = {(float)c[0], (float)c[1], (float)c[2]};
-        const float uf[3] = {(float)u[0], (float)u[1], (float)u[2]};
-        const float s0 = (float)sz[0], s1 = (float)sz[1], s2 = (float)sz[2];
-        if (typ == HT_SPHERE) {
-          for (int i = 0; i < 3; ++i) {
-            lo3[i] = cf[i] - s0;
-            hi3[i] = cf[i] + s0;
-          }
-        } else if (typ == HT_CYLINDER || typ == HT_CONE) {
-          // the solid is the convex hull of its two cap discs
-          const float r1 = typ == HT_CONE ? s2 : s0;
-          for (int i = 0; i < 3; ++i) {
-            const float sn = fast_sqrt(fmaxf(0.0f, 1.0f - uf[i] * uf[i]));
-            const float c1 = fmaf(s1, uf[i], cf[i]);
-            lo3[i] = fminf(cf[i] - s0 * sn, c1 - r1 * sn);
-            hi3[i] = fmaxf(cf[i] + s0 * sn, c1 + r1 * sn);
-          }
-        } else {
-          const bool ecyl = typ == HT_ECYLINDER;
-          for (int i = 0; i < 3; ++i) {
-            const float f0 = (float)F[i * 4 + 0] * s0;
-            const float f1 = (float)F[i * 4 + 1] * (ecyl ? s2 : s1);
-            const float f2 = ecyl ? 0.0f : (float)F[i * 4 + 2] * s2;
-            const float e = fast_sqrt(fmaf(f0, f0, fmaf(f1, f1, f2 * f2)));
-            const float c1 = ecyl ? fmaf(s1, uf[i], cf[i]) : cf[i];
-            lo3[i] = fminf(cf[i], c1) - e;
-            hi3[i] = fmaxf(cf[i], c1) + e;
-          }
-        }
+      // Conservative pixel box of an axis-aligned 3D box of the solid, and its bounding capsule,
+      // in FP32 (the rounding of a 600 mm coordinate, about 1e-4 mm or pixels, is covered by the
+      // quarter-pixel pads) and with selects in place of a branch per type.  The solid is the
+      // convex hull of a cross-section at c and one at c + L u (caps, not the sphere and the
+      // ellipsoid), each inside an ellipsoid with semi-axes g along the frame's columns.
+      const bool capped = typ != HT_SPHERE && typ != HT_ELLIPSOID;
+      const float s0 = (float)sz[0], s1 = (float)sz[1], s2 = (float)sz[2];
+      const float g0 = s0;
+      const float g1 = typ == HT_ELLIPSOID ? s1 : (typ == HT_ECYLINDER ? s2 : s0);
+      const float g2 = typ == HT_ELLIPSOID ? s2 : (typ == HT_SPHERE ? s0 : 0.0f);
+      const float k1 = typ == HT_CONE ? s2 * fast_rcp(s0) : 1.0f;   // the second section's scale
+      const float Lf = capped ? s1 : 0.0f;
+      const float cf[3] = {(float)c[0], (float)c[1], (float)c[2]};
+      float Ff[3][3], lo3[3], hi3[3];
+#pragma unroll
+      for (int i = 0; i < 3; ++i) {
+#pragma unroll
+        for (int j = 0; j < 3; ++j) Ff[i][j] = (float)F[i * 4 + j];
+        const float f0 = Ff[i][0] * g0, f1 = Ff[i][1] * g1, f2 = Ff[i][2] * g2;
+        const float e = fast_sqrt(fmaf(f0, f0, fmaf(f1, f1, f2 * f2))) * 1.000001f;
+        const float c1 = fmaf(Lf, Ff[i][2], cf[i]);
+        lo3[i] = fminf(cf[i] - e, c1 - k1 * e);
+        hi3[i] = fmaxf(cf[i] + e, c1 + k1 * e);
       }
       int4 box;
       if (!(lo3[2] > 1.0f)) {
@@ -908,34 +900,24 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
         // intersected with the box above (the capsule reaches past a cylinder's ends).  An
         // ellipsoid with semi-axes a >= b >= c lies in the capsule along its a-axis from
         // -(a - b) to (a - b) with radius b.
-        double q0[3], q1[3], cr;
-        if (typ == HT_SPHERE) {
-          for (int i = 0; i < 3; ++i) q0[i] = q1[i] = c[i];
-          cr = sz[0];
-        } else if (typ == HT_CYLINDER || typ == HT_CONE || typ == HT_ECYLINDER) {
-          for (int i = 0; i < 3; ++i) {
-            q0[i] = c[i];
-            q1[i] = c[i] + sz[1] * u[i];
-          }
-          cr = typ == HT_CYLINDER ? sz[0] : fmax(sz[0], sz[2]);
-        } else {
-          // longest semi-axis ia (the first of equal ones) by selects, so that no array is
-          // indexed at run time
-          const double s0 = sz[0], s1 = sz[1], s2 = sz[2];
-          const int i01 = s1 > s0 ? 1 : 0;
-          const double m01 = i01 ? s1 : s0;
-          const int ia = s2 > m01 ? 2 : i01;
-          const double sa = ia == 2 ? s2 : m01;
-          const double b2 = ia == 0 ? fmax(s1, s2) : (ia == 1 ? fmax(s0, s2) : fmax(s0, s1));
-          const double hl = sa - b2;
-          for (int i = 0; i < 3; ++i) {
-            const double ax = ia == 0 ? F[i * 4] : (ia == 1 ? F[i * 4 + 1] : F[i * 4 + 2]);
-            q0[i] = c[i] - hl * ax;
-            q1[i] = c[i] + hl * ax;
-          }
-          cr = b2;
+        // longest semi-axis ia of an ellipsoid (the first of equal ones)
+        const bool y_longer = s1 > s0;
+        const float m01 = fmaxf(s0, s1);
+        const int ia = s2 > m01 ? 2 : (y_longer ? 1 : 0);
+        const bool ell = typ == HT_ELLIPSOID;
+        const float sa = fmaxf(m01, s2);
+        const float b2 = ia == 2 ? m01 : fmaxf(fminf(s0, s1), s2);   // the larger of the others
+        const float o0 = ell ? b2 - sa : 0.0f, o1 = ell ? sa - b2 : Lf;
+        const int col = ell ? ia : 2;
+        float cr = ell ? b2 : (typ == HT_CONE || typ == HT_ECYLINDER ? fmaxf(s0, s2) : s0);
+        cr += 0.01f + 1e-6f * (fabsf(cf[0]) + fabsf(cf[1]) + fabsf(cf[2]));
+        float q0[3], q1[3];
+#pragma unroll
+        for (int i = 0; i < 3; ++i) {
+          const float ax = col == 0 ? Ff[i][0] : (col == 1 ? Ff[i][1] : Ff[i][2]);
+          q0[i] = fmaf(o0, ax, cf[i]);
+          q1[i] = fmaf(o1, ax, cf[i]);
         }
-        cr += 0.01 + 1e-6 * (fabs(c[0]) + fabs(c[1]) + fabs(c[2]));
         float e[4];
         if (capsule_extent(q0, q1, cr, fs, e)) {
           const float lim = 1.0e6f;
@@ -984,23 +966,11 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
     pi.slot = slot_ok ? slot : -1;
     pi.valid = valid ? 1 : 0;
     pi.skip = skip ? 1 : 0;
-    double kc = 0.0;
-    int kc_mask = 0;
-    if (valid) {
-      // the terms are differences of FP32 values: their FP64 sum is exact in any order
-#pragma unroll
-      for (int i = 0; i < HT_MAX_KC; ++i) {
-        const double v = s_kc[pb][i];
-        kc += v;
-        kc_mask |= v > 0.0 ? 1 << i : 0;
-      }
-    }
     pi.kc = (float)kc;
     pi.kc_mask = kc_mask;
     pi.bg_td = bg_td;
     pi.bg_or = bg_or;
     if (slot_ok) {
-      const FrameSlot& fs = a.slots[slot];
       pi.TW = fs.TW;
       pi.W = fs.W;
       pi.bg = fs.bg;
@@ -1026,7 +996,7 @@ __global__ __launch_bounds__(kBlock, 4) void fk_kernel(EvalArgs a, Workspace ws)
       const int y0 = __builtin_amdgcn_readfirstlane(s_rect[pb][r][2]);
       const int y1 = __builtin_amdgcn_readfirstlane(s_rect[pb][r][3]);
       live[r] = valid && x0 <= x1;
-      R[r] = make_int4(x0 / kTile, y0 / kTile, x1 / kTile, y1 / kTile);
+      R[r] = make_int4(x0 >> 3, y0 >> 3, x1 >> 3, y1 >> 3);   // (kTile = 8)
     }
     // a sweep without a merge is the fixed point; each earlier sweep merges at least once.
     // Only the model's trees can hold rectangles (a one-hand model needs no merge, two hands
@@ -2447,12 +2417,16 @@ hipError_t launch_eval_stage(int stage, const EvalArgs& a, const Workspace& ws, 
   switch (stage) {
     case kStageFk:
       if (a.src) break;   // the kinematics of the previous evaluation are reused
-      if (a.n_prim > kWave)
-        hipLaunchKernelGGL(fk_kernel<2>, dim3((n_total + kWavesPerBlock / 2 - 1) / (kWavesPerBlock / 2)),
-                           dim3(kBlock), 0, s, a, ws);
+      // wavefronts per particle: at least one per 64 primitives (a lane sets up one primitive);
+      // four while every particle still has a CU of its own (64 poses of a 128x128 frame: 25.1
+      // against 25.4 us per swarm generation), else few, the kernel being bound by its FP64
+      // instructions (4096 poses of 64 uneven frames: 95, 102 and 115 us with one, two, four)
+      if (n_total <= kFkSpread)
+        hipLaunchKernelGGL(fk_kernel<4>, dim3(n_total), dim3(kBlock), 0, s, a, ws);
+      else if (a.n_prim > kWave)
+        hipLaunchKernelGGL(fk_kernel<2>, dim3((n_total + 1) / 2), dim3(kBlock), 0, s, a, ws);
       else
-        hipLaunchKernelGGL(fk_kernel<1>, dim3((n_total + kWavesPerBlock - 1) / kWavesPerBlock),
-                           dim3(kBlock), 0, s, a, ws);
+        hipLaunchKernelGGL(fk_kernel<1>, dim3((n_total + 3) / 4), dim3(kBlock), 0, s, a, ws);
       break;
     case kStageSched:
       // (the forward cast needs no list, a small gradient cast builds its own)
