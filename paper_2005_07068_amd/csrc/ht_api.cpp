@@ -212,6 +212,9 @@ bool workspace_fits(const ht_ctx* c, int n_total, int max_tiles, bool grad) {
 constexpr int kMaxGroupsPerCu = 8;     // 2048 threads
 constexpr int kListGroupsPerCu = 5;    // nominal workgroups per CU of a gradient work list
 constexpr int kTilesPerPart = 16;      // tiles of the observation per part, at least
+constexpr int kSmallParticles = 64;    // launches in one kernel (see eval_impl)
+constexpr int kSmallTiles = 32768;
+constexpr int kSmallGroupsPerCu = 3;
 long long item_bound(const ht_ctx* c, long long n_total, int max_tiles, bool grad) {
   const long long fwd = std::max<long long>(n_total, (long long)kMaxGroupsPerCu * c->n_cu);
   return grad ? std::max(fwd, n_total * ((max_tiles + kMinTilesPerItem - 1) / kMinTilesPerItem)) : fwd;
@@ -391,6 +394,17 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
   const int most = (c->max_tiles() + kTilesPerPart - 1) / kTilesPerPart;
   a.parts = grad ? 1 : std::max(1, std::min(most, full / n_total));
   a.grid = grad ? full : (int)std::min<long long>(full, (long long)n_total * a.parts);
+  // Small forward launches take the kinematics and the cast in one: up to 64 particles of any
+  // size (64 poses: 320x240 21.1 to 18.8 us, two hands at 640x480 26.5 to 25.4 us), more of small
+  // observations (128 of 128x128 21.5 to 18.4 us, 200 of them 22.1 to 24.7 us: few parts repeat
+  // the kinematics on busy CUs).  Three workgroups fit a CU.
+  const bool small = !grad && !dbg_on && !src && !adjoint && !active && assemble &&
+                     (n_total <= kSmallParticles ||
+                      (long long)n_total * c->max_tiles() <= kSmallTiles);
+  if (small) {
+    a.parts = std::max(1, std::min(most, kSmallGroupsPerCu * c->n_cu / n_total));
+    a.grid = n_total * a.parts;
+  }
   a.direct = assemble && !grad && a.parts == 1 ? 1 : 0;
   if (grad) {
     // the nominal grid that sizes a gradient's items (part of its bits, see the work list)
@@ -407,7 +421,11 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
   const int kinds[kNumStages] = {HT_K_FK, HT_K_SCHED, grad ? HT_K_RAYCAST_GRAD : HT_K_RAYCAST,
                                  HT_K_FINALIZE};
   if (args_out) *args_out = a;
-  for (int stage = 0; stage < kNumStages; ++stage) {
+  if (small) {
+    HT_HIP(traced(c, HT_K_RAYCAST, n_total, s,
+                  [&] { return launch_eval_stage(kStageSmall, a, ws, s); }));
+  }
+  for (int stage = small ? kStageFinalize : 0; stage < kNumStages; ++stage) {
     if (stage == kStageFk && src) continue;   // reused from the previous evaluation
     if (stage == kStageFinalize && !assemble) continue;   // assembled by the next kernel
     if (stage == kStageFinalize && a.direct) continue;   // costs from the ray cast
@@ -574,26 +592,25 @@ ht_status build_model(const ht_model* m, ht::DevModel& d, ht::TypeMasks& tm) {
     const int t = m->prim_type[k], s = m->prim_seg[k];
     if (t < HT_SPHERE || t > HT_ECYLINDER) return fail(HT_ERR_ARG, "primitive %d: bad type %d", k, t);
     if (s < 0 || s >= m->n_seg) return fail(HT_ERR_ARG, "primitive %d: segment %d out of range", k, s);
-    d.prim_type[k] = t;
-    d.prim_seg[k] = s;
-    d.prim_root[k] = tree[s];
-    for (int i = 0; i < 3; ++i) {
-      const double z = m->prim_size[k * 3 + i];
-      d.prim_inv2[k][i] = z > 0.0 ? 1.0 / (z * z) : 0.0;
-    }
-    for (int i = 0; i < 12; ++i) d.prim_frame[k][i] = m->prim_frame[k * 12 + i];
     const int need = t == HT_SPHERE ? 1 : (t == HT_CYLINDER ? 2 : 3);   // sizes that must be > 0
-    for (int i = 0; i < 3; ++i) {
-      d.prim_size[k][i] = m->prim_size[k * 3 + i];
-      if (i < need && !(d.prim_size[k][i] > 0.0)) return fail(HT_ERR_ARG, "primitive %d: size %d must be > 0", k, i);
-    }
+    for (int i = 0; i < need; ++i)
+      if (!(m->prim_size[k * 3 + i] > 0.0)) return fail(HT_ERR_ARG, "primitive %d: size %d must be > 0", k, i);
     tm.m[t][k / 64] |= 1ull << (k % 64);
   }
-  {
-    int n = 0;
-    for (int t = HT_SPHERE; t <= HT_ECYLINDER; ++t)
-      for (int k = 0; k < m->n_prim; ++k)
-        if (m->prim_type[k] == t) d.prim_order[n++] = k;
+  // laid out in type order
+  int o = 0;
+  for (int t = HT_SPHERE; t <= HT_ECYLINDER; ++t) {
+    for (int k = 0; k < m->n_prim; ++k) {
+      if (m->prim_type[k] != t) continue;
+      d.prim_id[o] = make_int4(k, m->prim_seg[k], t, tree[m->prim_seg[k]]);
+      for (int i = 0; i < 12; ++i) d.prim_frame[o][i] = m->prim_frame[k * 12 + i];
+      for (int i = 0; i < 3; ++i) {
+        const double z = m->prim_size[k * 3 + i];
+        d.prim_size[o][i] = z;
+        d.prim_inv2[o][i] = z > 0.0 ? 1.0 / (z * z) : 0.0;
+      }
+      ++o;
+    }
   }
   for (int j = 0; j < m->n_dof; ++j) {
     if (!(m->bounds_lo[j] <= m->bounds_hi[j])) return fail(HT_ERR_ARG, "bounds of dof %d: lo > hi", j);

@@ -39,18 +39,17 @@ struct DevModel {
   int seg_dof[HT_MAX_SEG][2];
   double seg_off[HT_MAX_SEG][12];        // row-major 3x4
   double seg_axis[HT_MAX_SEG][2][3];
-  int prim_type[HT_MAX_PRIM];
-  int prim_seg[HT_MAX_PRIM];
+  // primitives in type order (so that neighbouring lanes take the same set-up path), each with
+  // its index in the model, segment, type and tree, so that a lane's loads depend on nothing
+  int4 prim_id[HT_MAX_PRIM];             // index, segment, type, tree
   double prim_frame[HT_MAX_PRIM][12];
   double prim_size[HT_MAX_PRIM][3];
+  double prim_inv2[HT_MAX_PRIM][3];      // 1 / size^2 (ellipsoid semi-axes)
   float lo[HT_MAX_DOF], hi[HT_MAX_DOF];
   int mutate[HT_MAX_DOF];
   int kc_a[HT_MAX_KC], kc_b[HT_MAX_KC];
   uint32_t dof_desc[HT_MAX_DOF];         // segments moved by each pose parameter
   int dof_trans[HT_MAX_DOF];             // 1 for the wrist translations (mm), else angle
-  int prim_root[HT_MAX_PRIM];            // tree of each primitive
-  int prim_order[HT_MAX_PRIM];           // primitive indices sorted by type
-  double prim_inv2[HT_MAX_PRIM][3];      // 1 / size^2 (ellipsoid semi-axes)
 };
 
 constexpr int kMaxRects = 4;             // tile rectangles per particle (one per tree)
@@ -177,7 +176,8 @@ struct EvalArgs {
 hipError_t launch_pack_observation(const uint16_t* depth, const uint8_t* skin, int W, int H,
                                    int TW, int TH, uint32_t* words, float* tile_td,
                                    int* tile_skin, double* totals, float bg, hipStream_t s);
-enum { kStageFk = 0, kStageSched = 1, kStageRaycast = 2, kStageFinalize = 3, kNumStages = 4 };
+enum { kStageFk = 0, kStageSched = 1, kStageRaycast = 2, kStageFinalize = 3, kNumStages = 4,
+       kStageSmall = 4 };   // small forward launches: kinematics and ray cast in one
 constexpr int kSelfSchedMax = 256;   // gradient launches of at most this many particles build
                                      // their own work list
 constexpr int kMinTilesPerItem = 4;  // lower bound of the configured tiles_per_item

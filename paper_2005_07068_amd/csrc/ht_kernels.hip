@@ -476,7 +476,7 @@ constexpr float kTileHalfDiag = 4.9498f;
 // ------------------------------------------------------------------------------------
 // forward kinematics prologue: one wavefront per particle (FP64 inside)
 
-// One primitive's model data (in type order: slot o holds primitive prim_order[o]).
+// One primitive's model data.
 struct PrimIn {
   int k, seg, type, root;
   double frame[12];
@@ -485,40 +485,51 @@ struct PrimIn {
 };
 
 __device__ __forceinline__ void load_prim(const DevModel* __restrict__ G, int o, PrimIn& q) {
-  const int k = G->prim_order[o];
-  q.k = k;
-  q.seg = G->prim_seg[k];
-  q.type = G->prim_type[k];
-  q.root = G->prim_root[k];
-  for (int i = 0; i < 12; ++i) q.frame[i] = G->prim_frame[k][i];
+  const int4 id = G->prim_id[o];
+  q.k = id.x;
+  q.seg = id.y;
+  q.type = id.z;
+  q.root = id.w;
+  for (int i = 0; i < 12; ++i) q.frame[i] = G->prim_frame[o][i];
   for (int i = 0; i < 3; ++i) {
-    q.size[i] = G->prim_size[k][i];
-    q.inv2[i] = G->prim_inv2[k][i];
+    q.size[i] = G->prim_size[o][i];
+    q.inv2[i] = G->prim_inv2[o][i];
   }
 }
 
-constexpr int kFkSpread = 256;   // launches of at most this many particles: WPP = 4
+// The kinematic tables of the model (everything before the primitive tables).
+constexpr int kSegBytes = ((int)offsetof(DevModel, prim_id) + 15) / 16 * 16;
+static_assert(kSegBytes <= (int)sizeof(DevModel), "copy stays inside the model");
 
-// WPP wavefronts per particle (the host's choice, see launch_eval_stage): the rows of the
-// transforms and the primitives are spread over them.
-template <int WPP>
-__global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a, Workspace ws) {
-  constexpr int kPpb = kWavesPerBlock / WPP;     // particles per workgroup
-  __shared__ double s_T[kPpb][HT_MAX_SEG][12];
-  __shared__ double s_h[kPpb][HT_MAX_DOF];
-  __shared__ double s_sin[kPpb][HT_MAX_DOF], s_cos[kPpb][HT_MAX_DOF];
-  // the wavefront index as a scalar, so that everything per particle below is wave-uniform
-  // (scalar instructions and branches)
-  const int lane = threadIdx.x & (kWave - 1);
-  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const int pb = w / WPP, h = w % WPP;           // particle in the workgroup, its wavefront
-  const int n_total = a.n_frames * a.n_particles;
-  const int p = blockIdx.x * kPpb + pb;
+// LDS of the kinematics of PPB particles.
+struct FkParticle {
+  double T[HT_MAX_SEG][12], L[HT_MAX_SEG][12];
+  double h[HT_MAX_DOF], sin[HT_MAX_DOF], cos[HT_MAX_DOF];
+  int rect[kMaxRects][4];
+  int fin;
+};
+template <int PPB>
+struct FkShared {
+  FkParticle p[PPB];
+  alignas(16) unsigned char model[kSegBytes];
+};
+
+// Kinematics of particle p0 + pb by wavefront h of its WPP ones (every thread of the BLOCK-thread
+// workgroup calls this, for its kPpb particles): the primitive tables go to tab, the header to
+// header(PInfo, lane), called by the first wavefront after the last barrier, and with a.adjoint the
+// joint frames and segment origins to the workspace.  Returns false where every particle of the
+// workgroup is skipped.  The rows of the transforms and the primitives are spread over the
+// particle's wavefronts.
+template <int BLOCK, int WPP, class Header>
+__device__ __forceinline__ bool fk_particle(const EvalArgs& a, const Workspace& ws,
+                                            FkShared<BLOCK / kWave / WPP>& sh, int p0, int pb,
+                                            int h, int lane, int n_total, float4* tab,
+                                            Header&& header) {
+  constexpr int kPpb = BLOCK / kWave / WPP;      // particles per workgroup
+  const int p = p0 + pb;
   const bool active = p < n_total;
   const int n_dof = a.n_dof, n_seg = a.n_seg, n_prim = a.n_prim;
   const DevModel* __restrict__ G = a.model;
-  // the work queues' counters of the ray cast that follows, and of one that reuses its tables
-  if (blockIdx.x == 0 && threadIdx.x < 2 * kQueues) ws.counters[threadIdx.x * kQueueStride] = 0;
   // Every load that depends on the particle alone is issued first, together and with clamped
   // indices (a load behind a branch, or issued after another whose result is awaited, adds a
   // memory latency to this latency-bound kernel): this lane's pose parameter, the frame's
@@ -536,14 +547,13 @@ __global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a
   // chains of dependent global loads.  The primitive tables are read from global memory by the
   // lane that sets a primitive up, issued here so that their latency overlaps the
   // trigonometry and the tree walk.
-  constexpr int kSegBytes = ((int)offsetof(DevModel, prim_type) + 15) / 16 * 16;
-  static_assert(kSegBytes <= (int)sizeof(DevModel), "copy stays inside the model");
-  __shared__ __align__(16) unsigned char s_model[kSegBytes];
-  constexpr int kN = kSegBytes / 16, kIt = (kN + kBlock - 1) / kBlock;
-  uint4 stage[kIt];
-#pragma unroll
-  for (int j = 0; j < kIt; ++j)
-    stage[j] = reinterpret_cast<const uint4*>(a.model)[min((int)threadIdx.x + j * kBlock, kN - 1)];
+  constexpr int kN = kSegBytes / 16;
+  static_assert(kN <= 2 * BLOCK, "two 16-byte words per thread");
+  const uint4* model4 = reinterpret_cast<const uint4*>(a.model);
+  const int tid = threadIdx.x;
+  const uint4 stage0 = model4[min(tid, kN - 1)];
+  uint4 stage1{};
+  if constexpr (kN > BLOCK) stage1 = model4[min(tid + BLOCK, kN - 1)];
   const int slot = active ? slot_raw : -1;
   const bool in_range = slot >= 0 && slot < HT_MAX_SLOTS;
   FrameSlotRef fs = scalar_ptr(a.slots)[in_range ? slot : 0];
@@ -560,53 +570,51 @@ __global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a
     bool all = true;
 #pragma unroll
     for (int j = 0; j < kPpb; ++j) {
-      const int q = min((int)blockIdx.x * kPpb + j, n_total - 1);
+      const int q = min(p0 + j, n_total - 1);
       all &= (a.frame_stop && scalar_ptr(a.frame_stop)[q / a.n_particles] != 0) ||
              (a.active && scalar_ptr(a.active)[q / a.active_div] == 0);
     }
     if (all) {
-      if (active && h == 0 && lane == 0) {
+      if (active && h == 0) {
         PInfo pi{};
         pi.slot = slot_ok ? slot : -1;
         pi.skip = 1;
-        ws.pinfo[p] = pi;
-        ws.tiles[p] = -1;
+        header(pi, lane);
       }
-      return;
+      return false;
     }
   }
 
-#pragma unroll
-  for (int j = 0; j < kIt; ++j)
-    if ((int)threadIdx.x + j * kBlock < kN)
-      reinterpret_cast<uint4*>(s_model)[threadIdx.x + j * kBlock] = stage[j];
-  // only the members before prim_type may be read through M
-  const DevModel& M = *reinterpret_cast<const DevModel*>(s_model);
-  __shared__ int s_fin[kPpb];
+  {
+    uint4* dst = reinterpret_cast<uint4*>(sh.model);
+    if (tid < kN) dst[tid] = stage0;
+    if constexpr (kN > BLOCK)
+      if (tid + BLOCK < kN) dst[tid + BLOCK] = stage1;
+  }
+  // only the members before prim_id may be read through M
+  const DevModel& M = *reinterpret_cast<const DevModel*>(sh.model);
   // this wavefront's primitives (slots of the type order): its share, in a row, so that its
   // lanes take few of the set-up paths
   const int o_per = (n_prim + WPP - 1) / WPP;
   const int o_end = min((h + 1) * o_per, n_prim);
-  PrimIn pin;
-  if (active && h * o_per + lane < o_end) load_prim(G, h * o_per + lane, pin);
   // every angle's sine and cosine at once (one lane per pose parameter, n_dof <= 64), so the
   // tree walk below is trigonometry-free
   static_assert(HT_MAX_DOF <= kWave, "one lane per pose parameter");
   bool finite = true;
   if (active && !skip && h == 0 && lane < n_dof) {
     const float x = x_lane;
-    s_h[pb][lane] = (double)x;
+    sh.p[pb].h[lane] = (double)x;
     finite = isfinite(x);
     double sv = 0.0, cv = 1.0;
     if (finite) sincos((double)x, &sv, &cv);
-    s_sin[pb][lane] = sv;
-    s_cos[pb][lane] = cv;
+    sh.p[pb].sin[lane] = sv;
+    sh.p[pb].cos[lane] = cv;
   }
   finite = __ballot(!finite) == 0ull;
-  if (h == 0 && lane == 0) s_fin[pb] = finite ? 1 : 0;
+  if (h == 0 && lane == 0) sh.p[pb].fin = finite ? 1 : 0;
   __syncthreads();
   // the first wavefront's finiteness test, for every wavefront of the particle
-  if (WPP > 1) finite = __builtin_amdgcn_readfirstlane(s_fin[pb]) != 0;
+  if (WPP > 1) finite = __builtin_amdgcn_readfirstlane(sh.p[pb].fin) != 0;
   const bool valid = slot_ok && finite && !skip;
   // the slot's background sums, needed only by the record written at the end (scalar loads, two
   // dependent latencies under the tree walk)
@@ -624,7 +632,6 @@ __global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a
   // product takes 60), stages it in LDS, and after one barrier carries its row of the wrist
   // down the path from the root (12 multiply-adds a segment).  48 of a hand's lanes work where
   // one lane per segment kept 16 busy with three times the operations each.
-  __shared__ double s_L[kPpb][HT_MAX_SEG][12];
   const int n_rows = valid ? 3 * n_seg : 0;
 #pragma unroll 1
   for (int q = lane + h * kWave; q < n_rows; q += kWave * WPP) {
@@ -637,7 +644,7 @@ __global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a
       const int dof = M.seg_dof[s][j];
       if (dof < 0) continue;
       const double* x = M.seg_axis[s][j];
-      const double sn = s_sin[pb][dof], cs = s_cos[pb][dof];
+      const double sn = sh.p[pb].sin[dof], cs = sh.p[pb].cos[dof];
       const double d = (1.0 - cs) * (v[0] * x[0] + v[1] * x[1] + v[2] * x[2]);
       const double c0 = v[1] * x[2] - v[2] * x[1], c1 = v[2] * x[0] - v[0] * x[2],
                    c2 = v[0] * x[1] - v[1] * x[0];
@@ -645,22 +652,26 @@ __global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a
       v[1] = cs * v[1] + d * x[1] + sn * c1;
       v[2] = cs * v[2] + d * x[2] + sn * c2;
     }
-    double* o = s_L[pb][s] + 4 * i;
+    double* o = sh.p[pb].L[s] + 4 * i;
     o[0] = v[0];
     o[1] = v[1];
     o[2] = v[2];
     o[3] = t;
   }
+  // the lane's primitive, loaded here so that the latency passes under the walk down the tree
+  // (issued with the loads above it held 40 registers over the trigonometry)
+  PrimIn pin;
+  if (valid && h * o_per + lane < o_end) load_prim(G, h * o_per + lane, pin);
   __syncthreads();
 #pragma unroll 1
   for (int q = lane + h * kWave; q < n_rows; q += kWave * WPP) {
     const int s = q / 3, i = q - 3 * s;
     // row i of the wrist: Trans(x, y, z) Rz(tz) Ry(ty) Rx(tx)
     const int b = M.seg_wrist[s];
-    const double hq = s_h[pb][b + i];
-    const double sx = s_sin[pb][b + 3], cx = s_cos[pb][b + 3];
-    const double sy = s_sin[pb][b + 4], cy = s_cos[pb][b + 4];
-    const double sz = s_sin[pb][b + 5], cz = s_cos[pb][b + 5];
+    const double hq = sh.p[pb].h[b + i];
+    const double sx = sh.p[pb].sin[b + 3], cx = sh.p[pb].cos[b + 3];
+    const double sy = sh.p[pb].sin[b + 4], cy = sh.p[pb].cos[b + 4];
+    const double sz = sh.p[pb].sin[b + 5], cz = sh.p[pb].cos[b + 5];
     const double z = i == 0 ? cz : sz;
     const double r0 = i == 2 ? -sy : z * cy, r1 = i == 0 ? -sz : (i == 1 ? cz : 0.0),
                  r2 = i == 2 ? cy : z * sy;
@@ -692,7 +703,7 @@ __global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a
       const uint32_t path = *reinterpret_cast<const uint32_t*>(&M.seg_path[s][d0]);
 #pragma unroll
       for (int d = 0; d < 4; ++d) {
-        const double* l = s_L[pb][(path >> (8 * d)) & 255u];
+        const double* l = sh.p[pb].L[(path >> (8 * d)) & 255u];
         const bool on = d0 + d <= depth;
         const double x = v[0], y = v[1], u = v[2];
         const double n0 = x * l[0] + y * l[4] + u * l[8];
@@ -705,7 +716,7 @@ __global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a
         t = on ? nt : t;
       }
     }
-    double* o = s_T[pb][s] + 4 * i;
+    double* o = sh.p[pb].T[s] + 4 * i;
     o[0] = v[0];
     o[1] = v[1];
     o[2] = v[2];
@@ -724,7 +735,7 @@ __global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a
         if (j == 0 && dof2 >= 0) {
           // Rot(a2, q2)^T x = c x - s (a2 x x) + (1 - c)(a2 . x) a2
           const double* a2 = M.seg_axis[s][1];
-          const double sn = s_sin[pb][dof2], cs = s_cos[pb][dof2];
+          const double sn = sh.p[pb].sin[dof2], cs = sh.p[pb].cos[dof2];
           const double dt = (1.0 - cs) * (a2[0] * x[0] + a2[1] * x[1] + a2[2] * x[2]);
           const double cr[3] = {a2[1] * x[2] - a2[2] * x[1], a2[2] * x[0] - a2[0] * x[2],
                                 a2[0] * x[1] - a2[1] * x[0]};
@@ -745,7 +756,7 @@ __global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a
   double kc = 0.0;
   int kc_mask = 0;
   if (valid && h == 0) {
-    const double v = lane < M.n_kc ? fmax(-(s_h[pb][kc_a] - s_h[pb][kc_b]), 0.0) : 0.0;
+    const double v = lane < M.n_kc ? fmax(-(sh.p[pb].h[kc_a] - sh.p[pb].h[kc_b]), 0.0) : 0.0;
     kc_mask = (int)__ballot(v > 0.0);
     for (int m = kc_mask; m; m &= m - 1) {
       const int l = __builtin_ctz(m);
@@ -754,9 +765,8 @@ __global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a
                                  (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(bits >> 32), l) << 32);
     }
   }
-  __shared__ int s_rect[kPpb][kMaxRects][4];
   if (h == 0 && lane < kMaxRects * 4)
-    s_rect[pb][lane >> 2][lane & 3] = (lane & 1) ? INT_MIN : INT_MAX;
+    sh.p[pb].rect[lane >> 2][lane & 3] = (lane & 1) ? INT_MIN : INT_MAX;
   __syncthreads();
 
   // primitive records and screen boxes, in type order; per-tree unions of the primitive boxes
@@ -764,18 +774,17 @@ __global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a
   // reductions)
   if (valid) {
     const Tables L(n_prim);
-    float4* tab = ws.tables + (size_t)p * L.words;
     if (h * o_per + lane < o_end) {   // (at most one primitive per lane, see launch_eval_stage)
       const int k = pin.k;
       const int s = pin.seg;
       double F[12];
-      mul34(s_T[pb][s], pin.frame, F);
+      mul34(sh.p[pb].T[s], pin.frame, F);
       const double* sz = pin.size;
       const int typ = pin.type;
       float rec[kRec];
       for (int i = 0; i < kRec; ++i) rec[i] = 0.0f;
       const double c[3] = {F[3], F[7], F[11]};
-      const double* T = s_T[pb][s];
+      const double* T = sh.p[pb].T[s];
       split(c[0], rec[0], rec[4]);
       split(c[1], rec[1], rec[5]);
       split(c[2], rec[2], rec[6]);
@@ -950,7 +959,7 @@ __global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a
       if (box.x > box.y || box.z > box.w) box = make_int4(1, 0, 1, 0);
       reinterpret_cast<int4*>(tab + L.box)[k] = box;
       if (box.x <= box.y) {
-        int* rq = s_rect[pb][pin.root];
+        int* rq = sh.p[pb].rect[pin.root];
         atomicMin(rq + 0, box.x);
         atomicMax(rq + 1, box.y);
         atomicMin(rq + 2, box.z);
@@ -991,10 +1000,10 @@ __global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a
     bool live[kMaxRects];
 #pragma unroll
     for (int r = 0; r < kMaxRects; ++r) {
-      const int x0 = __builtin_amdgcn_readfirstlane(s_rect[pb][r][0]);
-      const int x1 = __builtin_amdgcn_readfirstlane(s_rect[pb][r][1]);
-      const int y0 = __builtin_amdgcn_readfirstlane(s_rect[pb][r][2]);
-      const int y1 = __builtin_amdgcn_readfirstlane(s_rect[pb][r][3]);
+      const int x0 = __builtin_amdgcn_readfirstlane(sh.p[pb].rect[r][0]);
+      const int x1 = __builtin_amdgcn_readfirstlane(sh.p[pb].rect[r][1]);
+      const int y0 = __builtin_amdgcn_readfirstlane(sh.p[pb].rect[r][2]);
+      const int y1 = __builtin_amdgcn_readfirstlane(sh.p[pb].rect[r][3]);
       live[r] = valid && x0 <= x1;
       R[r] = make_int4(x0 >> 3, y0 >> 3, x1 >> 3, y1 >> 3);   // (kTile = 8)
     }
@@ -1034,11 +1043,34 @@ __global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a
     }
     pi.n_rects = n;
     pi.n_tiles = nt;
-    if (lane == 0) {
-      ws.pinfo[p] = pi;
-      ws.tiles[p] = skip ? -1 : nt;
-    }
+    header(pi, lane);
   }
+  return true;
+}
+
+constexpr int kFkSpread = 256;   // launches of at most this many particles: WPP = 4
+
+// WPP wavefronts per particle (the host's choice, see launch_eval_stage).
+template <int WPP>
+__global__ __launch_bounds__(kBlock, WPP == 1 ? 4 : 3) void fk_kernel(EvalArgs a, Workspace ws) {
+  constexpr int kPpb = kWavesPerBlock / WPP;
+  __shared__ FkShared<kPpb> sh;
+  // the wavefront index as a scalar, so that everything per particle is wave-uniform (scalar
+  // instructions and branches)
+  const int lane = threadIdx.x & (kWave - 1);
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int pb = w / WPP, h = w % WPP;           // particle in the workgroup, its wavefront
+  const int p0 = blockIdx.x * kPpb, p = p0 + pb;
+  // the work queues' counters of the ray cast that follows, and of one that reuses its tables
+  if (blockIdx.x == 0 && threadIdx.x < 2 * kQueues) ws.counters[threadIdx.x * kQueueStride] = 0;
+  fk_particle<kBlock, WPP>(a, ws, sh, p0, pb, h, lane, a.n_frames * a.n_particles,
+                           ws.tables + (size_t)p * Tables(a.n_prim).words,
+                           [&](const PInfo& pi, int l) {
+                             if (l == 0) {
+                               ws.pinfo[p] = pi;
+                               ws.tiles[p] = pi.skip ? -1 : pi.n_tiles;
+                             }
+                           });
 }
 
 // ------------------------------------------------------------------------------------
@@ -1420,21 +1452,42 @@ __device__ __forceinline__ void ecylinder_test(const float* r, float dx, float d
 // bookkeeping runs on the scalar unit and holds no vector registers
 
 __device__ __forceinline__ int uni(int x) { return __builtin_amdgcn_readfirstlane(x); }
+__device__ __forceinline__ float uni(float x) {
+  return __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(x)));
+}
+template <class T>
+__device__ __forceinline__ T* uni(T* x) {
+  const uint64_t v = reinterpret_cast<uint64_t>(x);
+  const uint32_t lo = __builtin_amdgcn_readfirstlane((uint32_t)v);
+  const uint32_t hi = __builtin_amdgcn_readfirstlane((uint32_t)(v >> 32));
+  return reinterpret_cast<T*>(((uint64_t)hi << 32) | lo);
+}
 // Walks a particle's tiles (the union of its rectangles, each row-major) in steps of the
 // number of wavefronts per workgroup, without a division per tile.
 using PInfoPtr = const __attribute__((address_space(4))) PInfo*;
 
+__device__ __forceinline__ int4 load_rect(PInfoPtr pi, int r) {
+  const __attribute__((address_space(4))) int* q =
+      (const __attribute__((address_space(4))) int*)pi + 4 * r;   // rect is the first member
+  return make_int4(q[0], q[1], q[2], q[3]);
+}
+// (a header in LDS)
+__device__ __forceinline__ int4 load_rect(const PInfo* pi, int r) {
+  const int4 q = pi->rect[r];
+  return make_int4(uni(q.x), uni(q.y), uni(q.z), uni(q.w));
+}
+
+template <class Ptr>
 struct TileWalk {
-  PInfoPtr pi;
+  Ptr pi;
   int n, ri, rx, ry, rw, rh, ox, oy;
 
   __device__ void load(int r) {
-    const __attribute__((address_space(4))) int* q =
-        (const __attribute__((address_space(4))) int*)pi + 4 * r;   // rect is the first member
-    rx = q[0];
-    ry = q[1];
-    rw = q[2];
-    rh = q[3];
+    const int4 q = load_rect(pi, r);
+    rx = q.x;
+    ry = q.y;
+    rw = q.z;
+    rh = q.w;
   }
   // position at tile t of the union
   __device__ void seek(int t) {
@@ -1445,9 +1498,9 @@ struct TileWalk {
     oy = t / rw;
     ox = t - oy * rw;
   }
-  __device__ void start(PInfoPtr p, int t) {
+  __device__ void start(Ptr p, int n_rects, int t) {
     pi = p;
-    n = p->n_rects;
+    n = n_rects;
     ri = 0;
     load(0);
     seek(t);
@@ -1603,6 +1656,229 @@ __device__ inline float cost_from_sums(double S_d, long long S_and, long long S_
   return (float)(D + kLambdaK * (double)kc);
 }
 
+// What the tile loop needs of a particle's header, wave-uniform.
+struct Head {
+  int n_rects, n_tiles, TW, W;
+  float sx, sy, sz, cx, cy, bg;
+  const uint32_t* words;
+  const float* tile_td;
+  const int* tile_skin;
+  const uint8_t* grad_mask;
+
+  __device__ __forceinline__ explicit Head(PInfoPtr p)
+      : n_rects(p->n_rects), n_tiles(p->n_tiles), TW(p->TW), W(p->W), sx(p->sx), sy(p->sy),
+        sz(p->sz), cx(p->cx), cy(p->cy), bg(p->bg), words(p->words), tile_td(p->tile_td),
+        tile_skin(p->tile_skin), grad_mask(p->grad_mask) {}
+  // (a header in LDS)
+  __device__ __forceinline__ explicit Head(const PInfo* p)
+      : n_rects(uni(p->n_rects)), n_tiles(uni(p->n_tiles)), TW(uni(p->TW)), W(uni(p->W)),
+        sx(uni(p->sx)), sy(uni(p->sy)), sz(uni(p->sz)), cx(uni(p->cx)), cy(uni(p->cy)),
+        bg(uni(p->bg)), words(uni(p->words)), tile_td(uni(p->tile_td)),
+        tile_skin(uni(p->tile_skin)), grad_mask(nullptr) {}
+};
+
+// One wavefront's tiles t0, t0 + stride, ... below t_end of a particle whose tables are in LDS
+// (s_tab): ray cast, cost terms and, for a gradient, the wrench rows wr ([segment][16-lane
+// row][6], this wavefront's).  Adds the clamped depth terms to acc_td (per lane), the tiles'
+// background depth sums to acc_bg (the same on every lane) and the match counts, less the
+// background's, to acc_a and acc_o (wavefront totals).
+template <bool GRAD, bool DEBUG, int NT, class Ptr>
+__device__ __forceinline__ void cast_tiles(const EvalArgs& a, const TypeMasks& tm,
+                                           const float4* s_tab, Ptr pi, const Head& hd, int t0,
+                                           int stride, int t_end, int lane, int r, float* wr,
+                                           double& acc_td, double& acc_bg, int& acc_a,
+                                           int& acc_o) {
+  const int n_prim = a.n_prim;
+  const Tables L(n_prim);
+  const int4* s_box = reinterpret_cast<const int4*>(s_tab + L.box);
+  const float4* s_cap = s_tab + L.cap;
+  const float2* s_capr = reinterpret_cast<const float2*>(s_tab + L.capr);
+  const float* recs = reinterpret_cast<const float*>(s_tab);
+  // the lane's pixel offset within a tile as a ray component: ((lane & 7) - cx) sx and
+  // ((lane >> 3) - cy) sy, so that a tile's rays cost one multiply-add per component
+  const float lane_dx = ((float)(lane & 7) - hd.cx) * hd.sx;
+  const float lane_dy = ((float)(lane >> 3) - hd.cy) * hd.sy;
+  TileWalk<Ptr> walk;
+  if (t0 < t_end) walk.start(pi, hd.n_rects, t0);
+  for (int t = t0; t < t_end; t += stride, walk.step(stride)) {
+    const int tx = walk.tx(), ty = walk.ty();
+    const int x0 = tx * kTile, y0 = ty * kTile;
+    const float x0f = (float)x0, y0f = (float)y0;
+    // culling, one lane per primitive: screen box overlap, then the distance of the tile's
+    // centre from the primitive's image segment
+    // (the three loads are issued together, the index clamped, so no branch waits on LDS;
+    // the segment test runs only where some lane's box overlaps; the second half is skipped
+    // outright for models of at most 64 primitives)
+    uint64_t mk[2] = {0ull, 0ull};
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+      if (half * kWave >= n_prim) break;
+      const int k = lane + half * kWave;
+      const int kk = min(k, n_prim - 1);
+      const int4 b = s_box[kk];
+      const float4 cp = s_cap[kk];
+      const float2 cq = s_capr[kk];
+      // one ballot per comparison, combined on the scalar unit with the half's primitive
+      // lanes (a ballot of the combined condition routes its lane mask through a vector
+      // register and back)
+      const int left = n_prim - half * kWave;
+      uint64_t m = (left >= kWave ? ~0ull : (1ull << left) - 1ull) &
+                   __builtin_amdgcn_ballot_w64(b.x <= x0 + kTile - 1) &
+                   __builtin_amdgcn_ballot_w64(b.y >= x0) &
+                   __builtin_amdgcn_ballot_w64(b.z <= y0 + kTile - 1) &
+                   __builtin_amdgcn_ballot_w64(b.w >= y0);
+      if (m) {
+        // on every lane (a uniform branch), the result a lane mask combined on the scalar
+        // unit: no per-lane branch whose outcome would go through a vector register
+        // tile centre (x0 + 3.5, y0 + 3.5) minus the first disc's centre (cp: less 3.5)
+        const float wx = x0f - cp.x, wy = y0f - cp.y;
+        const float sp = fminf(fmaxf(fmaf(wx, cp.z, wy * cp.w) * cq.x, 0.0f), 1.0f);
+        const float ex = fmaf(-sp, cp.z, wx), ey = fmaf(-sp, cp.w, wy);
+        m &= __builtin_amdgcn_ballot_w64(fmaf(ex, ex, ey * ey) <= cq.y);
+      }
+      mk[half] = m;
+    }
+    if ((mk[0] | mk[1]) == 0ull) continue;
+
+    const int tile_idx = ty * hd.TW + tx;
+    const int u = x0 + (lane & 7), v = y0 + (lane >> 3);
+    const uint32_t word = global_ptr(hd.words)[(size_t)tile_idx * kTilePx + lane];
+    // the tile's background sums, loaded with the words (one address for every lane) so
+    // that their latency overlaps the tests; lane 0 subtracts them after the tests
+    const float bg_td = global_ptr(hd.tile_td)[tile_idx];
+    const int bg_sk = global_ptr(hd.tile_skin)[tile_idx];
+    const bool valid = (word & kValidBit) != 0;
+    const float od = (float)(word & 0xFFFFu);
+    const bool os = (word & kSkinBit) != 0;
+    const float dx = fmaf(x0f, hd.sx, lane_dx);
+    const float dy = fmaf(y0f, hd.sy, lane_dy);
+    const float dz = hd.sz;
+    const float dd = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+    const float inv_dd = fast_rcp(dd);
+    float tmin = INFINITY;
+    int win = -1;   // tracked for the gradient and the debug images only
+    float wnx = 0, wny = 0, wnz = 0, wrx = 0, wry = 0, wrz = 0;
+    float wm = -INFINITY, mmax = -INFINITY;   // margins (debug images only)
+
+#pragma unroll
+    for (int half = 0; half < 2; ++half) {
+#pragma unroll
+      for (int typ = 0; typ < NT; ++typ) {
+        uint64_t m = mk[half] & tm.m[typ][half];
+        while (m) {
+          const int k = __builtin_ctzll(m) + half * kWave;
+          m &= m - 1;
+          const float* r = recs + k * kRec;
+          Hit h;
+          if (typ == HT_SPHERE) sphere_test<GRAD, DEBUG>(r, dx, dy, dz, inv_dd, h);
+          else if (typ == HT_CYLINDER) cylinder_test<GRAD, DEBUG>(r, dx, dy, dz, dd, h);
+          else if (typ == HT_ELLIPSOID) ellipsoid_test<GRAD, DEBUG>(r, dx, dy, dz, h);
+          else if (typ == HT_CONE) cone_test<GRAD, DEBUG>(r, dx, dy, dz, dd, h);
+          else ecylinder_test<GRAD, DEBUG>(r, dx, dy, dz, dd, h);
+          // nearest entry in front of the camera: as unsigned integers the bit patterns of
+          // non-negative floats keep their order and negative ones (entries behind the
+          // camera) exceed +inf; exact ties keep the first tested (branch-free selects)
+          const bool take = h.ok & (__float_as_uint(h.t) < __float_as_uint(tmin));
+          tmin = take ? h.t : tmin;
+          if (GRAD || DEBUG) win = take ? k : win;
+          if (DEBUG) {
+            // the nearest primitive's margin, and the largest of the tested ones (misses)
+            wm = take ? h.m : wm;
+            mmax = fmaxf(mmax, h.m);
+          }
+          if (GRAD) {
+            wnx = take ? h.nx : wnx;
+            wny = take ? h.ny : wny;
+            wnz = take ? h.nz : wnz;
+            wrx = take ? h.rx : wrx;
+            wry = take ? h.ry : wry;
+            wrz = take ? h.rz : wrz;
+          }
+        }
+      }
+    }
+    // depth of the nearest entry; behind the background plane it is hidden
+    const float zmin = tmin * dz;
+    const bool any = (GRAD || DEBUG) ? win >= 0 : __float_as_uint(tmin) < 0x7F800000u;
+    const bool hit = any & !(hd.bg > 0.0f && zmin >= hd.bg);
+    win = hit ? win : -1;
+    const float rd = hit ? zmin : (hd.bg > 0.0f ? hd.bg : 0.0f);
+    const float diff = fabsf(od - rd);
+    const float td = fminf(diff, kDClamp);
+    const bool rm = hit && (diff < kDMatch || od == 0.0f);
+    acc_td += (double)(valid ? td : 0.0f);
+    {
+      // one ballot per condition, combined on the scalar unit
+      const uint64_t m_valid = __builtin_amdgcn_ballot_w64(valid);
+      const uint64_t m_os = __builtin_amdgcn_ballot_w64(os);
+      const uint64_t m_rm = __builtin_amdgcn_ballot_w64(rm);
+      acc_a += __builtin_popcountll(m_valid & m_os & m_rm);
+      acc_o += __builtin_popcountll(m_valid & (m_os | m_rm));
+    }
+    {
+      // read back here (a convergent read, so the wait for the loads stays after the tests)
+      const float bgt = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(bg_td)));
+      const int bgs = __builtin_amdgcn_readfirstlane(bg_sk);
+      acc_bg += (double)bgt;
+      acc_o -= bgs;
+    }
+    // the debug images have the host's W x H of the debug slot; a frame slot of another
+    // size would write past them, so stores outside that extent are dropped
+    if (DEBUG && valid && u < a.dbg_W && v < a.dbg_H) {
+      const size_t pix = ((size_t)r * a.dbg_H + v) * a.dbg_W + u;
+      if (a.dbg.depth) a.dbg.depth[pix] = rd;
+      if (a.dbg.hit) a.dbg.hit[pix] = hit ? 1 : 0;
+      if (a.dbg.rm) a.dbg.rm[pix] = rm ? 1 : 0;
+      if (a.dbg.winner) a.dbg.winner[pix] = win;
+      if (a.dbg.margin) a.dbg.margin[pix] = any ? wm : mmax;
+    }
+    if (GRAD) {
+      // adjoint: coefficient of the depth term, then the per-segment wrench
+      bool act = valid && hit && diff < kDClamp && od != rd;
+      // the call's mask (one frame), else the frame's slot mask
+      const uint8_t* gmask = a.pixel_mask ? a.pixel_mask : hd.grad_mask;
+      if (act && gmask) act = global_ptr(gmask)[(size_t)v * hd.W + u] != 0;
+      int seg = -1;
+      float kap = 0.0f;
+      float mx = 0, my = 0, mz = 0;
+      if (act) {
+        const float* r = recs + win * kRec;
+        seg = __float_as_int(r[15]);
+        const float nd = fmaf(wnx, dx, fmaf(wny, dy, wnz * dz));
+        // (the hardware reciprocal: a quotient would expand into a range-safe sequence of
+        // ten instructions; nd is a dot product of normal and ray, far from the range ends)
+        kap = ((rd > od ? dz : -dz)) * fast_rcp(nd);
+        // lever arm from the segment origin: (entry - ref) + (ref - origin)
+        const float lx = wrx + r[12], ly = wry + r[13], lz = wrz + r[14];
+        mx = kap * (ly * wnz - lz * wny);
+        my = kap * (lz * wnx - lx * wnz);
+        mz = kap * (lx * wny - ly * wnx);
+      }
+      const float fx = kap * wnx, fy = kap * wny, fz = kap * wnz;
+      // segments present in this tile, one at a time (uniform loop): row sums on the
+      // vector unit, added by the first lane of each row into that row's accumulators (an
+      // LDS atomic add without return; the four lanes hit distinct addresses and the adds of
+      // a wavefront are applied in program order, so the result is deterministic)
+      uint32_t segmask = wave_or(act ? (1u << seg) : 0u);
+      while (segmask) {
+        const int s = __builtin_ctz(segmask);
+        segmask &= segmask - 1;
+        const bool mine = seg == s;
+        const float vals[6] = {mine ? mx : 0.f, mine ? my : 0.f, mine ? mz : 0.f,
+                               mine ? fx : 0.f, mine ? fy : 0.f, mine ? fz : 0.f};
+        float sum[6];
+#pragma unroll
+        for (int q = 0; q < 6; ++q) sum[q] = row_total(vals[q]);
+        if ((lane & 15) == 0) {
+          float* dst = wr + (s * 4 + (lane >> 4)) * 6;
+#pragma unroll
+          for (int q = 0; q < 6; ++q) atomicAdd(dst + q, sum[q]);
+        }
+      }
+    }
+  }
+}
+
 // NT: primitive types the model uses (3: spheres, cylinders, ellipsoids; kNumTypes: also
 // cones and elliptic cylinders), so a model without the latter keeps the smaller register
 // footprint.  The forward cast asks for eight wavefronts per SIMD, the gradient cast for six (80
@@ -1626,13 +1902,9 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
   // observation addresses are wave-uniform (scalar instructions)
   const int tid = threadIdx.x, lane = tid & (kWave - 1);
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int n_prim = a.n_prim, n_seg = a.n_seg;
-  const Tables L(n_prim);
-  const int4* s_box = reinterpret_cast<const int4*>(s_tab + L.box);
-  const float4* s_cap = s_tab + L.cap;
-  const float2* s_capr = reinterpret_cast<const float2*>(s_tab + L.capr);
+  const int n_seg = a.n_seg;
+  const Tables L(a.n_prim);
   float* s_wr = reinterpret_cast<float*>(s_tab + L.words);   // [wave][seg][row][6]
-  const float* recs = reinterpret_cast<const float*>(s_tab);
   const int parts = a.parts;
   const int G = gridDim.x, n_eval = a.n_frames * a.n_particles;
   // Forward: whole particles from the queues, or the particle's parts, one per workgroup.
@@ -1654,9 +1926,6 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
   const int held = (units - queue + kQueues - 1) / kQueues;
   int* counter = ws.counters + (a.src ? kCounterInts : 0) + queue * kQueueStride;
   int n_counted = 0;
-  // the lane's pixel offset within a tile as a ray component: ((lane & 7) - cx) sx and
-  // ((lane >> 3) - cy) sy, so that a tile's rays cost one multiply-add per component
-  float lane_dx = 0.0f, lane_dy = 0.0f;
 
   // (a gradient launch can have fewer items than workgroups: the first ones take them)
   const int end = queued ? held : GRAD ? units : n_eval * parts;
@@ -1690,13 +1959,7 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
     if (on) {
     const float4* src = ws.tables + (size_t)p * L.words;
     for (int i = tid; i < L.words; i += kBlock) s_tab[i] = src[i];
-    const float f_sx = pi->sx, f_sy = pi->sy, f_sz = pi->sz, f_bg = pi->bg;
-    lane_dx = ((float)(lane & 7) - pi->cx) * f_sx;
-    lane_dy = ((float)(lane >> 3) - pi->cy) * f_sy;
-    const int TW = pi->TW;
-    const uint32_t* words = pi->words;
-    const float* tile_td = pi->tile_td;
-    const int* tile_skin = pi->tile_skin;
+    const Head hd(pi);
     if (GRAD) {
       float* wr = s_wr + wave * n_seg * 24;
       for (int i = lane; i < n_seg * 24; i += kWave) wr[i] = 0.0f;
@@ -1715,185 +1978,9 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
     double acc_bg = 0.0;   // the tiles' background depth sums (the same on every lane)
     int acc_a = 0, acc_o = 0;   // wavefront totals: popcounts of lane masks (scalar unit)
 
-    TileWalk walk;
-    if (t0 < t_end) walk.start(pi, t0);
-    for (int t = t0; t < t_end; t += stride, walk.step(stride)) {
-      const int tx = walk.tx(), ty = walk.ty();
-      const int x0 = tx * kTile, y0 = ty * kTile;
-      const float x0f = (float)x0, y0f = (float)y0;
-      // culling, one lane per primitive: screen box overlap, then the distance of the tile's
-      // centre from the primitive's image segment
-      // (the three loads are issued together, the index clamped, so no branch waits on LDS;
-      // the segment test runs only where some lane's box overlaps; the second half is skipped
-      // outright for models of at most 64 primitives)
-      uint64_t mk[2] = {0ull, 0ull};
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-        if (half * kWave >= n_prim) break;
-        const int k = lane + half * kWave;
-        const int kk = min(k, n_prim - 1);
-        const int4 b = s_box[kk];
-        const float4 cp = s_cap[kk];
-        const float2 cq = s_capr[kk];
-        // one ballot per comparison, combined on the scalar unit with the half's primitive
-        // lanes (a ballot of the combined condition routes its lane mask through a vector
-        // register and back)
-        const int left = n_prim - half * kWave;
-        uint64_t m = (left >= kWave ? ~0ull : (1ull << left) - 1ull) &
-                     __builtin_amdgcn_ballot_w64(b.x <= x0 + kTile - 1) &
-                     __builtin_amdgcn_ballot_w64(b.y >= x0) &
-                     __builtin_amdgcn_ballot_w64(b.z <= y0 + kTile - 1) &
-                     __builtin_amdgcn_ballot_w64(b.w >= y0);
-        if (m) {
-          // on every lane (a uniform branch), the result a lane mask combined on the scalar
-          // unit: no per-lane branch whose outcome would go through a vector register
-          // tile centre (x0 + 3.5, y0 + 3.5) minus the first disc's centre (cp: less 3.5)
-          const float wx = x0f - cp.x, wy = y0f - cp.y;
-          const float sp = fminf(fmaxf(fmaf(wx, cp.z, wy * cp.w) * cq.x, 0.0f), 1.0f);
-          const float ex = fmaf(-sp, cp.z, wx), ey = fmaf(-sp, cp.w, wy);
-          m &= __builtin_amdgcn_ballot_w64(fmaf(ex, ex, ey * ey) <= cq.y);
-        }
-        mk[half] = m;
-      }
-      if ((mk[0] | mk[1]) == 0ull) continue;
-
-      const int tile_idx = ty * TW + tx;
-      const int u = x0 + (lane & 7), v = y0 + (lane >> 3);
-      const uint32_t word = global_ptr(words)[(size_t)tile_idx * kTilePx + lane];
-      // the tile's background sums, loaded with the words (one address for every lane) so
-      // that their latency overlaps the tests; lane 0 subtracts them after the tests
-      const float bg_td = global_ptr(tile_td)[tile_idx];
-      const int bg_sk = global_ptr(tile_skin)[tile_idx];
-      const bool valid = (word & kValidBit) != 0;
-      const float od = (float)(word & 0xFFFFu);
-      const bool os = (word & kSkinBit) != 0;
-      const float dx = fmaf(x0f, f_sx, lane_dx);
-      const float dy = fmaf(y0f, f_sy, lane_dy);
-      const float dz = f_sz;
-      const float dd = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
-      const float inv_dd = fast_rcp(dd);
-      float tmin = INFINITY;
-      int win = -1;   // tracked for the gradient and the debug images only
-      float wnx = 0, wny = 0, wnz = 0, wrx = 0, wry = 0, wrz = 0;
-      float wm = -INFINITY, mmax = -INFINITY;   // margins (debug images only)
-
-#pragma unroll
-      for (int half = 0; half < 2; ++half) {
-#pragma unroll
-        for (int typ = 0; typ < NT; ++typ) {
-          uint64_t m = mk[half] & tm.m[typ][half];
-          while (m) {
-            const int k = __builtin_ctzll(m) + half * kWave;
-            m &= m - 1;
-            const float* r = recs + k * kRec;
-            Hit h;
-            if (typ == HT_SPHERE) sphere_test<GRAD, DEBUG>(r, dx, dy, dz, inv_dd, h);
-            else if (typ == HT_CYLINDER) cylinder_test<GRAD, DEBUG>(r, dx, dy, dz, dd, h);
-            else if (typ == HT_ELLIPSOID) ellipsoid_test<GRAD, DEBUG>(r, dx, dy, dz, h);
-            else if (typ == HT_CONE) cone_test<GRAD, DEBUG>(r, dx, dy, dz, dd, h);
-            else ecylinder_test<GRAD, DEBUG>(r, dx, dy, dz, dd, h);
-            // nearest entry in front of the camera: as unsigned integers the bit patterns of
-            // non-negative floats keep their order and negative ones (entries behind the
-            // camera) exceed +inf; exact ties keep the first tested (branch-free selects)
-            const bool take = h.ok & (__float_as_uint(h.t) < __float_as_uint(tmin));
-            tmin = take ? h.t : tmin;
-            if (GRAD || DEBUG) win = take ? k : win;
-            if (DEBUG) {
-              // the nearest primitive's margin, and the largest of the tested ones (misses)
-              wm = take ? h.m : wm;
-              mmax = fmaxf(mmax, h.m);
-            }
-            if (GRAD) {
-              wnx = take ? h.nx : wnx;
-              wny = take ? h.ny : wny;
-              wnz = take ? h.nz : wnz;
-              wrx = take ? h.rx : wrx;
-              wry = take ? h.ry : wry;
-              wrz = take ? h.rz : wrz;
-            }
-          }
-        }
-      }
-      // depth of the nearest entry; behind the background plane it is hidden
-      const float zmin = tmin * dz;
-      const bool any = (GRAD || DEBUG) ? win >= 0 : __float_as_uint(tmin) < 0x7F800000u;
-      const bool hit = any & !(f_bg > 0.0f && zmin >= f_bg);
-      win = hit ? win : -1;
-      const float rd = hit ? zmin : (f_bg > 0.0f ? f_bg : 0.0f);
-      const float diff = fabsf(od - rd);
-      const float td = fminf(diff, kDClamp);
-      const bool rm = hit && (diff < kDMatch || od == 0.0f);
-      acc_td += (double)(valid ? td : 0.0f);
-      {
-        // one ballot per condition, combined on the scalar unit
-        const uint64_t m_valid = __builtin_amdgcn_ballot_w64(valid);
-        const uint64_t m_os = __builtin_amdgcn_ballot_w64(os);
-        const uint64_t m_rm = __builtin_amdgcn_ballot_w64(rm);
-        acc_a += __builtin_popcountll(m_valid & m_os & m_rm);
-        acc_o += __builtin_popcountll(m_valid & (m_os | m_rm));
-      }
-      {
-        // read back here (a convergent read, so the wait for the loads stays after the tests)
-        const float bgt = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(bg_td)));
-        const int bgs = __builtin_amdgcn_readfirstlane(bg_sk);
-        acc_bg += (double)bgt;
-        acc_o -= bgs;
-      }
-      // the debug images have the host's W x H of the debug slot; a frame slot of another
-      // size would write past them, so stores outside that extent are dropped
-      if (DEBUG && valid && u < a.dbg_W && v < a.dbg_H) {
-        const size_t pix = ((size_t)r * a.dbg_H + v) * a.dbg_W + u;
-        if (a.dbg.depth) a.dbg.depth[pix] = rd;
-        if (a.dbg.hit) a.dbg.hit[pix] = hit ? 1 : 0;
-        if (a.dbg.rm) a.dbg.rm[pix] = rm ? 1 : 0;
-        if (a.dbg.winner) a.dbg.winner[pix] = win;
-        if (a.dbg.margin) a.dbg.margin[pix] = any ? wm : mmax;
-      }
-      if (GRAD) {
-        // adjoint: coefficient of the depth term, then the per-segment wrench
-        bool act = valid && hit && diff < kDClamp && od != rd;
-        // the call's mask (one frame), else the frame's slot mask
-        const uint8_t* gmask = a.pixel_mask ? a.pixel_mask : pi->grad_mask;
-        if (act && gmask) act = global_ptr(gmask)[(size_t)v * pi->W + u] != 0;
-        int seg = -1;
-        float kap = 0.0f;
-        float mx = 0, my = 0, mz = 0;
-        if (act) {
-          const float* r = recs + win * kRec;
-          seg = __float_as_int(r[15]);
-          const float nd = fmaf(wnx, dx, fmaf(wny, dy, wnz * dz));
-          // (the hardware reciprocal: a quotient would expand into a range-safe sequence of
-          // ten instructions; nd is a dot product of normal and ray, far from the range ends)
-          kap = ((rd > od ? dz : -dz)) * fast_rcp(nd);
-          // lever arm from the segment origin: (entry - ref) + (ref - origin)
-          const float lx = wrx + r[12], ly = wry + r[13], lz = wrz + r[14];
-          mx = kap * (ly * wnz - lz * wny);
-          my = kap * (lz * wnx - lx * wnz);
-          mz = kap * (lx * wny - ly * wnx);
-        }
-        const float fx = kap * wnx, fy = kap * wny, fz = kap * wnz;
-        // segments present in this tile, one at a time (uniform loop): row sums on the
-        // vector unit, added by the first lane of each row into that row's accumulators (an
-        // LDS atomic add without return; the four lanes hit distinct addresses and the adds of
-        // a wavefront are applied in program order, so the result is deterministic)
-        uint32_t segmask = wave_or(act ? (1u << seg) : 0u);
-        while (segmask) {
-          const int s = __builtin_ctz(segmask);
-          segmask &= segmask - 1;
-          const bool mine = seg == s;
-          const float vals[6] = {mine ? mx : 0.f, mine ? my : 0.f, mine ? mz : 0.f,
-                                 mine ? fx : 0.f, mine ? fy : 0.f, mine ? fz : 0.f};
-          float sum[6];
-#pragma unroll
-          for (int q = 0; q < 6; ++q) sum[q] = row_total(vals[q]);
-          if ((lane & 15) == 0) {
-            float* dst = s_wr + ((wave * n_seg + s) * 4 + (lane >> 4)) * 6;
-#pragma unroll
-            for (int q = 0; q < 6; ++q) atomicAdd(dst + q, sum[q]);
-          }
-        }
-      }
-    }
+    cast_tiles<GRAD, DEBUG, NT>(a, tm, s_tab, pi, hd, t0, stride, t_end, lane, r,
+                                GRAD ? s_wr + wave * n_seg * 24 : nullptr, acc_td, acc_bg, acc_a,
+                                acc_o);
 
     acc_td = wave_sum(acc_td) - acc_bg;
     if (lane == 0) {
@@ -1935,6 +2022,63 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
   }
   if (!GRAD && tid == 0 && n_counted && a.eval_count)
     atomicAdd(&a.eval_count[blockIdx.x % kCountSlots], (unsigned long long)n_counted);
+}
+
+// ------------------------------------------------------------------------------------
+// small forward launches: the whole evaluation in one launch
+
+// One workgroup per part of a particle: the kinematics (repeated in every part, on CUs that would
+// be idle otherwise), its tables kept in LDS, then the part's tiles.  A chain of latencies (about
+// 5 us of kinematics, 1 us per tile of a wavefront): against separate launches it saves one launch
+// gap and the tables' way through memory (16 poses of a 64x64 frame 17.9 to 14.9 us, 64 of a
+// 128x128 frame 18.1 to 15.3 us).  Workgroups of eight and sixteen wavefronts, with fewer parts,
+// lost more to the barriers than they saved (15.8 and 17.3 us).
+template <int NT>
+__global__ __launch_bounds__(kBlock) void small_eval_kernel(EvalArgs a, Workspace ws,
+                                                            TypeMasks tm) {
+  extern __shared__ float4 s_tab[];
+  __shared__ FkShared<1> sh;
+  __shared__ PInfo s_head;
+  __shared__ double s_td[kWavesPerBlock];
+  __shared__ int s_a[kWavesPerBlock], s_o[kWavesPerBlock];
+  const int tid = threadIdx.x, lane = tid & (kWave - 1);
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int parts = a.parts, n_total = a.n_frames * a.n_particles;
+  const int item = blockIdx.x, r = item / parts, part = item - r * parts;
+  const bool cast = fk_particle<kBlock, kWavesPerBlock>(
+      a, ws, sh, r, 0, wave, lane, n_total, s_tab, [&](const PInfo& pi, int l) {
+        if (l == 0) {
+          s_head = pi;
+          if (!a.direct && part == 0) ws.pinfo[r] = pi;
+        }
+      });
+  if (!cast) return;   // (a skipped particle)
+  __syncthreads();
+  const Head hd(&s_head);
+  double acc_td = 0.0, acc_bg = 0.0;
+  int acc_a = 0, acc_o = 0;
+  cast_tiles<false, false, NT>(a, tm, s_tab, &s_head, hd, part * kWavesPerBlock + wave,
+                               parts * kWavesPerBlock, hd.n_tiles, lane, r, nullptr, acc_td, acc_bg,
+                               acc_a, acc_o);
+  acc_td = wave_sum(acc_td) - acc_bg;
+  if (lane == 0) {
+    s_td[wave] = acc_td;
+    s_a[wave] = acc_a;
+    s_o[wave] = acc_o;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    const double td = ((s_td[0] + s_td[1]) + s_td[2]) + s_td[3];
+    const int sa = s_a[0] + s_a[1] + s_a[2] + s_a[3];
+    const int so = s_o[0] + s_o[1] + s_o[2] + s_o[3];
+    const PInfo& pi = s_head;
+    if (a.direct)
+      a.cost[r] = pi.valid ? cost_from_sums(pi.bg_td + td, sa, (long long)pi.bg_or + so, pi.kc)
+                           : (pi.slot < 0 ? NAN : INFINITY);
+    else
+      ws.partial[item] = Partial{td, sa, so};
+    if (part == 0 && a.eval_count) atomicAdd(&a.eval_count[blockIdx.x % kCountSlots], 1ull);
+  }
 }
 
 // ------------------------------------------------------------------------------------
@@ -2415,6 +2559,19 @@ hipError_t launch_eval_stage(int stage, const EvalArgs& a, const Workspace& ws, 
   if (n_total == 0) return hipSuccess;
   const bool dbg = a.dbg.depth || a.dbg.hit || a.dbg.rm || a.dbg.winner || a.dbg.margin;
   switch (stage) {
+    case kStageSmall: {
+      const TypeMasks tm = a.type_masks;
+      const bool all = (tm.m[HT_CONE][0] | tm.m[HT_CONE][1] | tm.m[HT_ECYLINDER][0] |
+                        tm.m[HT_ECYLINDER][1]) != 0ull;
+      const size_t lds = raycast_lds(false, a.n_prim, a.n_seg);
+      if (all)
+        hipLaunchKernelGGL(small_eval_kernel<kNumTypes>, dim3(n_total * a.parts), dim3(kBlock),
+                           lds, s, a, ws, tm);
+      else
+        hipLaunchKernelGGL(small_eval_kernel<3>, dim3(n_total * a.parts), dim3(kBlock), lds, s,
+                           a, ws, tm);
+      break;
+    }
     case kStageFk:
       if (a.src) break;   // the kinematics of the previous evaluation are reused
       // wavefronts per particle: at least one per 64 primitives (a lane sets up one primitive);

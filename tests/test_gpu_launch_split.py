@@ -118,3 +118,27 @@ def test_refinement_larger_than_the_grid():
         assert torch.equal(x1[f, rest], x0[f, rest])
     assert moved > K
     ctx.close()
+
+
+@pytest.mark.parametrize("cfg_idx,n", [(4, 1), (4, 64), (5, 3), (5, 64), (1, 128), (1, 129), (0, 512),
+                                       (0, 513)])
+def test_evaluation_in_one_launch_equals_separate_launches(cfg_idx, n):
+    """Small forward launches (at most 64 particles, or few tiles: 128 of a 128x128 frame, 512 of
+    a 64x64 one) repeat the kinematics in every part; the costs of a gradient evaluation, which
+    never does, on both sides of the switch, for one and two hands and both primitive sets."""
+    torch = torch_cuda()
+    dev = torch.device("cuda:0")
+    cfg, model, fr = frame_for(cfg_idx)
+    ctx = make_ctx(model, [fr])
+    slots = torch.zeros(1, dtype=torch.int32, device=dev)
+    x = torch.tensor(particles_for(model, fr, n, seed=90 + n), device=dev)
+    x[0, 20] = 1.0e5                                # a hand out of view: background sums alone
+    if n > 1:
+        x[1, 4] = float("inf")
+    ctx.eval_counts(reset=True)
+    cost = ctx.eval(x, slots)
+    assert ctx.eval_counts() == (n, 0)
+    ref = ctx.eval_grad(x, slots)[0]
+    assert torch.equal(cost, ref) and torch.isfinite(cost[0])
+    assert n == 1 or torch.isinf(cost[1])
+    ctx.close()
