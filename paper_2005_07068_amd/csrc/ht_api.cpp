@@ -398,7 +398,7 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
   // size (64 poses: 320x240 21.1 to 18.8 us, two hands at 640x480 26.5 to 25.4 us), more of small
   // observations (128 of 128x128 21.5 to 18.4 us, 200 of them 22.1 to 24.7 us: few parts repeat
   // the kinematics on busy CUs).  Three workgroups fit a CU.
-  const bool small = !grad && !dbg_on && !src && !adjoint && !active && assemble &&
+  const bool small = !grad && !dbg_on && !src && !adjoint && !active &&
                      (n_total <= kSmallParticles ||
                       (long long)n_total * c->max_tiles() <= kSmallTiles);
   if (small) {
@@ -418,9 +418,9 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
   a.n_prim = c->n_prim;
   a.n_seg = c->n_seg;
   a.n_dof = c->n_dof;
+  if (args_out) *args_out = a;
   const int kinds[kNumStages] = {HT_K_FK, HT_K_SCHED, grad ? HT_K_RAYCAST_GRAD : HT_K_RAYCAST,
                                  HT_K_FINALIZE};
-  if (args_out) *args_out = a;
   if (small) {
     HT_HIP(traced(c, HT_K_RAYCAST, n_total, s,
                   [&] { return launch_eval_stage(kStageSmall, a, ws, s); }));
@@ -894,6 +894,17 @@ ht_status pso_step_impl(ht_ctx* c, const ht_swarm& sw, const ht_pso_params& p, h
   if (F * P == 0) return HT_OK;
   const int K = p.refine_topk;
   const bool refine = K > 0 && p.refine_steps > 0;
+  // a small plain swarm: its update assembles the evaluation, two launches per generation
+  if (!refine && ht::pso_update_is_small(sw, D)) {
+    ht::EvalArgs ev{};
+    ht_status st = ht::eval_impl(c, F, sw.frame_slots, P, sw.x, sw.cost, nullptr, nullptr, nullptr, s,
+                                 sw.stop_gen, nullptr, 0, nullptr, nullptr, 1, false, &ev);
+    if (st != HT_OK) return st;
+    HT_HIP(traced(c, HT_K_PSO, F * P, s, [&] {
+      return ht::launch_pso_update_small(c->d_model, sw, p, D, ev, c->ws, s);
+    }));
+    return HT_OK;
+  }
   // (the refinement's first gradient evaluation reads these particles' kinematics)
   ht_status st = ht::eval_impl(c, F, sw.frame_slots, P, sw.x, sw.cost, nullptr, nullptr, nullptr, s,
                                sw.stop_gen, nullptr, 0, nullptr, nullptr, 1, true, nullptr, refine);

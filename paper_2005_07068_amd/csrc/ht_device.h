@@ -172,6 +172,26 @@ struct EvalArgs {
   int n_prim, n_seg, n_dof;
 };
 
+// Tiles of a part: part q of a particle split into n parts takes tiles t with
+// (t / kWavesPerBlock) mod n = q, wavefront w of its workgroup those with t mod kWavesPerBlock
+// = w, so every part samples the whole hand and carries about equal work.  Parts past the
+// particle's tiles do nothing; the others' partials are read by the kernel that assembles the
+// evaluation.
+__device__ __forceinline__ int active_parts(int n_tiles, int parts) {
+  return min(parts, max((n_tiles + kWavesPerBlock - 1) / kWavesPerBlock, 1));
+}
+
+// Eq. 4-5 from the sums (FP64).
+__device__ inline float cost_from_sums(double S_d, long long S_and, long long S_or, float kc) {
+  double D;
+  if (S_or == 0) {
+    D = kLambda;
+  } else {
+    D = S_d / (double)S_or + kLambda * (1.0 - 2.0 * (double)S_and / (double)(S_and + S_or));
+  }
+  return (float)(D + kLambdaK * (double)kc);
+}
+
 // Launch helpers implemented in ht_kernels.hip.
 hipError_t launch_pack_observation(const uint16_t* depth, const uint8_t* skin, int W, int H,
                                    int TW, int TH, uint32_t* words, float* tile_td,
@@ -193,6 +213,12 @@ hipError_t launch_box_around(const DevModel* model, int n_frames, int n_dof, con
                              const float* halfwidth, float* lo, float* hi, hipStream_t s);
 hipError_t launch_pso_update(const DevModel* model, const ht_swarm& sw, const ht_pso_params& p,
                              int n_dof, int* flags, hipStream_t s);
+// The generation update of a small swarm in one launch, which also assembles the evaluation
+// before it (its arguments and workspace) into the costs.
+bool pso_update_is_small(const ht_swarm& sw, int n_dof);
+hipError_t launch_pso_update_small(const DevModel* model, const ht_swarm& sw,
+                                   const ht_pso_params& p, int n_dof, const EvalArgs& a,
+                                   const Workspace& ws, hipStream_t s);
 hipError_t launch_refine_select(const ht_swarm& sw, int K, int n_dof, int* sel, float* rx,
                                 float* rcost, int* active, hipStream_t s);
 // One refinement update (ht_kernels.hip), fused with the assembly of the evaluation before

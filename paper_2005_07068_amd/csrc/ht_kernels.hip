@@ -1636,26 +1636,6 @@ struct WaveList {
   }
 };
 
-// Tiles of a part: part q of a particle split into n parts takes tiles t with
-// (t / kWavesPerBlock) mod n = q, wavefront w of its workgroup those with t mod kWavesPerBlock
-// = w, so every part samples the whole hand and carries about equal work.  Parts past the
-// particle's tiles do nothing; the others' partials are read by the kernel that assembles the
-// evaluation.
-__device__ __forceinline__ int active_parts(int n_tiles, int parts) {
-  return min(parts, max((n_tiles + kWavesPerBlock - 1) / kWavesPerBlock, 1));
-}
-
-// Eq. 4-5 from the sums (FP64).
-__device__ inline float cost_from_sums(double S_d, long long S_and, long long S_or, float kc) {
-  double D;
-  if (S_or == 0) {
-    D = kLambda;
-  } else {
-    D = S_d / (double)S_or + kLambda * (1.0 - 2.0 * (double)S_and / (double)(S_and + S_or));
-  }
-  return (float)(D + kLambdaK * (double)kc);
-}
-
 // What the tile loop needs of a particle's header, wave-uniform.
 struct Head {
   int n_rects, n_tiles, TW, W;

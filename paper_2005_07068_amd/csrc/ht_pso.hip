@@ -308,6 +308,31 @@ __global__ __launch_bounds__(kPsoBlock) void pso_best_kernel(ht_swarm sw, ht_pso
   }
 }
 
+// A mutated parameter's new position, and Eq. 6-7 with the clamp to the bounds (a clamped
+// parameter loses its velocity).
+__device__ __forceinline__ float mutated_position(uint64_t key, int d, int gp, int gen, float lo,
+                                                  float hi) {
+  return fmaf(unit(draw(key, d, gp, gen, 2).x), hi - lo, lo);
+}
+
+__device__ __forceinline__ float moved_position(uint64_t key, const ht_pso_params& prm, int d,
+                                                int gp, int gen, float xd, float v, float pb,
+                                                float gb, float lo, float hi, float& vn) {
+  const uint4 r = draw(key, d, gp, gen, 0);
+  const float r1 = unit(r.x), r2 = unit(r.y);
+  const float t = fmaf(prm.c2 * r2, gb - xd, fmaf(prm.c1 * r1, pb - xd, v));
+  vn = prm.w * t;
+  float xn = xd + vn;
+  if (xn < lo) {
+    xn = lo;
+    vn = 0.0f;
+  } else if (xn > hi) {
+    xn = hi;
+    vn = 0.0f;
+  }
+  return xn;
+}
+
 // generation update, part 2: one thread per (frame, particle, dimension)
 __global__ __launch_bounds__(kBlock) void pso_move_kernel(const DevModel* __restrict__ M,
                                                           ht_swarm sw, ht_pso_params prm,
@@ -332,27 +357,183 @@ __global__ __launch_bounds__(kBlock) void pso_move_kernel(const DevModel* __rest
   const float lo = M->lo[d], hi = M->hi[d];
   if (fl & kFlagMutated) {
     if (M->mutate[d]) {
-      const float u = unit(draw(swarm_key(sw), d, gp, gen, 2).x);
-      sw.x[i] = fmaf(u, hi - lo, lo);
+      sw.x[i] = mutated_position(swarm_key(sw), d, gp, gen, lo, hi);
       sw.v[i] = 0.0f;
     }
     return;
   }
-  const uint4 r = draw(swarm_key(sw), d, gp, gen, 0);
-  const float r1 = unit(r.x), r2 = unit(r.y);
-  const float gb = sw.gbest_x[(size_t)f * n_dof + d];
-  const float t = fmaf(prm.c2 * r2, gb - xd, fmaf(prm.c1 * r1, pb - xd, sw.v[i]));
-  float vn = prm.w * t;
-  float xn = xd + vn;
-  if (xn < lo) {
-    xn = lo;
-    vn = 0.0f;
-  } else if (xn > hi) {
-    xn = hi;
-    vn = 0.0f;
-  }
+  float vn;
+  const float xn = moved_position(swarm_key(sw), prm, d, gp, gen, xd, sw.v[i], pb,
+                                  sw.gbest_x[(size_t)f * n_dof + d], lo, hi, vn);
   sw.x[i] = xn;
   sw.v[i] = vn;
+}
+
+// Small swarms: the whole update in one launch, one workgroup per frame, assembling the
+// evaluation that precedes it as well (the ray cast's partials into costs), so that a generation
+// of a plain small swarm is two launches.  Sixteen lanes work on a particle: they add its parts'
+// partials, and then count how many costs and how many personal bests lie below its own (which
+// ranks the mutation and finds the global best without a sort; keys are unique).  The positions
+// and velocities are loaded before all that, kIter elements per thread, so that their latency
+// passes under it.  A chain of latencies, like the kernels it replaces.
+constexpr int kSmallSwarm = 256;         // particles per frame, at most
+constexpr int kGroup = 16;               // lanes per particle: one DPP row
+constexpr int kSmallIter = 8;            // elements per thread, at most
+
+// Sum over the 16 lanes of a row, on every lane (DPP quad permutations and row rotations).
+__device__ __forceinline__ int row_sum(int v) {
+  v += __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);
+  v += __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);
+  v += __builtin_amdgcn_mov_dpp(v, 0x124, 0xF, 0xF, true);
+  v += __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true);
+  return v;
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const uint64_t b = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true);
+  const uint32_t hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
+  return v + __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double row_sum(double v) {
+  return dpp_add<0x128>(dpp_add<0x124>(dpp_add<0x4E>(dpp_add<0xB1>(v))));
+}
+
+template <int ITER>
+__global__ __launch_bounds__(kPsoBlock) void pso_update_small_kernel(
+    const DevModel* __restrict__ M, ht_swarm sw, ht_pso_params prm, int n_dof, EvalArgs a,
+    Workspace ws) {
+  __shared__ uint64_t s_ck[kSmallSwarm], s_bk[kSmallSwarm];   // keys: costs, personal bests
+  __shared__ int s_fl[kSmallSwarm], s_rank[kSmallSwarm];
+  __shared__ float s_gb[HT_MAX_DOF];
+  __shared__ int s_g;
+  const int P = sw.n_particles, f = blockIdx.x, tid = threadIdx.x;
+  const size_t base = (size_t)f * P;
+  if (sw.stop_gen && sw.stop_gen[f] != 0) return;   // stopped earlier: nothing changes
+  const int gen = sw.gen[f];
+  const uint64_t key = swarm_key(sw);
+  const int n = P * n_dof;
+  float x[ITER], v[ITER], pb[ITER];
+#pragma unroll
+  for (int k = 0; k < ITER; ++k) {
+    const size_t e = base * n_dof + min(tid + k * kPsoBlock, n - 1);
+    x[k] = sw.x[e];
+    v[k] = sw.v[e];
+    pb[k] = sw.pbest_x[e];
+  }
+  // 1. costs from the partials, personal bests
+  const int l = tid % kGroup;
+  for (int i0 = 0; i0 < P; i0 += kPsoBlock / kGroup) {
+    const int i = i0 + tid / kGroup;
+    if (i >= P) break;                       // (a whole row at a time)
+    const size_t gp = base + i;
+    const PInfo& pi = ws.pinfo[gp];
+    const float old = sw.pbest_cost[gp];
+    const Partial p0 = ws.partial[gp * a.parts + min(l, a.parts - 1)];
+    const int act = active_parts(pi.n_tiles, a.parts);
+    double td = l < act ? p0.td : 0.0;
+    int sa = l < act ? p0.a : 0, so = l < act ? p0.o : 0;
+    for (int q = l + kGroup; q < act; q += kGroup) {
+      const Partial pr = ws.partial[gp * a.parts + q];
+      td += pr.td;
+      sa += pr.a;
+      so += pr.o;
+    }
+    td = row_sum(td);
+    sa = row_sum(sa);
+    so = row_sum(so);
+    if (l == 0) {
+      const float cost = pi.valid ? cost_from_sums(pi.bg_td + td, sa, (long long)pi.bg_or + so, pi.kc)
+                                  : (pi.slot < 0 ? NAN : INFINITY);
+      sw.cost[gp] = cost;
+      const float c = cost_key(cost);
+      const bool better = c < old;
+      if (better) sw.pbest_cost[gp] = c;
+      s_fl[i] = better ? kFlagImproved : 0;
+      s_ck[i] = select_key(cost, i);
+      s_bk[i] = select_key(better ? c : old, i);
+    }
+  }
+  __syncthreads();
+  // 2. ranks
+  for (int i0 = 0; i0 < P; i0 += kPsoBlock / kGroup) {
+    const int i = i0 + tid / kGroup;
+    if (i >= P) break;
+    const uint64_t ck = s_ck[i], bk = s_bk[i];
+    int rc = 0, rb = 0;
+    for (int j = l; j < P; j += kGroup) {
+      rc += s_ck[j] < ck ? 1 : 0;
+      rb += s_bk[j] < bk ? 1 : 0;
+    }
+    rc = row_sum(rc);
+    rb = row_sum(rb);
+    if (l == 0) {
+      s_rank[i] = rc;
+      // the lowest personal best; all of them +inf (no finite cost yet): particle 0, the lowest
+      // index
+      if (rb == 0) s_g = i;
+    }
+  }
+  __syncthreads();
+  // 3. global best (its position is read before any position moves), stop rule, mutation
+  const int g = s_g;
+  const float best = select_cost(s_bk[g]);
+  if (tid < n_dof) {
+    const float xg = (s_fl[g] & kFlagImproved) ? sw.x[(base + g) * n_dof + tid]
+                                               : sw.pbest_x[(base + g) * n_dof + tid];
+    s_gb[tid] = xg;
+    sw.gbest_x[(size_t)f * n_dof + tid] = xg;
+  }
+  const bool stop = sw.stop_gen && prm.stop_cost > 0.0f && best < prm.stop_cost;
+  const bool mutate_gen = prm.mutate_every > 0 && (gen + 1) % prm.mutate_every == 0;
+  const int n_mut = mutate_gen ? (int)floorf((float)P * prm.mutate_frac) : 0;
+  __syncthreads();
+  if (tid == 0) {
+    sw.gbest_cost[f] = best;
+    sw.gen[f] = gen + 1;
+    if (stop) sw.stop_gen[f] = gen + 1;
+  }
+#pragma unroll
+  for (int k = 0; k < ITER; ++k) {
+    const int e = tid + k * kPsoBlock;
+    if (e >= n) break;
+    const int i = e / n_dof, d = e - i * n_dof;
+    const size_t at = base * n_dof + e;
+    if (s_fl[i] & kFlagImproved) {
+      pb[k] = x[k];
+      sw.pbest_x[at] = x[k];
+    }
+    if (stop) continue;
+    const bool mutated = s_rank[i] >= P - n_mut;
+    if (mutated && !M->mutate[d]) continue;
+    const float lo = M->lo[d], hi = M->hi[d];
+    float xn, vn;
+    if (mutated) {
+      xn = mutated_position(key, d, (int)base + i, gen, lo, hi);
+      vn = 0.0f;
+    } else {
+      xn = moved_position(key, prm, d, (int)base + i, gen, x[k], v[k], pb[k], s_gb[d], lo, hi, vn);
+    }
+    sw.x[at] = xn;
+    sw.v[at] = vn;
+  }
+}
+
+bool pso_update_is_small(const ht_swarm& sw, int n_dof) {
+  return sw.n_particles <= kSmallSwarm && sw.n_particles * n_dof <= kSmallIter * kPsoBlock;
+}
+
+hipError_t launch_pso_update_small(const DevModel* model, const ht_swarm& sw,
+                                   const ht_pso_params& p, int n_dof, const EvalArgs& a,
+                                   const Workspace& ws, hipStream_t s) {
+  const int n = sw.n_particles * n_dof;
+  const dim3 grid(sw.n_frames), block(kPsoBlock);
+  if (n <= 2 * kPsoBlock)
+    hipLaunchKernelGGL(pso_update_small_kernel<2>, grid, block, 0, s, model, sw, p, n_dof, a, ws);
+  else
+    hipLaunchKernelGGL(pso_update_small_kernel<kSmallIter>, grid, block, 0, s, model, sw, p, n_dof,
+                       a, ws);
+  return hipGetLastError();
 }
 
 hipError_t launch_pso_update(const DevModel* model, const ht_swarm& sw, const ht_pso_params& p,

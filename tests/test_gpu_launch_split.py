@@ -142,3 +142,46 @@ def test_evaluation_in_one_launch_equals_separate_launches(cfg_idx, n):
     assert torch.equal(cost, ref) and torch.isfinite(cost[0])
     assert n == 1 or torch.isinf(cost[1])
     ctx.close()
+
+
+@pytest.mark.parametrize("cfg_idx,P", [(1, 1), (1, 2), (1, 63), (1, 65), (1, 256), (1, 257), (4, 157),
+                                       (4, 158)])
+def test_swarm_update_in_one_launch_matches_the_oracle(cfg_idx, P):
+    """A mutation generation from a mid-run state on both sides of the one-launch update (at most
+    256 particles and 8192 pose parameters per frame), two frames, tied costs, a particle without
+    a finite cost: bests and generation exactly as the oracle's update of the same costs,
+    positions to the bars of the other single-generation tests."""
+    from oracle import pso
+    torch = torch_cuda()
+    dev = torch.device("cuda:0")
+    cfg, model, fr = frame_for(cfg_idx)
+    ctx = make_ctx(model, [fr, fr])
+    slots = torch.tensor([0, 1], dtype=torch.int32, device=dev)
+    x0 = torch.tensor(np.stack([particles_for(model, fr, P, seed=s) for s in (5, 6)]), device=dev)
+    sw = ctx.swarm(slots, P, x0[:, 0], x0[:, 0], seed=77)
+    ctx.pso_init(sw)
+    x0[:, P // 2:] = x0[:, P // 2:P // 2 + 1]       # ties
+    if P > 2:
+        x0[1, 1, 3] = float("nan")
+    rng = np.random.default_rng(P)
+    sw["x"].copy_(x0)
+    sw["v"].copy_(torch.tensor(rng.uniform(-0.05, 0.05, sw["v"].shape).astype(np.float32)))
+    sw["pbest_x"].copy_(sw["x"])
+    sw["pbest_cost"].copy_(torch.tensor(rng.uniform(40, 120, (2, P)).astype(np.float32)))
+    sw["gen"].fill_(2)
+    keys = ("x", "v", "pbest_x", "pbest_cost", "gbest_x", "gbest_cost", "gen")
+    before = {k: sw[k].cpu().numpy().astype(np.int64 if k == "gen" else np.float64) for k in keys}
+    ctx.pso_step(sw, ht.pso_params(w=0.72, c1=2.05, c2=2.05))
+    costs = sw["cost"]
+    assert torch.equal(torch.nan_to_num(ctx.eval(x0, slots)), torch.nan_to_num(costs))
+    ref = pso.update(before, costs.cpu().numpy().astype(np.float64),
+                     pso.PsoParams(w=float(np.float32(0.72)), c1=2.05, c2=2.05, mutate_every=3),
+                     model["bounds_lo"].astype(np.float32), model["bounds_hi"].astype(np.float32),
+                     model["mutate_mask"], 77)
+    after = {k: sw[k].cpu().numpy().astype(np.float64) for k in keys}
+    for k in ("pbest_cost", "gbest_cost", "gen"):
+        assert np.array_equal(after[k], ref[k]), k
+    for k in ("x", "v", "pbest_x", "gbest_x"):
+        ok = np.isfinite(ref[k])
+        assert np.allclose(after[k][ok], ref[k][ok], rtol=1e-5, atol=2e-5), k
+    ctx.close()
