@@ -38,40 +38,39 @@ __device__ __forceinline__ const __attribute__((address_space(4))) T* scalar_ptr
   return (const __attribute__((address_space(4))) T*)p;
 }
 
-__device__ __forceinline__ float wave_sum(float v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
-__device__ __forceinline__ double wave_sum(double v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
-__device__ __forceinline__ int wave_sum(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v += __shfl_xor(v, o);
-  return v;
-}
 // Wavefront total on the vector unit: DPP moves within each 16-lane row (quad permutations,
 // then row rotations by 4 and 8), then the four row sums read from lanes 0, 16, 32, 48 and
 // added in a fixed order.  Deterministic; the result is wave-uniform.  (__shfl_xor lowers to
-// ds_bpermute, an LDS round trip per step.)
+// ds_bpermute, an LDS round trip per step: with it the wavefront totals at the end of every
+// item, of finalize and of the gradient's list cost 1 to 2 us a launch; gradients of 256 poses
+// of a 64x64 hand 54.4 us, 52.5 with DPP.)  Every lane must be active.
 template <int CTRL>
 __device__ __forceinline__ int dpp(int v) {
   return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
 }
-__device__ __forceinline__ float wave_total(float v) {
-  v += __int_as_float(dpp<0xB1>(__float_as_int(v)));    // quad_perm [1, 0, 3, 2]
-  v += __int_as_float(dpp<0x4E>(__float_as_int(v)));    // quad_perm [2, 3, 0, 1]
-  v += __int_as_float(dpp<0x124>(__float_as_int(v)));   // row_ror:4
-  v += __int_as_float(dpp<0x128>(__float_as_int(v)));   // row_ror:8
-  const int b = __float_as_int(v);
-  const float r0 = __int_as_float(__builtin_amdgcn_readlane(b, 0));
-  const float r1 = __int_as_float(__builtin_amdgcn_readlane(b, 16));
-  const float r2 = __int_as_float(__builtin_amdgcn_readlane(b, 32));
-  const float r3 = __int_as_float(__builtin_amdgcn_readlane(b, 48));
-  return (r0 + r1) + (r2 + r3);
+__device__ __forceinline__ int wave_sum(int v) {
+  v += dpp<0xB1>(v);    // quad_perm [1, 0, 3, 2]
+  v += dpp<0x4E>(v);    // quad_perm [2, 3, 0, 1]
+  v += dpp<0x124>(v);   // row_ror:4
+  v += dpp<0x128>(v);   // row_ror:8
+  return (__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16)) +
+         (__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp_add(double v) {
+  const uint64_t b = __double_as_longlong(v);
+  const uint32_t lo = dpp<CTRL>((int)b), hi = dpp<CTRL>((int)(b >> 32));
+  return v + __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double read_lane(double v, int lane) {
+  const uint64_t b = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)b, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+__device__ __forceinline__ double wave_sum(double v) {
+  v = dpp_add<0x128>(dpp_add<0x124>(dpp_add<0x4E>(dpp_add<0xB1>(v))));
+  return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
 }
 // Row total: after the same four DPP steps every lane holds the sum over its 16-lane row.
 __device__ __forceinline__ float row_total(float v) {
@@ -90,17 +89,6 @@ __device__ __forceinline__ uint32_t wave_or(uint32_t v) {
   return (uint32_t)(__builtin_amdgcn_readlane(x, 0) | __builtin_amdgcn_readlane(x, 16) |
                     __builtin_amdgcn_readlane(x, 32) | __builtin_amdgcn_readlane(x, 48));
 }
-__device__ __forceinline__ int wave_min(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = min(v, __shfl_xor(v, o));
-  return v;
-}
-__device__ __forceinline__ int wave_max(int v) {
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) v = max(v, __shfl_xor(v, o));
-  return v;
-}
-
 // Work queues of the ray cast (below) and the ints between two queues' counters (1 KB).
 constexpr int kQueues = 8;
 constexpr int kQueueStride = 256;
@@ -151,7 +139,10 @@ __global__ __launch_bounds__(kBlock) void pack_kernel(const uint16_t* __restrict
     sk = s;
   }
   words[(size_t)tile * kTilePx + lane] = w;
-  td = wave_sum(td);
+  // (FP32: a background that is no whole number makes this sum round, so its order is part of
+  // the result)
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) td += __shfl_xor(td, o);
   sk = wave_sum(sk);
   if (lane == 0) {
     tile_td[tile] = td;
@@ -760,9 +751,7 @@ __device__ __forceinline__ bool fk_particle(const EvalArgs& a, const Workspace& 
     kc_mask = (int)__ballot(v > 0.0);
     for (int m = kc_mask; m; m &= m - 1) {
       const int l = __builtin_ctz(m);
-      const uint64_t bits = __double_as_longlong(v);
-      kc += __longlong_as_double((uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)bits, l) |
-                                 (uint64_t)(uint32_t)__builtin_amdgcn_readlane((int)(bits >> 32), l) << 32);
+      kc += read_lane(v, l);
     }
   }
   if (h == 0 && lane < kMaxRects * 4)
