@@ -107,7 +107,8 @@ struct Partial {
 
 // A particle's primitive tables as the ray cast stages them in LDS, one contiguous run of
 // 16-byte words per particle: the records ([n_prim][kRec] floats), the pixel boxes ([n_prim]
-// int4 (u0, u1, v0, v1), empty = (1, 0, 1, 0)), the image segments of the bounding capsules
+// float4 (cx, hx, cy, hy): a tile overlaps when its corner pixel (x, y) has |x - cx| <= hx and
+// |y - cy| <= hy; negative halves: empty), the image segments of the bounding capsules
 // ([n_prim] float4 (x0, y0, dx, dy): the centres of the end spheres' image discs, pixels) and
 // their reaches ([n_prim] float2 (1 / |(dx, dy)|^2 or 0, reach^2): a tile whose centre lies
 // farther than reach from the segment sees none of the primitive).

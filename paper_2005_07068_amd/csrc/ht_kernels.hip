@@ -933,7 +933,14 @@ __device__ __forceinline__ bool fk_particle(const EvalArgs& a, const Workspace& 
       tab[L.cap + k] = cap;
       reinterpret_cast<float2*>(tab + L.capr)[k] = capr;
       if (box.x > box.y || box.z > box.w) box = make_int4(1, 0, 1, 0);
-      reinterpret_cast<int4*>(tab + L.box)[k] = box;
+      {
+        // |x - cx| <= hx and |y - cy| <= hy for a tile's corner pixel (x, y), exact in FP32
+        const bool none = box.x > box.y;
+        tab[L.box + k] = make_float4(0.5f * (float)(box.x + box.y - (kTile - 1)),
+                                     none ? -1.0f : 0.5f * (float)(box.y - box.x + kTile - 1),
+                                     0.5f * (float)(box.z + box.w - (kTile - 1)),
+                                     none ? -1.0f : 0.5f * (float)(box.w - box.z + kTile - 1));
+      }
       if (box.x <= box.y) {
         int* rq = sh.p[pb].rect[pin.root];
         atomicMin(rq + 0, box.x);
@@ -1633,6 +1640,16 @@ struct Head {
         tile_skin(uni(p->tile_skin)), grad_mask(nullptr) {}
 };
 
+// Bound by the issue of vector instructions (65536 poses of a 64x64 hand: 2.1e9 of them, 3.1
+// cycles each and SIMD, every cycle of the launch).  A multiply-add of vector registers takes 2.4
+// cycles, a comparison, select, minimum, conversion, FP64 or DPP instruction or one with a scalar
+// operand 4.2, a transcendental 16, so the code around the tests counts those: boxes compared by
+// distance from their centre (2 subtractions and 2 comparisons for 4), the nearest entry and the
+// background plane by integer minimum, one comparison per match term.  65536 poses 2600 to 2440
+// us, 1024 two-hand poses 128.0 to 120.7 us.  Fewer scalar instructions alone do not help: culling
+// 16 tiles at a time (a lane per tile and quarter of the primitives) took 18 % of them away, added
+// 5 % vector instructions, and 65536 poses took 2660 us.
+//
 // One wavefront's tiles t0, t0 + stride, ... below t_end of a particle whose tables are in LDS
 // (s_tab): ray cast, cost terms and, for a gradient, the wrench rows wr ([segment][16-lane
 // row][6], this wavefront's).  Adds the clamped depth terms to acc_td (per lane), the tiles'
@@ -1646,7 +1663,7 @@ __device__ __forceinline__ void cast_tiles(const EvalArgs& a, const TypeMasks& t
                                            int& acc_o) {
   const int n_prim = a.n_prim;
   const Tables L(n_prim);
-  const int4* s_box = reinterpret_cast<const int4*>(s_tab + L.box);
+  const float4* s_box = s_tab + L.box;
   const float4* s_cap = s_tab + L.cap;
   const float2* s_capr = reinterpret_cast<const float2*>(s_tab + L.capr);
   const float* recs = reinterpret_cast<const float*>(s_tab);
@@ -1654,6 +1671,9 @@ __device__ __forceinline__ void cast_tiles(const EvalArgs& a, const TypeMasks& t
   // ((lane >> 3) - cy) sy, so that a tile's rays cost one multiply-add per component
   const float lane_dx = ((float)(lane & 7) - hd.cx) * hd.sx;
   const float lane_dy = ((float)(lane >> 3) - hd.cy) * hd.sy;
+  const float dz = hd.sz, dz2 = hd.sz * hd.sz;
+  // depth of a hidden entry: the background plane, or none
+  const float plane = hd.bg > 0.0f ? hd.bg : INFINITY;
   // gradient: the lane's place in the fold of a row's sums (below)
   const bool odd = lane & 1, odd2 = lane & 2, upper = lane & 8;
   const bool writer = (lane & 4) == 0 && (lane & 10) != 10;
@@ -1675,7 +1695,7 @@ __device__ __forceinline__ void cast_tiles(const EvalArgs& a, const TypeMasks& t
       if (half * kWave >= n_prim) break;
       const int k = lane + half * kWave;
       const int kk = min(k, n_prim - 1);
-      const int4 b = s_box[kk];
+      const float4 b = s_box[kk];
       const float4 cp = s_cap[kk];
       const float2 cq = s_capr[kk];
       // one ballot per comparison, combined on the scalar unit with the half's primitive
@@ -1683,10 +1703,8 @@ __device__ __forceinline__ void cast_tiles(const EvalArgs& a, const TypeMasks& t
       // register and back)
       const int left = n_prim - half * kWave;
       uint64_t m = (left >= kWave ? ~0ull : (1ull << left) - 1ull) &
-                   __builtin_amdgcn_ballot_w64(b.x <= x0 + kTile - 1) &
-                   __builtin_amdgcn_ballot_w64(b.y >= x0) &
-                   __builtin_amdgcn_ballot_w64(b.z <= y0 + kTile - 1) &
-                   __builtin_amdgcn_ballot_w64(b.w >= y0);
+                   __builtin_amdgcn_ballot_w64(fabsf(x0f - b.x) <= b.y) &
+                   __builtin_amdgcn_ballot_w64(fabsf(y0f - b.z) <= b.w);
       if (m) {
         // on every lane (a uniform branch), the result a lane mask combined on the scalar
         // unit: no per-lane branch whose outcome would go through a vector register
@@ -1707,13 +1725,13 @@ __device__ __forceinline__ void cast_tiles(const EvalArgs& a, const TypeMasks& t
     // that their latency overlaps the tests; lane 0 subtracts them after the tests
     const float bg_td = global_ptr(hd.tile_td)[tile_idx];
     const int bg_sk = global_ptr(hd.tile_skin)[tile_idx];
-    const bool valid = (word & kValidBit) != 0;
+    // (a pixel outside the image is 0, so the skin bit stands on valid pixels only)
+    const bool valid = word >= kValidBit;
     const float od = (float)(word & 0xFFFFu);
-    const bool os = (word & kSkinBit) != 0;
+    const bool os = word >= (kValidBit | kSkinBit);
     const float dx = fmaf(x0f, hd.sx, lane_dx);
     const float dy = fmaf(y0f, hd.sy, lane_dy);
-    const float dz = hd.sz;
-    const float dd = fmaf(dx, dx, fmaf(dy, dy, dz * dz));
+    const float dd = fmaf(dx, dx, fmaf(dy, dy, dz2));
     const float inv_dd = fast_rcp(dd);
     float tmin = INFINITY;
     int win = -1;   // tracked for the gradient and the debug images only
@@ -1738,6 +1756,11 @@ __device__ __forceinline__ void cast_tiles(const EvalArgs& a, const TypeMasks& t
           // nearest entry in front of the camera: as unsigned integers the bit patterns of
           // non-negative floats keep their order and negative ones (entries behind the
           // camera) exceed +inf; exact ties keep the first tested (branch-free selects)
+          if (!GRAD && !DEBUG) {
+            const float t = h.ok ? h.t : INFINITY;
+            tmin = __uint_as_float(min(__float_as_uint(t), __float_as_uint(tmin)));
+            continue;
+          }
           const bool take = h.ok & (__float_as_uint(h.t) < __float_as_uint(tmin));
           tmin = take ? h.t : tmin;
           if (GRAD || DEBUG) win = take ? k : win;
@@ -1757,29 +1780,33 @@ __device__ __forceinline__ void cast_tiles(const EvalArgs& a, const TypeMasks& t
         }
       }
     }
-    // depth of the nearest entry; behind the background plane it is hidden
+    // depth of the nearest entry (without one infinite); behind the background plane it is
+    // hidden
     const float zmin = tmin * dz;
-    const bool any = (GRAD || DEBUG) ? win >= 0 : __float_as_uint(tmin) < 0x7F800000u;
-    const bool hit = any & !(hd.bg > 0.0f && zmin >= hd.bg);
-    win = hit ? win : -1;
-    const float rd = hit ? zmin : (hd.bg > 0.0f ? hd.bg : 0.0f);
+    const bool any = __float_as_uint(tmin) < 0x7F800000u;
+    const bool hit = zmin < plane;
+    if (GRAD || DEBUG) win = hit ? win : -1;
+    float rd = fminf(zmin, plane);
+    if (!(hd.bg > 0.0f)) rd = hit ? rd : 0.0f;
     const float diff = fabsf(od - rd);
-    const float td = fminf(diff, kDClamp);
-    const bool rm = hit && (diff < kDMatch || od == 0.0f);
-    acc_td += (double)(valid ? td : 0.0f);
-    {
-      // one ballot per condition, combined on the scalar unit
-      const uint64_t m_valid = __builtin_amdgcn_ballot_w64(valid);
-      const uint64_t m_os = __builtin_amdgcn_ballot_w64(os);
-      const uint64_t m_rm = __builtin_amdgcn_ballot_w64(rm);
-      acc_a += __builtin_popcountll(m_valid & m_os & m_rm);
-      acc_o += __builtin_popcountll(m_valid & (m_os | m_rm));
-    }
+    float td = fminf(diff, kDClamp);
+    td = valid ? td : 0.0f;
+    // (kept in FP32 up to here: the select would be moved behind the conversion, where it takes
+    // two instructions)
+    asm("" : "+v"(td));
+    acc_td += (double)td;
+    // one ballot per comparison, combined on the scalar unit
+    const uint64_t m_valid = __builtin_amdgcn_ballot_w64(valid);
+    const uint64_t m_os = __builtin_amdgcn_ballot_w64(os);
+    const uint64_t m_rm = __builtin_amdgcn_ballot_w64(hit) &
+                          (__builtin_amdgcn_ballot_w64(diff < kDMatch) |
+                           __builtin_amdgcn_ballot_w64(od == 0.0f));
+    acc_a += __builtin_popcountll(m_os & m_rm);
+    acc_o += __builtin_popcountll(m_valid & (m_os | m_rm));
     {
       // read back here (a convergent read, so the wait for the loads stays after the tests)
-      const float bgt = __int_as_float(__builtin_amdgcn_readfirstlane(__float_as_int(bg_td)));
       const int bgs = __builtin_amdgcn_readfirstlane(bg_sk);
-      acc_bg += (double)bgt;
+      acc_bg += (double)bg_td;
       acc_o -= bgs;
     }
     // the debug images have the host's W x H of the debug slot; a frame slot of another
@@ -1788,7 +1815,7 @@ __device__ __forceinline__ void cast_tiles(const EvalArgs& a, const TypeMasks& t
       const size_t pix = ((size_t)r * a.dbg_H + v) * a.dbg_W + u;
       if (a.dbg.depth) a.dbg.depth[pix] = rd;
       if (a.dbg.hit) a.dbg.hit[pix] = hit ? 1 : 0;
-      if (a.dbg.rm) a.dbg.rm[pix] = rm ? 1 : 0;
+      if (a.dbg.rm) a.dbg.rm[pix] = m_rm >> lane & 1 ? 1 : 0;
       if (a.dbg.winner) a.dbg.winner[pix] = win;
       if (a.dbg.margin) a.dbg.margin[pix] = any ? wm : mmax;
     }
