@@ -144,6 +144,7 @@ struct ht_ctx {
   int cap_seg = 0;
   std::map<GraphKey, hipGraphExec_t> graphs;
   void* scratch = nullptr;    // this device's address of the no-allocation scratch array
+  int* d_done = nullptr;   // [n_cu * kMaxGroupsPerCu] parts counted per particle, zero between launches
   unsigned long long* d_eval_count = nullptr;   // [2][kCountSlots] forward / gradient sums
   unsigned int* d_errors = nullptr;              // HT_DEVERR_* flags
   // tracing of eager launches
@@ -405,7 +406,10 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
     a.parts = std::max(1, std::min(most, kSmallGroupsPerCu * c->n_cu / n_total));
     a.grid = n_total * a.parts;
   }
-  a.direct = assemble && !grad && a.parts == 1 ? 1 : 0;
+  // A small launch also writes the costs, unless its parts would have to be counted for a
+  // workspace that is not the context's (a call recorded with the fixed one may run beside it).
+  a.done = small && assemble && (!fixed || a.parts == 1) ? c->d_done : nullptr;
+  a.direct = !small && assemble && !grad && a.parts == 1 ? 1 : 0;
   if (grad) {
     // the nominal grid that sizes a gradient's items (part of its bits, see the work list)
     const long long items =
@@ -428,7 +432,7 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
   for (int stage = small ? kStageFinalize : 0; stage < kNumStages; ++stage) {
     if (stage == kStageFk && src) continue;   // reused from the previous evaluation
     if (stage == kStageFinalize && !assemble) continue;   // assembled by the next kernel
-    if (stage == kStageFinalize && a.direct) continue;   // costs from the ray cast
+    if (stage == kStageFinalize && (a.direct || a.done)) continue;   // costs from the ray cast
     if (stage == kStageSched && (!grad || n_total <= kSelfSchedMax)) continue;   // no work list
     if (fixed)
       HT_HIP(launch_eval_stage(stage, a, ws, s));
@@ -466,6 +470,8 @@ ht_status ht_create(ht_ctx** out, int hip_device) {
   if (e == hipSuccess) e = hipMalloc(&c->d_model, sizeof(ht::DevModel));
   if (e == hipSuccess) e = hipMalloc(&c->d_eval_count, 2 * ht::kCountSlots * sizeof(unsigned long long));
   if (e == hipSuccess) e = hipMemset(c->d_eval_count, 0, 2 * ht::kCountSlots * sizeof(unsigned long long));
+  if (e == hipSuccess) e = hipMalloc(&c->d_done, (size_t)c->n_cu * kMaxGroupsPerCu * sizeof(int));
+  if (e == hipSuccess) e = hipMemset(c->d_done, 0, (size_t)c->n_cu * kMaxGroupsPerCu * sizeof(int));
   if (e == hipSuccess) e = hipMalloc(&c->d_errors, sizeof(unsigned int));
   if (e == hipSuccess) e = hipMemset(c->d_errors, 0, sizeof(unsigned int));
   if (e != hipSuccess) {
@@ -511,6 +517,7 @@ void ht_destroy(ht_ctx* c) {
   dfree(c->d_slots);
   dfree(c->d_model);
   dfree(c->d_eval_count);
+  dfree(c->d_done);
   dfree(c->d_errors);
   delete c;
 }

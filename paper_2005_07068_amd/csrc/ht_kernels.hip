@@ -2023,13 +2023,64 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
 // ------------------------------------------------------------------------------------
 // small forward launches: the whole evaluation in one launch
 
+// A particle's cost from its parts' sums.
+__device__ __forceinline__ float particle_cost(const PInfo& pi, double td, int sa, int so) {
+  return pi.valid ? cost_from_sums(pi.bg_td + td, sa, (long long)pi.bg_or + so, pi.kc)
+                  : (pi.slot < 0 ? NAN : INFINITY);
+}
+
+// The last part of a particle to finish writes its cost (small launches: 16 poses of a 64x64
+// frame 13.0 to 12.0 us, a frame's ingest with one pose 57 to 54.5 us without a finalize launch;
+// of the larger ones 256 poses of a 320x240 frame took 29.3 instead of 30.0 us, 200 of the
+// paper's model 46.4 instead of 46.2, a two-hand refined generation 303.6 instead of 303.0, so
+// they keep theirs).  Called by every lane of the workgroup's first wavefront with the part's
+// sums, which are exact in any order.  A partial passes through agent-scope atomic accesses,
+// visible on every XCD once its stores have completed, and that is waited for before the part is
+// counted; a release fence would write the XCD's whole L2 back (256 poses: 54 us).  The counter
+// is left at zero for the next launch.
+__device__ __forceinline__ void finish_part(const EvalArgs& a, const Workspace& ws, int r,
+                                            int item, int n_parts, double td, int sa, int so,
+                                            const PInfo& pi, int lane) {
+  int before = 0;
+  if (lane == 0 && n_parts > 1) {
+    uint64_t* q = reinterpret_cast<uint64_t*>(ws.partial + item);
+    __hip_atomic_store(q, (uint64_t)__double_as_longlong(td), __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    __hip_atomic_store(q + 1, (uint64_t)(uint32_t)so << 32 | (uint32_t)sa, __ATOMIC_RELAXED,
+                       __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
+    before = __hip_atomic_fetch_add(a.done + r, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  }
+  if (uni(before) + 1 != n_parts) return;
+  if (n_parts == 1) {
+    if (lane == 0) a.cost[r] = particle_cost(pi, td, sa, so);
+    return;
+  }
+  if (lane == 0) __hip_atomic_store(a.done + r, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  double d = 0.0;
+  int ia = 0, io = 0;
+  for (int i = lane; i < n_parts; i += kWave) {
+    uint64_t* q = reinterpret_cast<uint64_t*>(ws.partial + (size_t)r * a.parts + i);
+    const uint64_t q0 = __hip_atomic_load(q, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    const uint64_t q1 = __hip_atomic_load(q + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    d += __longlong_as_double(q0);
+    ia += (int)(uint32_t)q1;
+    io += (int)(uint32_t)(q1 >> 32);
+  }
+  d = wave_sum(d);
+  ia = wave_sum(ia);
+  io = wave_sum(io);
+  if (lane == 0) a.cost[r] = particle_cost(pi, d, ia, io);
+}
+
 // One workgroup per part of a particle: the kinematics (repeated in every part, on CUs that would
 // be idle otherwise), its tables kept in LDS, then the part's tiles.  A chain of latencies (about
 // 5 us of kinematics, 1 us per tile of a wavefront): against separate launches it saves one launch
 // gap and the tables' way through memory (16 poses of a 64x64 frame 17.9 to 14.9 us, 64 of a
 // 128x128 frame 18.1 to 15.3 us).  Workgroups of eight and sixteen wavefronts, with fewer parts,
 // lost more to the barriers than they saved (15.8 and 17.3 us).
-template <int NT>
+// FINISH: the costs are written here (else the partials are assembled by the next kernel).
+template <int NT, bool FINISH>
 __global__ __launch_bounds__(kBlock) void small_eval_kernel(EvalArgs a, Workspace ws,
                                                             TypeMasks tm) {
   extern __shared__ float4 s_tab[];
@@ -2045,7 +2096,7 @@ __global__ __launch_bounds__(kBlock) void small_eval_kernel(EvalArgs a, Workspac
       a, ws, sh, r, 0, wave, lane, n_total, s_tab, [&](const PInfo& pi, int l) {
         if (l == 0) {
           s_head = pi;
-          if (!a.direct && part == 0) ws.pinfo[r] = pi;
+          if (!FINISH && part == 0) ws.pinfo[r] = pi;
         }
       });
   if (!cast) return;   // (a skipped particle)
@@ -2063,18 +2114,16 @@ __global__ __launch_bounds__(kBlock) void small_eval_kernel(EvalArgs a, Workspac
     s_o[wave] = acc_o;
   }
   __syncthreads();
-  if (tid == 0) {
-    const double td = ((s_td[0] + s_td[1]) + s_td[2]) + s_td[3];
-    const int sa = s_a[0] + s_a[1] + s_a[2] + s_a[3];
-    const int so = s_o[0] + s_o[1] + s_o[2] + s_o[3];
-    const PInfo& pi = s_head;
-    if (a.direct)
-      a.cost[r] = pi.valid ? cost_from_sums(pi.bg_td + td, sa, (long long)pi.bg_or + so, pi.kc)
-                           : (pi.slot < 0 ? NAN : INFINITY);
-    else
-      ws.partial[item] = Partial{td, sa, so};
-    if (part == 0 && a.eval_count) atomicAdd(&a.eval_count[blockIdx.x % kCountSlots], 1ull);
-  }
+  if (FINISH ? wave != 0 : tid != 0) return;
+  const double td = ((s_td[0] + s_td[1]) + s_td[2]) + s_td[3];
+  const int sa = s_a[0] + s_a[1] + s_a[2] + s_a[3];
+  const int so = s_o[0] + s_o[1] + s_o[2] + s_o[3];
+  if (!FINISH)
+    ws.partial[item] = Partial{td, sa, so};
+  else if (part < active_parts(hd.n_tiles, parts))
+    finish_part(a, ws, r, item, active_parts(hd.n_tiles, parts), td, sa, so, s_head, lane);
+  if (lane == 0 && part == 0 && a.eval_count)
+    atomicAdd(&a.eval_count[blockIdx.x % kCountSlots], 1ull);
 }
 
 // ------------------------------------------------------------------------------------
@@ -2560,12 +2609,9 @@ hipError_t launch_eval_stage(int stage, const EvalArgs& a, const Workspace& ws, 
       const bool all = (tm.m[HT_CONE][0] | tm.m[HT_CONE][1] | tm.m[HT_ECYLINDER][0] |
                         tm.m[HT_ECYLINDER][1]) != 0ull;
       const size_t lds = raycast_lds(false, a.n_prim, a.n_seg);
-      if (all)
-        hipLaunchKernelGGL(small_eval_kernel<kNumTypes>, dim3(n_total * a.parts), dim3(kBlock),
-                           lds, s, a, ws, tm);
-      else
-        hipLaunchKernelGGL(small_eval_kernel<3>, dim3(n_total * a.parts), dim3(kBlock), lds, s,
-                           a, ws, tm);
+      const auto f = a.done ? (all ? small_eval_kernel<kNumTypes, true> : small_eval_kernel<3, true>)
+                            : (all ? small_eval_kernel<kNumTypes, false> : small_eval_kernel<3, false>);
+      hipLaunchKernelGGL(f, dim3(n_total * a.parts), dim3(kBlock), lds, s, a, ws, tm);
       break;
     }
     case kStageFk:

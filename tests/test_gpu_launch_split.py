@@ -185,3 +185,24 @@ def test_swarm_update_in_one_launch_matches_the_oracle(cfg_idx, P):
         ok = np.isfinite(ref[k])
         assert np.allclose(after[k][ok], ref[k][ok], rtol=1e-5, atol=2e-5), k
     ctx.close()
+
+
+@pytest.mark.parametrize("n", [1, 2, 16, 64])
+def test_the_last_part_writes_the_cost_in_every_call(n):
+    """Consecutive launches of other poses (a NaN and an image-filling one among them): the parts
+    are counted from zero each time.  The no-allocation entry assembles its partials in a launch of
+    its own, so its costs are the reference, bit for bit."""
+    torch = torch_cuda()
+    dev = torch.device("cuda:0")
+    cfg, model, fr = frame_for(1)
+    ctx = make_ctx(model, [fr])
+    slots = torch.zeros(1, dtype=torch.int32, device=dev)
+    for call in range(6):
+        x = torch.tensor(particles_for(model, fr, n, seed=70 + call), device=dev)
+        if call == 1:
+            x[n // 2, 3] = float("nan")
+        if call == 2:
+            x[n - 1, 2] = 0.0                       # a hand around the camera covers the frame
+        got = ctx.eval(x, slots).cpu().numpy()
+        ref = ctx.eval_noalloc(x, slots).cpu().numpy()
+        assert np.array_equal(got, ref, equal_nan=True), call
