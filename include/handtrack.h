@@ -304,12 +304,11 @@ ht_status ht_pso_run_graph(ht_ctx* ctx, const ht_swarm* swarm, const ht_pso_para
 ht_status ht_pso_box_around(ht_ctx* ctx, int n_frames, const float* center,
                             const float* halfwidth, float* lo, float* hi, void* hip_stream);
 
-/* Launch shape of the batched persistent ray-cast kernel.  The work items follow from the launch
+/* Launch shape of the batched persistent ray-cast kernel.  Forward work follows from the launch
  * itself: whole particles where there are more of them than workgroups, else equal parts of a
- * particle, one per workgroup.  tiles_per_item is checked and kept for callers that set it and
- * does not change the items. */
+ * particle, one per workgroup.  tiles_per_item bounds the work items of gradient launches. */
 typedef struct {
-  int32_t tiles_per_item;   /* 4..1024 (see above)                                          */
+  int32_t tiles_per_item;   /* 4..1024: most tiles per gradient work item                   */
   int32_t groups_per_cu;    /* persistent workgroups per compute unit: 1..3, or 4 and more
                                for as many as fit                                           */
   int32_t cull;             /* 0: primitive screen boxes from their 3D bounding boxes;
@@ -321,9 +320,9 @@ ht_status ht_set_launch_config(ht_ctx* ctx, const ht_launch_config* cfg);
 
 /* Autotune the launch shape on the given workload (timed with HIP events on hip_stream,
  * synchronising it), keep the fastest in the context and return it in *out.
- * The candidates are tiles_per_item in {4..64} x groups_per_cu in {1..8} (powers of two) x
- * cull in {0, 1}, tried from cull 1, 64 tiles and 8 workgroups down; a candidate must be more
- * than 1 % faster than the best before it to replace it. */
+ * The candidates are groups_per_cu in {1..8} (powers of two) x cull in {0, 1} with 64 tiles per
+ * item, tried from cull 1 and 8 workgroups down; a candidate must be more than 1 % faster than the
+ * best before it to replace it. */
 ht_status ht_autotune(ht_ctx* ctx, int n_frames, const int32_t* frame_slots, int n_particles,
                       const float* poses, float* cost, int repeats, ht_launch_config* out,
                       void* hip_stream);

@@ -2613,7 +2613,7 @@ int raycast_groups_per_cu(bool grad, bool dbg, bool all_types, bool self, int n_
   return r;
 }
 
-// The evaluation is three launches on one stream; `stage` selects one so the host can
+// The evaluation is one to four launches on one stream; `stage` selects one so the host can
 // bracket each with HIP events when profiling.
 hipError_t launch_eval_stage(int stage, const EvalArgs& a, const Workspace& ws, hipStream_t s) {
   const int n_total = a.n_frames * a.n_particles;
