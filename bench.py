@@ -37,9 +37,9 @@ METRIC = "particle evals/s (render+cost, +adjoint) and ms/frame vs plain PSO at 
 # FP32 operations (SQ_INSTS_VALU_FLOPS_FP32 x 64 lanes).  Keyed by the SHA-256 of the kernel
 # sources they were measured on: any later change of the kernel reports null.
 MEASURED_COUNTERS = {
-    "b8e10b079db9c15c2a359c301d7148ed1447a763777aa38a022bfda969d3f8a1": {
-        "config": 4, "fetch_kib": 9098.114, "write_kib": 234.957, "fetch_scale": 2.0,
-        "write_scale": 1.0, "fp32_flop": 2.170e9},
+    "2fca6c4447cd256ccd0ab9d7fbd1912a4c3580c889491ea60aaf81922d29f993": {
+        "config": 4, "fetch_kib": 3359.264, "write_kib": 49.831, "fetch_scale": 2.0,
+        "write_scale": 1.0, "fp32_flop": 2.220e9},
 }
 KERNEL_SOURCES = ("paper_2005_07068_amd/csrc/ht_kernels.hip",
                   "paper_2005_07068_amd/csrc/ht_device.h")
@@ -497,7 +497,7 @@ def roofline_figures(work, avg_ms, particles_per_launch, model, frames, counters
     alg_bytes = particles_per_launch * (pose_b + 4) + obs_b
     return {"bound": "alu", "achieved": achieved / 1e12, "peak": PEAK_FP32_VALU / 1e12,
             "unit": "TFLOP/s", "frac": achieved / PEAK_FP32_VALU, "traffic": traffic,
-            # both variants: the swarm's launches and the self-scheduled small ones
+            # the swarm's launches and the refinement's last ones
             "kernel": "raycast_kernel<false,false,%d,*>" % (5 if model["prim_type"].max() > 2
                                                             else 3),
             "avg_launch_ms": avg_ms, "particles_per_launch": particles_per_launch,
