@@ -213,9 +213,11 @@ bool workspace_fits(const ht_ctx* c, int n_total, int max_tiles, bool grad) {
 constexpr int kMaxGroupsPerCu = 8;     // 2048 threads
 constexpr int kListGroupsPerCu = 5;    // nominal workgroups per CU of a gradient work list
 constexpr int kTilesPerPart = 16;      // tiles of the observation per part, at least
-constexpr int kSmallParticles = 64;    // launches in one kernel (see eval_impl)
+constexpr int kSmallParticles = 128;   // launches in one kernel (see eval_impl)
 constexpr int kSmallTiles = 32768;
 constexpr int kSmallGroupsPerCu = 3;
+constexpr int kFewParts = 8;           // two workgroups per CU give a particle as many, at least
+constexpr int kFewTiles = 128;         // and a part at most this many tiles of the observation
 long long item_bound(const ht_ctx* c, long long n_total, int max_tiles, bool grad) {
   const long long fwd = std::max<long long>(n_total, (long long)kMaxGroupsPerCu * c->n_cu);
   return grad ? std::max(fwd, n_total * ((max_tiles + kMinTilesPerItem - 1) / kMinTilesPerItem)) : fwd;
@@ -395,15 +397,21 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
   const int most = (c->max_tiles() + kTilesPerPart - 1) / kTilesPerPart;
   a.parts = grad ? 1 : std::max(1, std::min(most, full / n_total));
   a.grid = grad ? full : (int)std::min<long long>(full, (long long)n_total * a.parts);
-  // Small forward launches take the kinematics and the cast in one: up to 64 particles of any
-  // size (64 poses: 320x240 21.1 to 18.8 us, two hands at 640x480 26.5 to 25.4 us), more of small
-  // observations (128 of 128x128 21.5 to 18.4 us, 200 of them 22.1 to 24.7 us: few parts repeat
-  // the kinematics on busy CUs).  Three workgroups fit a CU.
+  // Small forward launches take the kinematics and the cast in one: up to 128 particles of any
+  // size (64 poses: 320x240 21.1 to 18.8 us, two hands at 640x480 26.5 to 25.4 us; 128 poses 23.0
+  // to 19.6 us and 31.3 to 30.3 us; 192 poses 26.1 to 33 us), more of small observations (128 of
+  // 128x128 21.5 to 18.4 us, 200 of them 22.1 to 24.7 us: few parts repeat the kinematics on busy
+  // CUs).  Three workgroups fit a CU; two are better while a particle keeps eight parts and these
+  // stay short (32 poses of 320x240 15.7 to 13.9 us, 64 of 128x128 14.0 to 13.1 us, four two-hand
+  // poses 14.7 to 14.0 us), not where the parts grow long or few (64 poses of 320x240 15.9 to
+  // 16.6 us, 64 two-hand ones 21.7 to 23.5 us, 128 of 128x128 15.0 to 15.4 us).
   const bool small = !grad && !dbg_on && !src && !adjoint && !active &&
                      (n_total <= kSmallParticles ||
                       (long long)n_total * c->max_tiles() <= kSmallTiles);
   if (small) {
-    a.parts = std::max(1, std::min(most, kSmallGroupsPerCu * c->n_cu / n_total));
+    const int two = 2 * c->n_cu / n_total;
+    const bool few = two >= kFewParts && c->max_tiles() <= kFewTiles * two;
+    a.parts = std::max(1, std::min(most, few ? two : kSmallGroupsPerCu * c->n_cu / n_total));
     a.grid = n_total * a.parts;
   }
   // A small launch also writes the costs, unless its parts would have to be counted for a

@@ -187,7 +187,7 @@ def test_swarm_update_in_one_launch_matches_the_oracle(cfg_idx, P):
     ctx.close()
 
 
-@pytest.mark.parametrize("n", [1, 2, 16, 64])
+@pytest.mark.parametrize("n", [1, 2, 16, 64, 65, 128, 129])
 def test_the_last_part_writes_the_cost_in_every_call(n):
     """Consecutive launches of other poses (a NaN and an image-filling one among them): the parts
     are counted from zero each time.  The no-allocation entry assembles its partials in a launch of
