@@ -123,7 +123,7 @@ def test_refinement_larger_than_the_grid():
 @pytest.mark.parametrize("cfg_idx,n", [(4, 1), (4, 64), (5, 3), (5, 64), (1, 128), (1, 129), (0, 512),
                                        (0, 513)])
 def test_evaluation_in_one_launch_equals_separate_launches(cfg_idx, n):
-    """Small forward launches (at most 64 particles, or few tiles: 128 of a 128x128 frame, 512 of
+    """Small forward launches (at most 128 particles, or few tiles: 128 of a 128x128 frame, 512 of
     a 64x64 one) repeat the kinematics in every part; the costs of a gradient evaluation, which
     never does, on both sides of the switch, for one and two hands and both primitive sets."""
     torch = torch_cuda()
