@@ -144,7 +144,8 @@ struct ht_ctx {
   int cap_seg = 0;
   std::map<GraphKey, hipGraphExec_t> graphs;
   void* scratch = nullptr;    // this device's address of the no-allocation scratch array
-  int* d_done = nullptr;   // [n_cu * kMaxGroupsPerCu] parts counted per particle, zero between launches
+  unsigned long long* d_done = nullptr;   // [n_cu * kMaxGroupsPerCu] parts counted per particle
+  unsigned long long done_base = 0;       // what the last launch that counted them started at
   unsigned long long* d_eval_count = nullptr;   // [2][kCountSlots] forward / gradient sums
   unsigned int* d_errors = nullptr;              // HT_DEVERR_* flags
   // tracing of eager launches
@@ -218,6 +219,7 @@ constexpr int kSmallTiles = 32768;
 constexpr int kSmallGroupsPerCu = 3;
 constexpr int kFewParts = 8;           // two workgroups per CU give a particle as many, at least
 constexpr int kFewTiles = 128;         // and a part at most this many tiles of the observation
+constexpr unsigned long long kDoneStep = 1ull << 16;   // more than a launch's parts
 long long item_bound(const ht_ctx* c, long long n_total, int max_tiles, bool grad) {
   const long long fwd = std::max<long long>(n_total, (long long)kMaxGroupsPerCu * c->n_cu);
   return grad ? std::max(fwd, n_total * ((max_tiles + kMinTilesPerItem - 1) / kMinTilesPerItem)) : fwd;
@@ -414,9 +416,12 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
     a.parts = std::max(1, std::min(most, few ? two : kSmallGroupsPerCu * c->n_cu / n_total));
     a.grid = n_total * a.parts;
   }
-  // A small launch also writes the costs, unless its parts would have to be counted for a
-  // workspace that is not the context's (a call recorded with the fixed one may run beside it).
-  a.done = small && assemble && (!fixed || a.parts == 1) ? c->d_done : nullptr;
+  // A small launch also writes the costs.  Parts are counted for it only in the context's own
+  // workspace and outside capture: a call recorded with the fixed one may run beside it, and the
+  // replays of a recorded launch would all count from one base.
+  const bool counts = small && assemble && a.parts > 1 && !fixed && !capturing(s);
+  a.done = small && assemble && (a.parts == 1 || counts) ? c->d_done : nullptr;
+  if (counts) a.done_base = c->done_base += kDoneStep;
   a.direct = !small && assemble && !grad && a.parts == 1 ? 1 : 0;
   if (grad) {
     // the nominal grid that sizes a gradient's items (part of its bits, see the work list)
@@ -478,8 +483,8 @@ ht_status ht_create(ht_ctx** out, int hip_device) {
   if (e == hipSuccess) e = hipMalloc(&c->d_model, sizeof(ht::DevModel));
   if (e == hipSuccess) e = hipMalloc(&c->d_eval_count, 2 * ht::kCountSlots * sizeof(unsigned long long));
   if (e == hipSuccess) e = hipMemset(c->d_eval_count, 0, 2 * ht::kCountSlots * sizeof(unsigned long long));
-  if (e == hipSuccess) e = hipMalloc(&c->d_done, (size_t)c->n_cu * kMaxGroupsPerCu * sizeof(int));
-  if (e == hipSuccess) e = hipMemset(c->d_done, 0, (size_t)c->n_cu * kMaxGroupsPerCu * sizeof(int));
+  if (e == hipSuccess) e = hipMalloc(&c->d_done, (size_t)c->n_cu * kMaxGroupsPerCu * sizeof(*c->d_done));
+  if (e == hipSuccess) e = hipMemset(c->d_done, 0, (size_t)c->n_cu * kMaxGroupsPerCu * sizeof(*c->d_done));
   if (e == hipSuccess) e = hipMalloc(&c->d_errors, sizeof(unsigned int));
   if (e == hipSuccess) e = hipMemset(c->d_errors, 0, sizeof(unsigned int));
   if (e != hipSuccess) {

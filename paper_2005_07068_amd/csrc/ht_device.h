@@ -170,8 +170,10 @@ struct EvalArgs {
   int tiles_per_item;          // gradient work list: most tiles per item, and the nominal grid
   int list_grid;               // that its items are sized for
   int direct;                  // 1 (forward, whole particles): the ray cast writes the costs
-  int* done;                   // small launches: [n_total] parts counted per particle, zero between
-                               // launches (the last one writes the cost); NULL: partials only
+  // small launches: [n_total] parts counted per particle from done_base on (the last one writes
+  // the cost); NULL: partials only
+  unsigned long long* done;
+  unsigned long long done_base;
   int n_prim, n_seg, n_dof;
 };
 

@@ -2077,29 +2077,32 @@ __device__ __forceinline__ float particle_cost(const PInfo& pi, double td, int s
 // of the larger ones 256 poses of a 320x240 frame took 29.3 instead of 30.0 us, 200 of the
 // paper's model 46.4 instead of 46.2, a two-hand refined generation 303.6 instead of 303.0, so
 // they keep theirs).  Called by every lane of the workgroup's first wavefront with the part's
-// sums, which are exact in any order.  A partial passes through agent-scope atomic accesses,
-// visible on every XCD once its stores have completed, and that is waited for before the part is
-// counted; a release fence would write the XCD's whole L2 back (256 poses: 54 us).  The counter
-// is left at zero for the next launch.
+// sums, which are exact in any order.  A partial passes through agent-scope atomic accesses, the
+// count through a release and the last part through an acquire.
+// The counter is zero between launches.  A count left behind by launches that overlapped against
+// the rules must not reach a later one, so every launch counts from a base of its own, higher
+// than those before it, which the parts raise the counter to.
 __device__ __forceinline__ void finish_part(const EvalArgs& a, const Workspace& ws, int r,
                                             int item, int n_parts, double td, int sa, int so,
                                             const PInfo& pi, int lane) {
+  if (n_parts == 1) {
+    if (lane == 0) a.cost[r] = particle_cost(pi, td, sa, so);
+    return;
+  }
   int before = 0;
-  if (lane == 0 && n_parts > 1) {
+  if (lane == 0) {
     uint64_t* q = reinterpret_cast<uint64_t*>(ws.partial + item);
     __hip_atomic_store(q, (uint64_t)__double_as_longlong(td), __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
     __hip_atomic_store(q + 1, (uint64_t)(uint32_t)so << 32 | (uint32_t)sa, __ATOMIC_RELAXED,
                        __HIP_MEMORY_SCOPE_AGENT);
-    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");
-    before = __hip_atomic_fetch_add(a.done + r, 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    (void)__hip_atomic_fetch_max(a.done + r, a.done_base, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    before = (int)(__hip_atomic_fetch_add(a.done + r, 1ull, __ATOMIC_RELEASE,
+                                          __HIP_MEMORY_SCOPE_AGENT) - a.done_base);
   }
   if (uni(before) + 1 != n_parts) return;
-  if (n_parts == 1) {
-    if (lane == 0) a.cost[r] = particle_cost(pi, td, sa, so);
-    return;
-  }
-  if (lane == 0) __hip_atomic_store(a.done + r, 0, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "agent");
+  if (lane == 0) __hip_atomic_store(a.done + r, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   double d = 0.0;
   int ia = 0, io = 0;
   for (int i = lane; i < n_parts; i += kWave) {
