@@ -390,7 +390,7 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
   const int lc = c->lc.groups_per_cu;
   const int fit = std::min(resident_groups(c, grad != nullptr, dbg_on, all_types,
                                            n_total <= kSelfSchedMax), kMaxGroupsPerCu);
-  const int full = std::max(c->n_cu * (lc >= 4 ? fit : std::min(lc, fit)), 8);
+  const int full = std::max(c->n_cu * (lc >= 4 ? fit : std::min(lc, fit)), kQueues);
   // Parts per particle: as many as give every resident workgroup one item, rounded down (a
   // launch with more items than workgroups waits for the few that take two: 256 poses of a
   // 320x240 frame 34 us with one item per workgroup, 39 us with two), but parts of 16 tiles of
@@ -430,7 +430,9 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
     a.tiles_per_item = c->lc.tiles_per_item;
     a.list_grid = (int)std::max<long long>(
         1, std::min<long long>((long long)c->n_cu * std::min(lc, kListGroupsPerCu), items));
-    a.grid = (int)std::max<long long>(1, std::min<long long>(full, items));
+    // (a recorded launch may be replayed on larger observations, with more items than workgroups:
+    // every queue needs one)
+    a.grid = (int)std::max<long long>(kQueues, std::min<long long>(full, items));
   }
   a.n_prim = c->n_prim;
   a.n_seg = c->n_seg;

@@ -15,7 +15,9 @@ constexpr int kBlock = 256;         // 4 wavefronts per workgroup
 constexpr int kWavesPerBlock = kBlock / kWave;
 constexpr int kRec = 20;            // floats per primitive record
 constexpr int kNumTypes = 5;        // HT_SPHERE .. HT_ECYLINDER
-constexpr int kCounterInts = 8 * 256;   // work queue counters of one launch
+constexpr int kQueues = 8;          // work queues of the ray cast: a grid has as many workgroups
+constexpr int kQueueStride = 256;   // at least; ints between two queues' counters (1 KB)
+constexpr int kCounterInts = kQueues * kQueueStride;
 constexpr float kDMatch = 10.0f;    // d_m, mm
 constexpr float kDClamp = 40.0f;    // d_M, mm
 constexpr double kLambda = 20.0;

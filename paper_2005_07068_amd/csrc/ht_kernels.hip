@@ -76,10 +76,6 @@ __device__ __forceinline__ double wave_sum(double v) {
   v = dpp_add<0x128>(dpp_add<0x124>(dpp_add<0x4E>(dpp_add<0xB1>(v))));
   return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
 }
-// Work queues of the ray cast (below) and the ints between two queues' counters (1 KB).
-constexpr int kQueues = 8;
-constexpr int kQueueStride = 256;
-static_assert(kQueues * kQueueStride == kCounterInts, "room for the counters of one launch");
 
 // C = A * B for 3x4 affine transforms (row-major, implicit last row 0 0 0 1).
 __device__ inline void mul34(const double* A, const double* B, double* C) {
