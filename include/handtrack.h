@@ -313,7 +313,9 @@ ht_status ht_pso_box_around(ht_ctx* ctx, int n_frames, const float* center,
 typedef struct {
   int32_t tiles_per_item;   /* 4..1024: most tiles per gradient work item                   */
   int32_t groups_per_cu;    /* persistent workgroups per compute unit: 1..3, or 4 and more
-                               for as many as fit                                           */
+                               for as many as fit.  A gradient's work items are sized for
+                               this many, at most 5; forward launches of few particles take
+                               no account of it                                             */
   int32_t cull;             /* 0: primitive screen boxes from their 3D bounding boxes;
                                1: clipped to the image extent of a bounding capsule        */
 } ht_launch_config;
@@ -324,8 +326,9 @@ ht_status ht_set_launch_config(ht_ctx* ctx, const ht_launch_config* cfg);
 /* Autotune the launch shape on the given workload (timed with HIP events on hip_stream,
  * synchronising it), keep the fastest in the context and return it in *out.
  * The candidates are groups_per_cu in {1..8} (powers of two) x cull in {0, 1} with 64 tiles per
- * item, tried from cull 1 and 8 workgroups down; a candidate must be more than 1 % faster than the
- * best before it to replace it. */
+ * item, tried from cull 1 and 8 workgroups down, less those that launch this workload as the
+ * candidate before them does; a candidate must be more than 1 % faster than the best before it to
+ * replace it. */
 ht_status ht_autotune(ht_ctx* ctx, int n_frames, const int32_t* frame_slots, int n_particles,
                       const float* poses, float* cost, int repeats, ht_launch_config* out,
                       void* hip_stream);

@@ -333,6 +333,53 @@ static int resident_groups(ht_ctx* c, bool grad, bool dbg, bool all_types, bool 
   return n;
 }
 
+// Workgroups of a ray cast at most: groups_per_cu per CU, four and more standing for every workgroup
+// that fits (five to eight of them); a cap at four left 65536 poses of a 320x240 frame at 3.53 ms
+// against 2.71 ms with eight.
+static int grid_limit(ht_ctx* c, int groups_per_cu, bool grad, bool dbg, int n_total) {
+  const bool all_types = (c->tmask.m[HT_CONE][0] | c->tmask.m[HT_CONE][1] |
+                          c->tmask.m[HT_ECYLINDER][0] | c->tmask.m[HT_ECYLINDER][1]) != 0ull;
+  const int fit = std::min(resident_groups(c, grad, dbg, all_types, n_total <= kSelfSchedMax),
+                           kMaxGroupsPerCu);
+  return std::max(c->n_cu * (groups_per_cu >= 4 ? fit : std::min(groups_per_cu, fit)), kQueues);
+}
+
+// How a forward launch of n_total particles is split, with at most `full` workgroups; one: it may
+// take the kinematics and the cast in one kernel.
+struct ForwardShape {
+  bool small;        // one kernel
+  int parts, grid;   // parts per particle, workgroups of the cast
+};
+static ForwardShape forward_shape(const ht_ctx* c, int n_total, int full, bool one) {
+  // Parts per particle: as many as give every resident workgroup one item, rounded down (a
+  // launch with more items than workgroups waits for the few that take two: 256 poses of a
+  // 320x240 frame 34 us with one item per workgroup, 39 us with two), but parts of 16 tiles of
+  // the observation at least (64 poses of a 128x128 frame: 16 parts 27.2 us per generation, 32
+  // parts 30.9 us: their workgroups' start costs more than the few tiles they take over).
+  const int most = (c->max_tiles() + kTilesPerPart - 1) / kTilesPerPart;
+  ForwardShape f{};
+  // Small forward launches take the kinematics and the cast in one: up to 128 particles of any
+  // size (64 poses: 320x240 21.1 to 18.8 us, two hands at 640x480 26.5 to 25.4 us; 128 poses 23.0
+  // to 19.6 us and 31.3 to 30.3 us; 192 poses 26.1 to 33 us), more of small observations (128 of
+  // 128x128 21.5 to 18.4 us, 200 of them 22.1 to 24.7 us: few parts repeat the kinematics on busy
+  // CUs).  Three workgroups fit a CU; two are better while a particle keeps eight parts and these
+  // stay short (32 poses of 320x240 15.7 to 13.9 us, 64 of 128x128 14.0 to 13.1 us, four two-hand
+  // poses 14.7 to 14.0 us), not where the parts grow long or few (64 poses of 320x240 15.9 to
+  // 16.6 us, 64 two-hand ones 21.7 to 23.5 us, 128 of 128x128 15.0 to 15.4 us).
+  f.small = one && (n_total <= kSmallParticles ||
+                    (long long)n_total * c->max_tiles() <= kSmallTiles);
+  if (f.small) {
+    const int two = 2 * c->n_cu / n_total;
+    const bool few = two >= kFewParts && c->max_tiles() <= kFewTiles * two;
+    f.parts = std::max(1, std::min(most, few ? two : kSmallGroupsPerCu * c->n_cu / n_total));
+    f.grid = n_total * f.parts;
+  } else {
+    f.parts = std::max(1, std::min(most, full / n_total));
+    f.grid = (int)std::min<long long>(full, (long long)n_total * f.parts);
+  }
+  return f;
+}
+
 // Evaluation shared by ht_eval_particles, ht_eval_particles_grad and the swarm step.
 // With src, particle r of frame f reuses the kinematics that the previous evaluation (of
 // src_stride particles per frame) left for its particle src[r] of frame f: poses must equal
@@ -383,38 +430,24 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
   a.cull = c->lc.cull;
   a.adjoint = adjoint || grad ? 1 : 0;
   const bool dbg_on = a.dbg.depth || a.dbg.hit || a.dbg.rm || a.dbg.winner || a.dbg.margin;
-  const bool all_types = (c->tmask.m[HT_CONE][0] | c->tmask.m[HT_CONE][1] |
-                          c->tmask.m[HT_ECYLINDER][0] | c->tmask.m[HT_ECYLINDER][1]) != 0ull;
-  // groups_per_cu: four and more stand for every workgroup that fits (five to eight of them);
-  // a cap at four left 65536 poses of a 320x240 frame at 3.53 ms against 2.71 ms with eight
-  const int lc = c->lc.groups_per_cu;
-  const int fit = std::min(resident_groups(c, grad != nullptr, dbg_on, all_types,
-                                           n_total <= kSelfSchedMax), kMaxGroupsPerCu);
-  const int full = std::max(c->n_cu * (lc >= 4 ? fit : std::min(lc, fit)), kQueues);
-  // Parts per particle: as many as give every resident workgroup one item, rounded down (a
-  // launch with more items than workgroups waits for the few that take two: 256 poses of a
-  // 320x240 frame 34 us with one item per workgroup, 39 us with two), but parts of 16 tiles of
-  // the observation at least (64 poses of a 128x128 frame: 16 parts 27.2 us per generation, 32
-  // parts 30.9 us: their workgroups' start costs more than the few tiles they take over).
-  const int most = (c->max_tiles() + kTilesPerPart - 1) / kTilesPerPart;
-  a.parts = grad ? 1 : std::max(1, std::min(most, full / n_total));
-  a.grid = grad ? full : (int)std::min<long long>(full, (long long)n_total * a.parts);
-  // Small forward launches take the kinematics and the cast in one: up to 128 particles of any
-  // size (64 poses: 320x240 21.1 to 18.8 us, two hands at 640x480 26.5 to 25.4 us; 128 poses 23.0
-  // to 19.6 us and 31.3 to 30.3 us; 192 poses 26.1 to 33 us), more of small observations (128 of
-  // 128x128 21.5 to 18.4 us, 200 of them 22.1 to 24.7 us: few parts repeat the kinematics on busy
-  // CUs).  Three workgroups fit a CU; two are better while a particle keeps eight parts and these
-  // stay short (32 poses of 320x240 15.7 to 13.9 us, 64 of 128x128 14.0 to 13.1 us, four two-hand
-  // poses 14.7 to 14.0 us), not where the parts grow long or few (64 poses of 320x240 15.9 to
-  // 16.6 us, 64 two-hand ones 21.7 to 23.5 us, 128 of 128x128 15.0 to 15.4 us).
-  const bool small = !grad && !dbg_on && !src && !adjoint && !active &&
-                     (n_total <= kSmallParticles ||
-                      (long long)n_total * c->max_tiles() <= kSmallTiles);
-  if (small) {
-    const int two = 2 * c->n_cu / n_total;
-    const bool few = two >= kFewParts && c->max_tiles() <= kFewTiles * two;
-    a.parts = std::max(1, std::min(most, few ? two : kSmallGroupsPerCu * c->n_cu / n_total));
-    a.grid = n_total * a.parts;
+  const int full = grid_limit(c, c->lc.groups_per_cu, grad != nullptr, dbg_on, n_total);
+  bool small = false;
+  if (grad) {
+    a.parts = 1;
+    // the nominal grid that sizes a gradient's items (part of its bits, see the work list)
+    const long long items =
+        (long long)n_total * ((c->max_tiles() + kMinTilesPerItem - 1) / kMinTilesPerItem);
+    a.tiles_per_item = c->lc.tiles_per_item;
+    a.list_grid = (int)std::max<long long>(
+        1, std::min<long long>((long long)c->n_cu * std::min(c->lc.groups_per_cu, kListGroupsPerCu), items));
+    // (a recorded launch may be replayed on larger observations, with more items than workgroups:
+    // every queue needs one)
+    a.grid = (int)std::max<long long>(kQueues, std::min<long long>(full, items));
+  } else {
+    const ForwardShape f = forward_shape(c, n_total, full, !dbg_on && !src && !adjoint && !active);
+    small = f.small;
+    a.parts = f.parts;
+    a.grid = f.grid;
   }
   // A small launch also writes the costs.  Parts are counted for it only in the context's own
   // workspace and outside capture: a call recorded with the fixed one may run beside it, and the
@@ -423,17 +456,6 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
   a.done = small && assemble && (a.parts == 1 || counts) ? c->d_done : nullptr;
   if (counts) a.done_base = c->done_base += kDoneStep;
   a.direct = !small && assemble && !grad && a.parts == 1 ? 1 : 0;
-  if (grad) {
-    // the nominal grid that sizes a gradient's items (part of its bits, see the work list)
-    const long long items =
-        (long long)n_total * ((c->max_tiles() + kMinTilesPerItem - 1) / kMinTilesPerItem);
-    a.tiles_per_item = c->lc.tiles_per_item;
-    a.list_grid = (int)std::max<long long>(
-        1, std::min<long long>((long long)c->n_cu * std::min(lc, kListGroupsPerCu), items));
-    // (a recorded launch may be replayed on larger observations, with more items than workgroups:
-    // every queue needs one)
-    a.grid = (int)std::max<long long>(kQueues, std::min<long long>(full, items));
-  }
   a.n_prim = c->n_prim;
   a.n_seg = c->n_seg;
   a.n_dof = c->n_dof;
@@ -1163,6 +1185,7 @@ ht_status ht_autotune(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n
   if (st != HT_OK) return st;
   if (n_frames <= 0 || n_particles <= 0 || !frame_slots || !poses || !cost || repeats < 1 || !out)
     return fail(HT_ERR_ARG, "bad autotune arguments");
+  if ((long long)n_frames * n_particles > INT32_MAX) return fail(HT_ERR_ARG, "too many particles");
   if ((st = check_slots_set(c)) != HT_OK) return st;
   DeviceGuard g(c->device);
   hipStream_t s = (hipStream_t)stream;
@@ -1174,15 +1197,22 @@ ht_status ht_autotune(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n
   float best = INFINITY;
   ht_launch_config best_cfg = saved;
   // a candidate replaces the best so far only if it is faster by more than 1 %, so that
-  // timing noise does not pick among near-equal shapes; culling is tried first (it is what the
+  // timing noise does not pick among near-equal shapes, and one whose launch is that of a candidate
+  // before it is not timed at all (four workgroups per CU and eight are one launch, and so are all
+  // of them where the kinematics and the cast go in one).  Culling is tried first (it is what the
   // gradient launches, which are not timed here, gain most from).  tiles_per_item stays at 64:
   // the forward launches that are timed do not depend on it any more, so a choice would be
   // noise, and the gradient launches are best with the largest (two-hand refined run of 20
   // generations: 5.51 ms with 64, 6.04 ms with 8, 6.54 ms with 4).  64 x 8 is timed twice, the
   // first time to leave the card's idle clocks.
-  const int gpcs[] = {8, 8, 4, 2, 1};
+  const int n_total = n_frames * n_particles;
   for (int cull = 1; cull >= 0 && st == HT_OK; --cull) {
-    for (int gpc : gpcs) {
+    ht::ForwardShape last{};
+    for (int gpc : {8, 8, 4, 2, 1}) {
+      const ht::ForwardShape f =
+          ht::forward_shape(c, n_total, ht::grid_limit(c, gpc, false, false, n_total), true);
+      if (gpc != 8 && f.parts == last.parts && f.grid == last.grid) continue;
+      last = f;
       c->lc = ht_launch_config{64, gpc, cull};
       st = ht::eval_impl(c, n_frames, frame_slots, n_particles, poses, cost, nullptr, nullptr,
                          nullptr, s);
