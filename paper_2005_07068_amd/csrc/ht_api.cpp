@@ -100,6 +100,13 @@ struct SlotHost {
   ht::FrameSlot entry{};
 };
 
+constexpr int kSmallGroupsPerCu = 3;   // workgroups per CU of a small launch, at most
+
+// Counters of a small launch's parts.  A launch finds its set at zero: the launch kDoneSets / 2
+// before it on the context cleared it, after the set's last use.  So a count left behind by launches
+// that overlapped against the rules is gone before the set is used again.
+constexpr int kDoneSets = 64;
+
 struct GraphKey {
   ht_swarm sw;
   ht_pso_params p;
@@ -144,8 +151,8 @@ struct ht_ctx {
   int cap_seg = 0;
   std::map<GraphKey, hipGraphExec_t> graphs;
   void* scratch = nullptr;    // this device's address of the no-allocation scratch array
-  unsigned long long* d_done = nullptr;   // [n_cu * kMaxGroupsPerCu] parts counted per particle
-  unsigned long long done_base = 0;       // what the last launch that counted them started at
+  int* d_done = nullptr;      // [kDoneSets][done_ints()] parts counted per particle
+  unsigned done_launches = 0; // small launches that counted their parts
   unsigned long long* d_eval_count = nullptr;   // [2][kCountSlots] forward / gradient sums
   unsigned int* d_errors = nullptr;              // HT_DEVERR_* flags
   // tracing of eager launches
@@ -157,6 +164,8 @@ struct ht_ctx {
   bool prof = false;
   std::vector<ProfRec> prof_recs;
 
+  int done_ints() const { return kSmallGroupsPerCu * n_cu; }   // more than the particles of a
+                                                              // launch that counts parts
   int max_tiles() const {
     int m = 0;
     for (const auto& s : slots)
@@ -216,10 +225,8 @@ constexpr int kListGroupsPerCu = 5;    // nominal workgroups per CU of a gradien
 constexpr int kTilesPerPart = 16;      // tiles of the observation per part, at least
 constexpr int kSmallParticles = 128;   // launches in one kernel (see eval_impl)
 constexpr int kSmallTiles = 32768;
-constexpr int kSmallGroupsPerCu = 3;
 constexpr int kFewParts = 8;           // two workgroups per CU give a particle as many, at least
 constexpr int kFewTiles = 128;         // and a part at most this many tiles of the observation
-constexpr unsigned long long kDoneStep = 1ull << 16;   // more than a launch's parts
 long long item_bound(const ht_ctx* c, long long n_total, int max_tiles, bool grad) {
   const long long fwd = std::max<long long>(n_total, (long long)kMaxGroupsPerCu * c->n_cu);
   return grad ? std::max(fwd, n_total * ((max_tiles + kMinTilesPerItem - 1) / kMinTilesPerItem)) : fwd;
@@ -451,10 +458,14 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
   }
   // A small launch also writes the costs.  Parts are counted for it only in the context's own
   // workspace and outside capture: a call recorded with the fixed one may run beside it, and the
-  // replays of a recorded launch would all count from one base.
+  // replays of a recorded launch would all count in one set.
   const bool counts = small && assemble && a.parts > 1 && !fixed && !capturing(s);
-  a.done = small && assemble && (a.parts == 1 || counts) ? c->d_done : nullptr;
-  if (counts) a.done_base = c->done_base += kDoneStep;
+  a.finish = small && assemble && (a.parts == 1 || counts) ? 1 : 0;
+  if (counts) {
+    a.done_ints = c->done_ints();
+    a.done = c->d_done + (size_t)(c->done_launches % kDoneSets) * a.done_ints;
+    a.done_next = c->d_done + (size_t)((c->done_launches + kDoneSets / 2) % kDoneSets) * a.done_ints;
+  }
   a.direct = !small && assemble && !grad && a.parts == 1 ? 1 : 0;
   a.n_prim = c->n_prim;
   a.n_seg = c->n_seg;
@@ -463,13 +474,16 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
   const int kinds[kNumStages] = {HT_K_FK, HT_K_SCHED, grad ? HT_K_RAYCAST_GRAD : HT_K_RAYCAST,
                                  HT_K_FINALIZE};
   if (small) {
-    HT_HIP(traced(c, HT_K_RAYCAST, n_total, s,
-                  [&] { return launch_eval_stage(kStageSmall, a, ws, s); }));
+    HT_HIP(traced(c, HT_K_RAYCAST, n_total, s, [&] {
+      const hipError_t e = launch_eval_stage(kStageSmall, a, ws, s);
+      if (counts && e == hipSuccess) ++c->done_launches;
+      return e;
+    }));
   }
   for (int stage = small ? kStageFinalize : 0; stage < kNumStages; ++stage) {
     if (stage == kStageFk && src) continue;   // reused from the previous evaluation
     if (stage == kStageFinalize && !assemble) continue;   // assembled by the next kernel
-    if (stage == kStageFinalize && (a.direct || a.done)) continue;   // costs from the ray cast
+    if (stage == kStageFinalize && (a.direct || a.finish)) continue;   // costs from the ray cast
     if (stage == kStageSched && (!grad || n_total <= kSelfSchedMax)) continue;   // no work list
     if (fixed)
       HT_HIP(launch_eval_stage(stage, a, ws, s));
@@ -507,8 +521,8 @@ ht_status ht_create(ht_ctx** out, int hip_device) {
   if (e == hipSuccess) e = hipMalloc(&c->d_model, sizeof(ht::DevModel));
   if (e == hipSuccess) e = hipMalloc(&c->d_eval_count, 2 * ht::kCountSlots * sizeof(unsigned long long));
   if (e == hipSuccess) e = hipMemset(c->d_eval_count, 0, 2 * ht::kCountSlots * sizeof(unsigned long long));
-  if (e == hipSuccess) e = hipMalloc(&c->d_done, (size_t)c->n_cu * kMaxGroupsPerCu * sizeof(*c->d_done));
-  if (e == hipSuccess) e = hipMemset(c->d_done, 0, (size_t)c->n_cu * kMaxGroupsPerCu * sizeof(*c->d_done));
+  if (e == hipSuccess) e = hipMalloc(&c->d_done, (size_t)kDoneSets * c->done_ints() * sizeof(int));
+  if (e == hipSuccess) e = hipMemset(c->d_done, 0, (size_t)kDoneSets * c->done_ints() * sizeof(int));
   if (e == hipSuccess) e = hipMalloc(&c->d_errors, sizeof(unsigned int));
   if (e == hipSuccess) e = hipMemset(c->d_errors, 0, sizeof(unsigned int));
   if (e != hipSuccess) {

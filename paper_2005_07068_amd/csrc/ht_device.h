@@ -172,10 +172,10 @@ struct EvalArgs {
   int tiles_per_item;          // gradient work list: most tiles per item, and the nominal grid
   int list_grid;               // that its items are sized for
   int direct;                  // 1 (forward, whole particles): the ray cast writes the costs
-  // small launches: [n_total] parts counted per particle from done_base on (the last one writes
-  // the cost); NULL: partials only
-  unsigned long long* done;
-  unsigned long long done_base;
+  int finish;                  // 1: a small launch writes the costs, the last part of a particle
+  int* done;                   // to finish, counted in done [n_total] where there are several;
+  int* done_next;              // the launch clears a later one's counters, done_ints of them
+  int done_ints;
   int n_prim, n_seg, n_dof;
 };
 

@@ -36,6 +36,14 @@ def test_calls_after_overlapping_ones_are_right():
     ctx.close()
 
 
+def test_many_calls_in_a_row():
+    torch, ctx, slots, xs, refs = _setup()
+    got = [(k % 4, ctx.eval(xs[k % 4], slots)) for k in range(203)]
+    for k, (i, c) in enumerate(got):
+        assert np.array_equal(c.cpu().numpy(), refs[i]), k
+    ctx.close()
+
+
 def test_recorded_and_eager_calls_take_turns():
     torch, ctx, slots, xs, refs = _setup()
     outs = [torch.empty((1, len(x)), device="cuda:0") for x in xs]
