@@ -365,16 +365,20 @@ static ForwardShape forward_shape(const ht_ctx* c, int n_total, int full, bool o
   // parts 30.9 us: their workgroups' start costs more than the few tiles they take over).
   const int most = (c->max_tiles() + kTilesPerPart - 1) / kTilesPerPart;
   ForwardShape f{};
-  // Small forward launches take the kinematics and the cast in one: up to 128 particles of any
-  // size (64 poses: 320x240 21.1 to 18.8 us, two hands at 640x480 26.5 to 25.4 us; 128 poses 23.0
-  // to 19.6 us and 31.3 to 30.3 us; 192 poses 26.1 to 33 us), more of small observations (128 of
-  // 128x128 21.5 to 18.4 us, 200 of them 22.1 to 24.7 us: few parts repeat the kinematics on busy
+  // Small forward launches take the kinematics and the cast in one: up to 128 particles (64 poses:
+  // 320x240 21.1 to 18.8 us, two hands at 640x480 26.5 to 25.4 us; 128 poses 23.0 to 19.6 us and
+  // 31.3 to 30.3 us; 192 poses 26.1 to 33 us; it loses where a hand fills a large image: 128 poses
+  // of 640x480 35.8 to 37.9 us, of 1280x960 75 to 102 us), and more of small observations while
+  // every workgroup has its place at once (64x64 frames: 256 poses 19.4 to 15.3 us, 512 poses 24.0
+  // to 17.5 us; 48x48: 700 poses 24.5 to 18.8 us, 900 poses 26.2 to 28.6 us; 16x16: 8192 poses 72
+  // to 121 us; 200 poses of 128x128 22.1 to 24.7 us: few parts repeat the kinematics on busy
   // CUs).  Three workgroups fit a CU; two are better while a particle keeps eight parts and these
   // stay short (32 poses of 320x240 15.7 to 13.9 us, 64 of 128x128 14.0 to 13.1 us, four two-hand
   // poses 14.7 to 14.0 us), not where the parts grow long or few (64 poses of 320x240 15.9 to
   // 16.6 us, 64 two-hand ones 21.7 to 23.5 us, 128 of 128x128 15.0 to 15.4 us).
   f.small = one && (n_total <= kSmallParticles ||
-                    (long long)n_total * c->max_tiles() <= kSmallTiles);
+                    (n_total <= kSmallGroupsPerCu * c->n_cu &&
+                     (long long)n_total * c->max_tiles() <= kSmallTiles));
   if (f.small) {
     const int two = 2 * c->n_cu / n_total;
     const bool few = two >= kFewParts && c->max_tiles() <= kFewTiles * two;
