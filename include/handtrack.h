@@ -334,16 +334,17 @@ ht_status ht_autotune(ht_ctx* ctx, int n_frames, const int32_t* frame_slots, int
                       void* hip_stream);
 
 /* Per-kernel tracing of eager calls: between ht_profile_begin and ht_profile_end every kernel
- * the library enqueues outside graph capture is bracketed by HIP events on its own stream.
+ * the library enqueues outside graph capture is bracketed by HIP events on its own stream
+ * (ht_eval_particles_noalloc's are not: events are allocated).
  * ht_profile_end synchronises those events, fills stats[HT_K_COUNT] (launch count, particles
  * processed, summed device milliseconds per kernel kind) and stops tracing. */
 enum {
   HT_K_FK = 0,            /* kinematics prologue             */
   HT_K_SCHED = 1,         /* work-list scan                  */
-  HT_K_RAYCAST = 2,       /* ray cast + cost terms (forward) */
+  HT_K_RAYCAST = 2,       /* ray cast + cost terms (forward); of few particles, whole evaluations */
   HT_K_RAYCAST_GRAD = 3,  /* ray cast + cost + adjoint       */
   HT_K_FINALIZE = 4,      /* cost assembly (+ kinematic adjoint) */
-  HT_K_PSO = 5,           /* swarm init / update             */
+  HT_K_PSO = 5,           /* swarm init / update; of small plain swarms, with the cost assembly */
   HT_K_REFINE = 6,        /* refinement select/propose/accept/gather */
   HT_K_COUNT = 7
 };

@@ -477,23 +477,21 @@ ht_status eval_impl(ht_ctx* c, int n_frames, const int32_t* frame_slots, int n_p
   if (args_out) *args_out = a;
   const int kinds[kNumStages] = {HT_K_FK, HT_K_SCHED, grad ? HT_K_RAYCAST_GRAD : HT_K_RAYCAST,
                                  HT_K_FINALIZE};
-  if (small) {
-    HT_HIP(traced(c, HT_K_RAYCAST, n_total, s, [&] {
-      const hipError_t e = launch_eval_stage(kStageSmall, a, ws, s);
-      if (counts && e == hipSuccess) ++c->done_launches;
-      return e;
-    }));
-  }
+  const auto launch = [&](int stage) {
+    const hipError_t e = launch_eval_stage(stage, a, ws, s);
+    if (stage == kStageSmall && counts && e == hipSuccess) ++c->done_launches;
+    return e;
+  };
+  const auto run = [&](int kind, int stage) {
+    return fixed ? launch(stage) : traced(c, kind, n_total, s, [&] { return launch(stage); });
+  };
+  if (small) HT_HIP(run(HT_K_RAYCAST, kStageSmall));
   for (int stage = small ? kStageFinalize : 0; stage < kNumStages; ++stage) {
     if (stage == kStageFk && src) continue;   // reused from the previous evaluation
     if (stage == kStageFinalize && !assemble) continue;   // assembled by the next kernel
     if (stage == kStageFinalize && (a.direct || a.finish)) continue;   // costs from the ray cast
     if (stage == kStageSched && (!grad || n_total <= kSelfSchedMax)) continue;   // no work list
-    if (fixed)
-      HT_HIP(launch_eval_stage(stage, a, ws, s));
-    else
-      HT_HIP(traced(c, kinds[stage], n_total, s,
-                    [&] { return launch_eval_stage(stage, a, ws, s); }));
+    HT_HIP(run(kinds[stage], stage));
   }
   return HT_OK;
 }
