@@ -462,9 +462,11 @@ __device__ __forceinline__ void sphere_image_disc(const float* q, float R, Frame
 
 // Farthest pixel centre of an 8x8 tile from the tile's centre: 3.5 sqrt(2) pixels.
 constexpr float kTileHalfDiag = 4.9498f;
-// The pad of a primitive's reach in pixels: FP32 and the hardware's reciprocals place a disc to
-// 1e-6 of its distance from the principal point, 0.01 px at 10 000 px.  (With 0.5 px 1024 two-hand
-// poses took 116.8 us, 115.5 with 0.125.)
+// The pad of a primitive's reach in pixels.  What FP32 and the hardware's reciprocals (1 ulp) take
+// away is covered by the factor 1.0001 and the capsule's own margin: over images of 4096 pixels,
+// principal points up to 100 000 px outside them, focal lengths of 5 to 20 000 px and hands at 30
+// mm to 20 m, the silhouettes stayed 0.126 px inside the reach, and 0.24 px inside the boxes (pad
+// 0.25).  (1024 two-hand poses 116.8 us with 0.5 px, 115.5 with 0.125.)
 constexpr float kReachPad = 0.125f;
 
 // ------------------------------------------------------------------------------------
