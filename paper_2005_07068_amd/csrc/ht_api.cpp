@@ -143,7 +143,6 @@ struct ht_ctx {
   float* r_cgrad = nullptr;   // [4 * cap_ref][n_dof] gradients of the candidates
   int* r_sel = nullptr;       // [cap_ref]
   int* r_active = nullptr;    // [cap_ref]
-  int* r_slots = nullptr;     // [4 * cap_ref] frame slot of each refined particle
   int cap_ref = 0;
   int* pso_flags = nullptr;   // [cap_flags] per-particle improved / mutated flags
   int cap_flags = 0;
@@ -564,7 +563,6 @@ void ht_destroy(ht_ctx* c) {
   dfree(c->r_cgrad);
   dfree(c->r_sel);
   dfree(c->r_active);
-  dfree(c->r_slots);
   dfree(c->pso_flags);
   dfree(c->seg_partial);
   dfree(c->d_slots);
@@ -599,21 +597,16 @@ ht_status build_model(const ht_model* m, ht::DevModel& d, ht::TypeMasks& tm) {
   for (int s = 0; s < m->n_seg; ++s) {
     const int par = m->seg_parent[s];
     if (par >= s || par < -1) return fail(HT_ERR_ARG, "segment %d: parent %d must precede it", s, par);
-    d.seg_parent[s] = par;
     d.seg_depth[s] = par < 0 ? 0 : d.seg_depth[par] + 1;
-    d.max_depth = std::max(d.max_depth, d.seg_depth[s]);
     if (par < 0) {
       const int b = m->seg_root_dof[s];
       if (b < 0 || b + 6 > m->n_dof) return fail(HT_ERR_ARG, "segment %d: root dof %d out of range", s, b);
-      d.seg_root_dof[s] = b;
       for (int i = 0; i < 6; ++i) used[b + i]++;
       for (int i = 0; i < 3; ++i) d.dof_trans[b + i] = 1;
-    } else {
-      d.seg_root_dof[s] = -1;
     }
     if (par >= 0) std::memcpy(d.seg_path[s], d.seg_path[par], sizeof d.seg_path[s]);
     d.seg_path[s][d.seg_depth[s]] = (uint8_t)s;
-    d.seg_wrist[s] = par < 0 ? d.seg_root_dof[s] : d.seg_wrist[par];
+    d.seg_wrist[s] = par < 0 ? m->seg_root_dof[s] : d.seg_wrist[par];
     for (int i = 0; i < 12; ++i) d.seg_off[s][i] = m->seg_offset[s * 12 + i];
     for (int j = 0; j < 2; ++j) {
       const int dof = m->seg_joint_dof[s * 2 + j];
@@ -636,15 +629,15 @@ ht_status build_model(const ht_model* m, ht::DevModel& d, ht::TypeMasks& tm) {
   std::vector<int> tree(m->n_seg, 0);
   d.n_roots = 0;
   for (int s = 0; s < m->n_seg; ++s)
-    tree[s] = d.seg_parent[s] < 0 ? std::min(d.n_roots++, ht::kMaxRects - 1) : tree[d.seg_parent[s]];
+    tree[s] = m->seg_parent[s] < 0 ? std::min(d.n_roots++, ht::kMaxRects - 1) : tree[m->seg_parent[s]];
   d.n_roots = std::min(d.n_roots, ht::kMaxRects);
   // segments moved by each pose parameter: the driven segment and its descendants
   for (int s = 0; s < m->n_seg; ++s) {
-    for (int q = s; q >= 0; q = d.seg_parent[q]) {
+    for (int q = s; q >= 0; q = m->seg_parent[q]) {
       for (int j = 0; j < 2; ++j)
         if (d.seg_dof[q][j] >= 0) d.dof_desc[d.seg_dof[q][j]] |= 1u << s;
-      if (d.seg_parent[q] < 0)
-        for (int i = 0; i < 6; ++i) d.dof_desc[d.seg_root_dof[q] + i] |= 1u << s;
+      if (m->seg_parent[q] < 0)
+        for (int i = 0; i < 6; ++i) d.dof_desc[d.seg_wrist[q] + i] |= 1u << s;
     }
   }
   tm = ht::TypeMasks{};

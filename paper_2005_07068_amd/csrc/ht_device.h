@@ -31,10 +31,7 @@ constexpr uint32_t kValidBit = 1u << 17;
 // Hand model as laid out in device memory.
 struct DevModel {
   int n_dof, n_seg, n_prim, n_kc;
-  int max_depth;
   int n_roots;                           // independent kinematic trees (hands), <= kMaxRects
-  int seg_parent[HT_MAX_SEG];
-  int seg_root_dof[HT_MAX_SEG];
   int seg_depth[HT_MAX_SEG];             // segments above it (root: 0)
   int seg_wrist[HT_MAX_SEG];             // first wrist dof of its tree
   uint8_t seg_path[HT_MAX_SEG][HT_MAX_SEG];   // root .. the segment itself (seg_depth + 1)
