@@ -222,7 +222,7 @@ bool workspace_fits(const ht_ctx* c, int n_total, int max_tiles, bool grad) {
 constexpr int kMaxGroupsPerCu = 8;     // 2048 threads
 constexpr int kListGroupsPerCu = 5;    // nominal workgroups per CU of a gradient work list
 constexpr int kTilesPerPart = 16;      // tiles of the observation per part, at least
-constexpr int kSmallParticles = 128;   // launches in one kernel (see eval_impl)
+constexpr int kSmallParticles = 128;   // launches in one kernel (see forward_shape)
 constexpr int kSmallTiles = 32768;
 constexpr int kFewParts = 8;           // two workgroups per CU give a particle as many, at least
 constexpr int kFewTiles = 128;         // and a part at most this many tiles of the observation
@@ -266,8 +266,10 @@ ht_status ensure_workspace(ht_ctx* c, int n_total, int max_tiles, bool grad, hip
 }
 
 // What ht_eval_particles_noalloc accepts (its documented size limit): the bytes of a workspace
-// that holds, per particle, its tables, header, joint frames and segment origins, and per work item of
-// kMinTilesPerItem tiles a partial and its bookkeeping.  The workspace it lays out (below) is smaller.
+// that holds, per particle, 120 bytes a primitive, a header, joint frames and segment origins, and
+// per work item of kMinTilesPerItem tiles a partial and its bookkeeping.  It is a limit on sizes, not
+// a layout: near the 64 MiB the workspace laid out below takes less, for few particles more (it
+// always holds partials for every resident workgroup), so the caller checks that one too.
 size_t noalloc_need(const ht_ctx* c, long long np, int max_tiles) {
   const long long runs = std::max<long long>(np * ((max_tiles + kMinTilesPerItem - 1) / kMinTilesPerItem), 1);
   size_t off = 0;
