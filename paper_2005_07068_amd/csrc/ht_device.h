@@ -2,6 +2,7 @@
 #pragma once
 
 #include <hip/hip_runtime.h>
+#include <math.h>
 #include <stdint.h>
 
 #include "handtrack.h"
@@ -194,6 +195,60 @@ __device__ inline float cost_from_sums(double S_d, long long S_and, long long S_
     D = S_d / (double)S_or + kLambda * (1.0 - 2.0 * (double)S_and / (double)(S_and + S_or));
   }
   return (float)(D + kLambdaK * (double)kc);
+}
+
+// The cost of a particle that has none: of an unset slot, or of a pose that is not finite.
+__device__ __forceinline__ float no_cost(int slot) { return slot < 0 ? NAN : INFINITY; }
+
+// A particle's cost from its parts' sums (pi: its header).
+template <class Ptr>
+__device__ __forceinline__ float particle_cost(Ptr pi, double td, int sa, int so) {
+  return pi->valid ? cost_from_sums(pi->bg_td + td, sa, (long long)pi->bg_or + so, pi->kc)
+                   : no_cost(pi->slot);
+}
+
+// Sums over lanes on the vector unit: DPP moves within each 16-lane row (quad permutations, then
+// row rotations by 4 and 8), on every lane of the row; for a wavefront the four row sums read from
+// lanes 0, 16, 32, 48 and added in a fixed order.  Deterministic; a wavefront's total is
+// wave-uniform.  (__shfl_xor lowers to ds_bpermute, an LDS round trip per step: with it the wavefront
+// totals at the end of every item, of finalize and of the gradient's list cost 1 to 2 us a launch;
+// gradients of 256 poses of a 64x64 hand 54.4 us, 52.5 with DPP.)  Every lane must be active, of a
+// row or of the wavefront.
+template <int CTRL>
+__device__ __forceinline__ int dpp(int v) {
+  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
+}
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) {
+  return __int_as_float(dpp<CTRL>(__float_as_int(v)));
+}
+template <int CTRL>
+__device__ __forceinline__ double dpp(double v) {
+  const uint64_t b = __double_as_longlong(v);
+  const uint32_t lo = dpp<CTRL>((int)b), hi = dpp<CTRL>((int)(b >> 32));
+  return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+template <class T>
+__device__ __forceinline__ T row_sum(T v) {
+  v += dpp<0xB1>(v);    // quad_perm [1, 0, 3, 2]
+  v += dpp<0x4E>(v);    // quad_perm [2, 3, 0, 1]
+  v += dpp<0x124>(v);   // row_ror:4
+  v += dpp<0x128>(v);   // row_ror:8
+  return v;
+}
+__device__ __forceinline__ int read_lane(int v, int lane) {
+  return __builtin_amdgcn_readlane(v, lane);
+}
+__device__ __forceinline__ double read_lane(double v, int lane) {
+  const uint64_t b = __double_as_longlong(v);
+  const uint32_t lo = __builtin_amdgcn_readlane((int)b, lane);
+  const uint32_t hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
+  return __longlong_as_double(((uint64_t)hi << 32) | lo);
+}
+template <class T>
+__device__ __forceinline__ T wave_sum(T v) {
+  v = row_sum(v);
+  return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
 }
 
 // Launch helpers implemented in ht_kernels.hip.

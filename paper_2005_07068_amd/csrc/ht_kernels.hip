@@ -38,45 +38,6 @@ __device__ __forceinline__ const __attribute__((address_space(4))) T* scalar_ptr
   return (const __attribute__((address_space(4))) T*)p;
 }
 
-// Wavefront total on the vector unit: DPP moves within each 16-lane row (quad permutations,
-// then row rotations by 4 and 8), then the four row sums read from lanes 0, 16, 32, 48 and
-// added in a fixed order.  Deterministic; the result is wave-uniform.  (__shfl_xor lowers to
-// ds_bpermute, an LDS round trip per step: with it the wavefront totals at the end of every
-// item, of finalize and of the gradient's list cost 1 to 2 us a launch; gradients of 256 poses
-// of a 64x64 hand 54.4 us, 52.5 with DPP.)  Every lane must be active.
-template <int CTRL>
-__device__ __forceinline__ int dpp(int v) {
-  return __builtin_amdgcn_mov_dpp(v, CTRL, 0xF, 0xF, true);
-}
-template <int CTRL>
-__device__ __forceinline__ float dpp(float v) {
-  return __int_as_float(dpp<CTRL>(__float_as_int(v)));
-}
-__device__ __forceinline__ int wave_sum(int v) {
-  v += dpp<0xB1>(v);    // quad_perm [1, 0, 3, 2]
-  v += dpp<0x4E>(v);    // quad_perm [2, 3, 0, 1]
-  v += dpp<0x124>(v);   // row_ror:4
-  v += dpp<0x128>(v);   // row_ror:8
-  return (__builtin_amdgcn_readlane(v, 0) + __builtin_amdgcn_readlane(v, 16)) +
-         (__builtin_amdgcn_readlane(v, 32) + __builtin_amdgcn_readlane(v, 48));
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_add(double v) {
-  const uint64_t b = __double_as_longlong(v);
-  const uint32_t lo = dpp<CTRL>((int)b), hi = dpp<CTRL>((int)(b >> 32));
-  return v + __longlong_as_double(((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ double read_lane(double v, int lane) {
-  const uint64_t b = __double_as_longlong(v);
-  const uint32_t lo = __builtin_amdgcn_readlane((int)b, lane);
-  const uint32_t hi = __builtin_amdgcn_readlane((int)(b >> 32), lane);
-  return __longlong_as_double(((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ double wave_sum(double v) {
-  v = dpp_add<0x128>(dpp_add<0x124>(dpp_add<0x4E>(dpp_add<0xB1>(v))));
-  return (read_lane(v, 0) + read_lane(v, 16)) + (read_lane(v, 32) + read_lane(v, 48));
-}
-
 // C = A * B for 3x4 affine transforms (row-major, implicit last row 0 0 0 1).
 __device__ inline void mul34(const double* A, const double* B, double* C) {
 #pragma unroll
@@ -2035,8 +1996,7 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
         const int so = s_o[buf][0] + s_o[buf][1] + s_o[buf][2] + s_o[buf][3];
         if (!GRAD && a.direct) {
           // the whole particle: its cost follows here (no finalize launch)
-          a.cost[r] = pi->valid ? cost_from_sums(pi->bg_td + td, sa, (long long)pi->bg_or + so, pi->kc)
-                                : (pi->slot < 0 ? NAN : INFINITY);
+          a.cost[r] = particle_cost(pi, td, sa, so);
         } else {
           ws.partial[item] = Partial{td, sa, so};
         }
@@ -2064,12 +2024,6 @@ void raycast_kernel(EvalArgs a, Workspace ws, TypeMasks tm) {
 // ------------------------------------------------------------------------------------
 // small forward launches: the whole evaluation in one launch
 
-// A particle's cost from its parts' sums.
-__device__ __forceinline__ float particle_cost(const PInfo& pi, double td, int sa, int so) {
-  return pi.valid ? cost_from_sums(pi.bg_td + td, sa, (long long)pi.bg_or + so, pi.kc)
-                  : (pi.slot < 0 ? NAN : INFINITY);
-}
-
 // The last part of a particle to finish writes its cost (small launches: 16 poses of a 64x64
 // frame 13.0 to 12.0 us, a frame's ingest with one pose 57 to 54.5 us without a finalize launch;
 // of the larger ones 256 poses of a 320x240 frame took 29.3 instead of 30.0 us, 200 of the
@@ -2084,7 +2038,7 @@ __device__ __forceinline__ void finish_part(const EvalArgs& a, const Workspace& 
                                             int item, int n_parts, double td, int sa, int so,
                                             const PInfo& pi, int lane) {
   if (n_parts == 1) {
-    if (lane == 0) a.cost[r] = particle_cost(pi, td, sa, so);
+    if (lane == 0) a.cost[r] = particle_cost(&pi, td, sa, so);
     return;
   }
   int before = 0;
@@ -2112,7 +2066,7 @@ __device__ __forceinline__ void finish_part(const EvalArgs& a, const Workspace& 
   d = wave_sum(d);
   ia = wave_sum(ia);
   io = wave_sum(io);
-  if (lane == 0) a.cost[r] = particle_cost(pi, d, ia, io);
+  if (lane == 0) a.cost[r] = particle_cost(&pi, d, ia, io);
 }
 
 // One workgroup per part of a particle: the kinematics (repeated in every part, on CUs that would
@@ -2221,7 +2175,7 @@ __global__ __launch_bounds__(kBlock) void finalize_kernel(EvalArgs a, Workspace 
   wave_partial_sums(pi.bg_td, pi.bg_or, ws, b, e, lane, pr0, S_d, S_and, S_or);
   if (pi.skip) return;
   if (!pi.valid) {
-    if (lane == 0) a.cost[p] = pi.slot < 0 ? NAN : INFINITY;
+    if (lane == 0) a.cost[p] = no_cost(pi.slot);
     return;
   }
   if (lane == 0) a.cost[p] = cost_from_sums(S_d, S_and, S_or, pi.kc);
@@ -2301,7 +2255,7 @@ __global__ __launch_bounds__(kBlock) void finalize_grad_kernel(EvalArgs a, Works
   if (q == 1) wave_partial_sums(pi.bg_td, pi.bg_or, ws, b, e, lane, pr0, S_d, S_and, S_or);
   if (pi.skip) return;
   if (!pi.valid) {
-    if (t == 0) a.cost[p] = pi.slot < 0 ? NAN : INFINITY;
+    if (t == 0) a.cost[p] = no_cost(pi.slot);
     for (int i = t; i < n_dof; i += kBlock) a.grad[(size_t)p * n_dof + i] = 0.0f;
     return;
   }
@@ -2404,7 +2358,7 @@ __device__ bool assemble_wave(const EvalArgs& a, const Workspace& ws, int p, boo
   long long S_and, S_or;
   wave_partial_sums(ph->bg_td, ph->bg_or, ws, b, e, lane, pr0, S_d, S_and, S_or);
   if (!ph->valid) {
-    cost = ph->slot < 0 ? NAN : INFINITY;
+    cost = no_cost(ph->slot);
     return true;
   }
   cost = cost_from_sums(S_d, S_and, S_or, ph->kc);

@@ -380,25 +380,6 @@ constexpr int kSmallSwarm = 256;         // particles per frame, at most
 constexpr int kGroup = 16;               // lanes per particle: one DPP row
 constexpr int kSmallIter = 8;            // elements per thread, at most
 
-// Sum over the 16 lanes of a row, on every lane (DPP quad permutations and row rotations).
-__device__ __forceinline__ int row_sum(int v) {
-  v += __builtin_amdgcn_mov_dpp(v, 0xB1, 0xF, 0xF, true);
-  v += __builtin_amdgcn_mov_dpp(v, 0x4E, 0xF, 0xF, true);
-  v += __builtin_amdgcn_mov_dpp(v, 0x124, 0xF, 0xF, true);
-  v += __builtin_amdgcn_mov_dpp(v, 0x128, 0xF, 0xF, true);
-  return v;
-}
-template <int CTRL>
-__device__ __forceinline__ double dpp_add(double v) {
-  const uint64_t b = __double_as_longlong(v);
-  const uint32_t lo = __builtin_amdgcn_mov_dpp((int)b, CTRL, 0xF, 0xF, true);
-  const uint32_t hi = __builtin_amdgcn_mov_dpp((int)(b >> 32), CTRL, 0xF, 0xF, true);
-  return v + __longlong_as_double(((uint64_t)hi << 32) | lo);
-}
-__device__ __forceinline__ double row_sum(double v) {
-  return dpp_add<0x128>(dpp_add<0x124>(dpp_add<0x4E>(dpp_add<0xB1>(v))));
-}
-
 template <int ITER>
 __global__ __launch_bounds__(kPsoBlock) void pso_update_small_kernel(
     const DevModel* __restrict__ M, ht_swarm sw, ht_pso_params prm, int n_dof, EvalArgs a,
@@ -443,8 +424,7 @@ __global__ __launch_bounds__(kPsoBlock) void pso_update_small_kernel(
     sa = row_sum(sa);
     so = row_sum(so);
     if (l == 0) {
-      const float cost = pi.valid ? cost_from_sums(pi.bg_td + td, sa, (long long)pi.bg_or + so, pi.kc)
-                                  : (pi.slot < 0 ? NAN : INFINITY);
+      const float cost = particle_cost(&pi, td, sa, so);
       sw.cost[gp] = cost;
       const float c = cost_key(cost);
       const bool better = c < old;
