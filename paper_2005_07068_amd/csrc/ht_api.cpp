@@ -1152,7 +1152,8 @@ ht_status ht_pso_run_graph(ht_ctx* c, const ht_swarm* sw, const ht_pso_params* p
     const int most = std::max(F * P, refine ? F * 4 * K : 0);
     if ((st = ensure_workspace(c, most, c->max_tiles(), refine, s)) != HT_OK) return st;
     if (refine && (st = ensure_refine(c, F * K, s)) != HT_OK) return st;
-    if (F * P > c->cap_flags) {
+    // (the one-launch update of a small plain swarm needs no flags)
+    if ((refine || !ht::pso_update_is_small(*sw, c->n_dof)) && F * P > c->cap_flags) {
       HT_HIP(hipDeviceSynchronize());
       invalidate_graphs(c);   // captured graphs hold the old buffers
       dfree(c->pso_flags);
