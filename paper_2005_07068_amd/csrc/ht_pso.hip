@@ -9,7 +9,8 @@
 //
 // A generation's update is two launches: `pso_best_kernel` (one workgroup per frame: personal
 // and global bests, the mutation ranking, the generation counter) and `pso_move_kernel` (one
-// thread per particle dimension: personal-best copy, then mutation or Eq. 6-7 with clamping).
+// thread per particle dimension: personal-best copy, then mutation or Eq. 6-7 with clamping);
+// of a small plain swarm one, `pso_update_small_kernel`, which also assembles the costs.
 #include <math.h>
 
 #include "ht_device.h"
@@ -374,11 +375,15 @@ __global__ __launch_bounds__(kBlock) void pso_move_kernel(const DevModel* __rest
 // of a plain small swarm is two launches.  Sixteen lanes work on a particle: they add its parts'
 // partials, and then count how many costs and how many personal bests lie below its own (which
 // ranks the mutation and finds the global best without a sort; keys are unique).  The positions
-// and velocities are loaded before all that, kIter elements per thread, so that their latency
-// passes under it.  A chain of latencies, like the kernels it replaces.
-constexpr int kSmallSwarm = 256;         // particles per frame, at most
+// and velocities are loaded before all that, ITER elements per thread, so that their latency
+// passes under it.  A chain of latencies, like the kernels it replaces: every 64 particles add one of
+// partials and headers, so past 96 particles, or 64 two-hand ones, the separate kernels are faster
+// (ten generations: one hand at 128x128, 64 particles 182 us against 210, 96: 219 and 229, 104: 242
+// and 236, 256: 413 and 295; two hands, 64 particles 302 and 306, 72: 332 and 328).
+constexpr int kSmallSwarm = 96;          // particles per frame, at most
+constexpr int kSmallElems = 3328;        // and pose parameters
 constexpr int kGroup = 16;               // lanes per particle: one DPP row
-constexpr int kSmallIter = 8;            // elements per thread, at most
+constexpr int kSmallIter = (kSmallElems + kPsoBlock - 1) / kPsoBlock;   // elements per thread
 
 template <int ITER>
 __global__ __launch_bounds__(kPsoBlock) void pso_update_small_kernel(
@@ -500,7 +505,7 @@ __global__ __launch_bounds__(kPsoBlock) void pso_update_small_kernel(
 }
 
 bool pso_update_is_small(const ht_swarm& sw, int n_dof) {
-  return sw.n_particles <= kSmallSwarm && sw.n_particles * n_dof <= kSmallIter * kPsoBlock;
+  return sw.n_particles <= kSmallSwarm && sw.n_particles * n_dof <= kSmallElems;
 }
 
 hipError_t launch_pso_update_small(const DevModel* model, const ht_swarm& sw,
