@@ -342,8 +342,8 @@ static int resident_groups(ht_ctx* c, bool grad, bool dbg, bool all_types, bool 
 }
 
 // Workgroups of a ray cast at most: groups_per_cu per CU, four and more standing for every workgroup
-// that fits (five to eight of them); a cap at four left 65536 poses of a 320x240 frame at 3.53 ms
-// against 2.71 ms with eight.
+// that fits (five to eight of them); a cap at four leaves 65536 poses of a 320x240 frame at 3.02 ms
+// against 2.37 ms with eight, 1024 two-hand poses at 134 us against 115 us.
 static int grid_limit(ht_ctx* c, int groups_per_cu, bool grad, bool dbg, int n_total) {
   const bool all_types = (c->tmask.m[HT_CONE][0] | c->tmask.m[HT_CONE][1] |
                           c->tmask.m[HT_ECYLINDER][0] | c->tmask.m[HT_ECYLINDER][1]) != 0ull;
@@ -362,21 +362,23 @@ static ForwardShape forward_shape(const ht_ctx* c, int n_total, int full, bool o
   // Parts per particle: as many as give every resident workgroup one item, rounded down (a
   // launch with more items than workgroups waits for the few that take two: 256 poses of a
   // 320x240 frame 34 us with one item per workgroup, 39 us with two), but parts of 16 tiles of
-  // the observation at least (64 poses of a 128x128 frame: 16 parts 27.2 us per generation, 32
-  // parts 30.9 us: their workgroups' start costs more than the few tiles they take over).
+  // the observation at least (a refined generation of 64 poses of a 128x128 frame 120.5 us, 124.3 us
+  // with 8 tiles: more workgroups' start costs more than the few tiles they take over; 16 poses of a
+  // 64x64 frame 12.1 us, 13.4 us with 32).
   const int most = (c->max_tiles() + kTilesPerPart - 1) / kTilesPerPart;
   ForwardShape f{};
-  // Small forward launches take the kinematics and the cast in one: up to 128 particles (64 poses:
-  // 320x240 21.1 to 18.8 us, two hands at 640x480 26.5 to 25.4 us; 128 poses 23.0 to 19.6 us and
-  // 31.3 to 30.3 us; 192 poses 26.1 to 33 us; it loses where a hand fills a large image: 128 poses
-  // of 640x480 35.8 to 37.9 us, of 1280x960 75 to 102 us), and more of small observations while
-  // every workgroup has its place at once (64x64 frames: 256 poses 19.4 to 15.3 us, 512 poses 24.0
-  // to 17.5 us; 48x48: 700 poses 24.5 to 18.8 us, 900 poses 26.2 to 28.6 us; 16x16: 8192 poses 72
-  // to 121 us; 200 poses of 128x128 22.1 to 24.7 us: few parts repeat the kinematics on busy
-  // CUs).  Three workgroups fit a CU; two are better while a particle keeps eight parts and these
-  // stay short (32 poses of 320x240 15.7 to 13.9 us, 64 of 128x128 14.0 to 13.1 us, four two-hand
-  // poses 14.7 to 14.0 us), not where the parts grow long or few (64 poses of 320x240 15.9 to
-  // 16.6 us, 64 two-hand ones 21.7 to 23.5 us, 128 of 128x128 15.0 to 15.4 us).
+  // Small forward launches take the kinematics and the cast in one: up to 128 particles (us, separate
+  // launches and one: 16 poses of 64x64 18.1 and 12.1, 64 of 320x240 20.5 and 15.9, 128 of them 23.5
+  // and 19.7, 64 two-hand poses at 640x480 25.4 and 22.0, 128 of them 31.5 and 30.7; 192 of 320x240
+  // 26.5 and 27.1, 192 two-hand ones 38.9 and 40.7; it loses earlier where a hand fills a large image:
+  // 96 poses of 640x480 32.5 and 37.7, 128 of 1280x960 75 and 104), and more of small observations
+  // while every workgroup has its place at once (64x64: 256 poses 19.4 and 15.3, 512 poses 24.1 and
+  // 17.7; 48x48: 700 poses 24.8 and 19.0, 900 poses 26.3 and 28.6; 16x16: 8192 poses 72 and 121; 200
+  // poses of 128x128, past the bound on tiles, would gain: 21.1 and 17.5).  Three workgroups fit a
+  // CU; two are better while a particle keeps eight parts and these stay short (three and two: 32 poses
+  // of 320x240 15.7 and 14.0, 64 of 128x128 14.1 and 13.1, four two-hand poses 15.1 and 14.4), not
+  // where the parts grow long or few (64 poses of 320x240 15.9 and 17.0, 64 two-hand ones 22.0 and
+  // 23.8, 128 of 128x128 15.1 and 15.6).
   f.small = one && (n_total <= kSmallParticles ||
                     (n_total <= kSmallGroupsPerCu * c->n_cu &&
                      (long long)n_total * c->max_tiles() <= kSmallTiles));

@@ -94,10 +94,9 @@ __global__ __launch_bounds__(kBlock) void pack_kernel(const uint16_t* __restrict
   }
 }
 
-// Whole-ROI background sums in a fixed order (one workgroup).
-// (one workgroup, a chain of latencies: 16 wavefronts with four tiles a load take a 640x480
-// frame's 4800 tiles in two rounds, 4 wavefronts with one tile a load in 19: 6.8 to 2.2 us, a
-// frame's ingest 56 to 51.4 us)
+// Whole-ROI background sums in a fixed order (one workgroup, a chain of latencies: 16 wavefronts
+// with four tiles a load take a 640x480 frame's 4800 tiles in two rounds, 4 wavefronts with one
+// tile a load in 19: 6.8 to 2.2 us, a frame's ingest 56 to 51.4 us).
 constexpr int kTotalBlock = 1024;
 __global__ __launch_bounds__(kTotalBlock) void total_kernel(const float* __restrict__ tile_td,
                                                             const int* __restrict__ tile_skin,
@@ -159,7 +158,8 @@ hipError_t launch_pack_observation(const uint16_t* depth, const uint8_t* skin, i
 // sizes the workspace).  An exclusive scan of the per-particle item counts then gives the
 // item -> particle map.
 
-constexpr int kFloorTiles = 8;       // 16 left a 32-particle gradient launch at 22.5 us (19.2)
+constexpr int kFloorTiles = 8;       // (a refined generation of 64 poses of a 128x128 frame 120.5
+                                     // us, 126.6 us with 16)
 
 // Tiles per item of a list of total_tiles tiles.
 __device__ __forceinline__ int tiles_per_item(const EvalArgs& a, int total_tiles) {
@@ -427,7 +427,8 @@ constexpr float kTileHalfDiag = 4.9498f;
 // away is covered by the factor 1.0001 and the capsule's own margin: over images of 4096 pixels,
 // principal points up to 100 000 px outside them, focal lengths of 5 to 20 000 px and hands at 30
 // mm to 20 m, the silhouettes stayed 0.126 px inside the reach, and 0.24 px inside the boxes (pad
-// 0.25).  (1024 two-hand poses 116.8 us with 0.5 px, 115.5 with 0.125.)
+// 0.25).  (With 0.5 px 1024 two-hand poses take 116.0 us, 115.0 with 0.125; 65536 poses 2384 and
+// 2367 us.)
 constexpr float kReachPad = 0.125f;
 
 // ------------------------------------------------------------------------------------
@@ -933,8 +934,8 @@ __device__ __forceinline__ bool fk_particle(const EvalArgs& a, const Workspace& 
         // |x - cx| <= hx and |y - cy| <= hy for a tile's corner pixel (x, y), exact in FP32.
         // Rays pass through whole pixel coordinates, so the (padded) bounds round inwards here;
         // the tile rectangles, which size the gradient's work items, keep the box rounded outwards.
-        // A tile tests 6 to 8 % fewer primitives: 1024 two-hand poses 121.2 to 116.8 us, 64 uneven
-        // frames 89.9 to 83.8 us, 65536 poses 2465 to 2350 us.
+        // A tile tests 6 to 8 % fewer primitives (outwards and inwards: 1024 two-hand poses 118.8 and
+        // 115.0 us, 64 uneven frames 88.1 and 83.2 us, 65536 poses 2456 and 2367 us).
         const float x0 = fmaxf(ceilf(bx0), 0.0f), x1 = fminf(floorf(bx1), (float)(fs.W - 1));
         const float y0 = fmaxf(ceilf(by0), 0.0f), y1 = fminf(floorf(by1), (float)(fs.H - 1));
         const bool none = box.x > box.y || !(x0 <= x1) || !(y0 <= y1);
@@ -1881,9 +1882,9 @@ __device__ __forceinline__ void cast_tiles(const EvalArgs& a, const TypeMasks& t
 // cones and elliptic cylinders), so a model without the latter keeps the smaller register
 // footprint.  The forward cast asks for eight wavefronts per SIMD, the gradient cast for six (80
 // vector registers, about ten spilled around the tile loop): six workgroups per CU take a small
-// launch's items, a few more than its nominal grid of five, in one round, where five left the
-// last ones to a second round (two-hand refined generation 338 us, 333 us with six, 336 us with
-// seven).  SELF: the wavefronts build the work list (at most kSelfSched particles).
+// launch's items, a few more than its nominal grid of five, in one round, where five leave the
+// last ones to a second round (two-hand refined generation 304 us with five, 296 us with six, 299
+// us with seven; gradients of 128 two-hand poses 48.2, 45.3 and 46.8 us).  SELF: the wavefronts build the work list (at most kSelfSched particles).
 template <bool GRAD, bool DEBUG, int NT, bool SELF>
 __global__ __attribute__((amdgpu_flat_work_group_size(1, kBlock),
                           amdgpu_waves_per_eu(GRAD ? 6 : DEBUG ? 1 : 8)))
@@ -2072,8 +2073,8 @@ __device__ __forceinline__ void finish_part(const EvalArgs& a, const Workspace& 
 // One workgroup per part of a particle: the kinematics (repeated in every part, on CUs that would
 // be idle otherwise), its tables kept in LDS, then the part's tiles.  A chain of latencies (about
 // 5 us of kinematics, 1 us per tile of a wavefront): against separate launches it saves one launch
-// gap and the tables' way through memory (16 poses of a 64x64 frame 17.9 to 14.9 us, 64 of a
-// 128x128 frame 18.1 to 15.3 us).  Workgroups of eight and sixteen wavefronts, with fewer parts,
+// gap and the tables' way through memory, and a finalize launch where it writes the costs (16
+// poses of a 64x64 frame 18.1 to 12.1 us, 64 of a 128x128 frame 18.2 to 13.2 us).  Workgroups of eight and sixteen wavefronts, with fewer parts,
 // lost more to the barriers than they saved (15.8 and 17.3 us).
 // FINISH: the costs are written here (else the partials are assembled by the next kernel).
 template <int NT, bool FINISH>
@@ -2615,9 +2616,9 @@ hipError_t launch_eval_stage(int stage, const EvalArgs& a, const Workspace& ws, 
     case kStageFk:
       if (a.src) break;   // the kinematics of the previous evaluation are reused
       // wavefronts per particle: at least one per 64 primitives (a lane sets up one primitive);
-      // four while every particle still has a CU of its own (64 poses of a 128x128 frame: 25.1
-      // against 25.4 us per swarm generation), else few, the kernel being bound by its FP64
-      // instructions (4096 poses of 64 uneven frames: 95, 102 and 115 us with one, two, four)
+      // four while every particle still has a CU of its own (256 poses of a 320x240 frame 29.9 us,
+      // 31.1 us with one; gradients of them 49.4 and 51.1 us), else few, the kernel being bound by
+      // its FP64 instructions (4096 poses of 64 uneven frames: 83, 92 and 106 us with one, two, four)
       if (n_total <= kFkSpread)
         hipLaunchKernelGGL(fk_kernel<4>, dim3(n_total), dim3(kBlock), 0, s, a, ws);
       else if (a.n_prim > kWave)
