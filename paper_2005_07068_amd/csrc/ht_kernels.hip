@@ -1884,7 +1884,8 @@ __device__ __forceinline__ void cast_tiles(const EvalArgs& a, const TypeMasks& t
 // vector registers, about ten spilled around the tile loop): six workgroups per CU take a small
 // launch's items, a few more than its nominal grid of five, in one round, where five leave the
 // last ones to a second round (two-hand refined generation 304 us with five, 296 us with six, 299
-// us with seven; gradients of 128 two-hand poses 48.2, 45.3 and 46.8 us).  SELF: the wavefronts build the work list (at most kSelfSched particles).
+// us with seven; gradients of 128 two-hand poses 48.2, 45.3 and 46.8 us).  SELF: the wavefronts
+// build the work list (at most kSelfSched particles).
 template <bool GRAD, bool DEBUG, int NT, bool SELF>
 __global__ __attribute__((amdgpu_flat_work_group_size(1, kBlock),
                           amdgpu_waves_per_eu(GRAD ? 6 : DEBUG ? 1 : 8)))
@@ -2074,8 +2075,9 @@ __device__ __forceinline__ void finish_part(const EvalArgs& a, const Workspace& 
 // be idle otherwise), its tables kept in LDS, then the part's tiles.  A chain of latencies (about
 // 5 us of kinematics, 1 us per tile of a wavefront): against separate launches it saves one launch
 // gap and the tables' way through memory, and a finalize launch where it writes the costs (16
-// poses of a 64x64 frame 18.1 to 12.1 us, 64 of a 128x128 frame 18.2 to 13.2 us).  Workgroups of eight and sixteen wavefronts, with fewer parts,
-// lost more to the barriers than they saved (15.8 and 17.3 us).
+// poses of a 64x64 frame 18.1 to 12.1 us, 64 of a 128x128 frame 18.2 to 13.2 us).  Workgroups of
+// eight and sixteen wavefronts, with fewer parts, lost more to the barriers than they saved (15.8
+// and 17.3 us against 14.9 with four, each with a finalize launch).
 // FINISH: the costs are written here (else the partials are assembled by the next kernel).
 template <int NT, bool FINISH>
 __global__ __launch_bounds__(kBlock) void small_eval_kernel(EvalArgs a, Workspace ws,
@@ -2618,7 +2620,7 @@ hipError_t launch_eval_stage(int stage, const EvalArgs& a, const Workspace& ws, 
       // wavefronts per particle: at least one per 64 primitives (a lane sets up one primitive);
       // four while every particle still has a CU of its own (256 poses of a 320x240 frame 29.9 us,
       // 31.1 us with one; gradients of them 49.4 and 51.1 us), else few, the kernel being bound by
-      // its FP64 instructions (4096 poses of 64 uneven frames: 83, 92 and 106 us with one, two, four)
+      // its FP64 instructions (4096 poses of 64 uneven frames 83, 92 and 106 us with one, two, four)
       if (n_total <= kFkSpread)
         hipLaunchKernelGGL(fk_kernel<4>, dim3(n_total), dim3(kBlock), 0, s, a, ws);
       else if (a.n_prim > kWave)
