@@ -660,7 +660,11 @@ ht_status build_model(const ht_model* m, ht::DevModel& d, ht::TypeMasks& tm) {
     for (int k = 0; k < m->n_prim; ++k) {
       if (m->prim_type[k] != t) continue;
       d.prim_id[o] = make_int4(k, m->prim_seg[k], t, tree[m->prim_seg[k]]);
-      for (int i = 0; i < 12; ++i) d.prim_frame[o][i] = m->prim_frame[k * 12 + i];
+      // columns that the type's definition leaves free (all axes of a sphere, x and y of a circular
+      // cylinder or cone) may hold anything: the kinematics finds zeros there
+      const int free_cols = t == HT_SPHERE ? 3 : (t == HT_CYLINDER || t == HT_CONE ? 2 : 0);
+      for (int i = 0; i < 12; ++i)
+        d.prim_frame[o][i] = i % 4 < free_cols ? 0.0 : m->prim_frame[k * 12 + i];
       for (int i = 0; i < 3; ++i) {
         const double z = m->prim_size[k * 3 + i];
         d.prim_size[o][i] = z;

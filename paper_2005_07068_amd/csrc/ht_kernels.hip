@@ -815,18 +815,19 @@ __device__ __forceinline__ bool fk_particle(const EvalArgs& a, const Workspace& 
 
       // Conservative pixel box of an axis-aligned 3D box of the solid, and its bounding capsule,
       // in FP32 (the rounding of a 600 mm coordinate, about 1e-4 mm or pixels, is covered by the
-      // quarter-pixel pads) and with selects in place of a branch per type.  The solid is the
-      // convex hull of a cross-section at c and one at c + L u (caps, not the sphere and the
-      // ellipsoid).  A sphere reaches r along every axis, a disc across u r sqrt(1 - u_i^2), the
-      // ellipsoid and the elliptic disc sqrt(sum_j (F_ij g_j)^2) with semi-axes g along the
-      // frame's columns: only the columns that a type's definition names are read, the others
-      // may hold anything.
+      // quarter-pixel pads) and without branches or selects per axis.  The solid is the convex
+      // hull of a cross-section at c and one at c + L u (caps, not the sphere and the ellipsoid).
+      // A section's reach along an axis is the root of
+      //   r^2 (sphere), r^2 - r^2 u_i^2 (disc across u), sum_j F_ij^2 g_j^2 (ellipsoid, elliptic disc
+      // with semi-axes g along the frame's columns);
+      // columns that a type's definition leaves free are zero in the model's tables.
       const bool ball = typ == HT_SPHERE, round = typ == HT_CYLINDER || typ == HT_CONE;
       const bool capped = !ball && typ != HT_ELLIPSOID;
       const float s0 = (float)sz[0], s1 = (float)sz[1], s2 = (float)sz[2];
-      const float g1 = typ == HT_ELLIPSOID ? s1 : s2;
-      const float g2 = typ == HT_ELLIPSOID ? s2 : 0.0f;
-      const float r1 = typ == HT_CONE ? s2 : s0;
+      const float r2 = ball || round ? s0 * s0 : 0.0f;
+      const float g1 = typ == HT_ELLIPSOID ? s1 : (typ == HT_ECYLINDER ? s2 : 0.0f);
+      const float g22 = round ? -r2 : (typ == HT_ELLIPSOID ? s2 * s2 : 0.0f);
+      const float k1 = typ == HT_CONE ? s2 * fast_rcp(s0) : 1.0f;   // the second section's scale
       const float Lf = capped ? s1 : 0.0f;
       const float cf[3] = {(float)c[0], (float)c[1], (float)c[2]};
       float Ff[3][3], lo3[3], hi3[3];
@@ -834,15 +835,12 @@ __device__ __forceinline__ bool fk_particle(const EvalArgs& a, const Workspace& 
       for (int i = 0; i < 3; ++i) {
 #pragma unroll
         for (int j = 0; j < 3; ++j) Ff[i][j] = (float)F[i * 4 + j];
-        const float f0 = Ff[i][0] * s0, f1 = Ff[i][1] * g1, f2 = Ff[i][2] * g2;
-        const float q = round ? fmaf(-Ff[i][2], Ff[i][2], 1.0f)
-                              : fmaf(f0, f0, fmaf(f1, f1, f2 * f2));
-        const float rt = fast_sqrt(fmaxf(q, 0.0f));
-        const float e0 = ball ? s0 : (round ? s0 * rt : rt);
-        const float e1 = round ? r1 * rt : e0;
-        const float c1 = capped ? fmaf(Lf, Ff[i][2], cf[i]) : cf[i];
-        lo3[i] = fminf(cf[i] - e0, c1 - e1);
-        hi3[i] = fmaxf(cf[i] + e0, c1 + e1);
+        const float f0 = Ff[i][0] * s0, f1 = Ff[i][1] * g1;
+        const float q = fmaf(f0, f0, fmaf(f1, f1, fmaf(g22, Ff[i][2] * Ff[i][2], r2)));
+        const float e = fast_sqrt(fmaxf(q, 0.0f));
+        const float c1 = fmaf(Lf, Ff[i][2], cf[i]);
+        lo3[i] = fminf(cf[i] - e, c1 - k1 * e);
+        hi3[i] = fmaxf(cf[i] + e, c1 + k1 * e);
       }
       int4 box;
       // the same bounds unrounded, for the tile test below

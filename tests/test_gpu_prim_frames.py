@@ -1,6 +1,6 @@
 """A primitive's local frame counts only as far as its type's definition names it: a sphere has the
 frame's origin, a cylinder and a cone its origin and z axis.  The other columns are free (zeros,
-or anything finite), and every result must be that of a model whose frames are orthonormal."""
+or anything), and every result must be that of a model whose frames are orthonormal."""
 import numpy as np
 import pytest
 
@@ -16,12 +16,13 @@ def _with_free_columns(model, fill):
     m["prim_frame"] = np.array(model["prim_frame"], np.float64)
     for k, t in enumerate(np.asarray(model["prim_type"])):
         free = {SPHERE: 3, CYLINDER: 2, CONE: 2}.get(int(t), 0)
-        m["prim_frame"][k, :, :free] = 0.0 if fill == "zeros" else rng.uniform(-3, 3, (3, free))
+        m["prim_frame"][k, :, :free] = {"zeros": 0.0, "random": rng.uniform(-3, 3, (3, free)),
+                                        "nan": np.nan}[fill]
     return m
 
 
 @pytest.mark.parametrize("primitive_set", ["cylinders", "paper"])
-@pytest.mark.parametrize("fill", ["zeros", "random"])
+@pytest.mark.parametrize("fill", ["zeros", "random", "nan"])
 @pytest.mark.parametrize("cull", [0, 1])
 @pytest.mark.parametrize("n", [5, 300])
 def test_free_frame_columns_change_nothing(primitive_set, fill, cull, n):
