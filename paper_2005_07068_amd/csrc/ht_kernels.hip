@@ -1641,10 +1641,10 @@ struct Head {
         tile_skin(uni(p->tile_skin)), grad_mask(nullptr) {}
 };
 
-// Bound by the issue of vector instructions (65536 poses of a 64x64 hand: 2.1e9 of them, 3.1
-// cycles each and SIMD, every cycle of the launch).  A multiply-add of vector registers takes 2.4
-// cycles, a comparison, select, minimum, conversion, FP64 or DPP instruction or one with a scalar
-// operand 4.2, a transcendental 16, so the code around the tests counts those: boxes compared by
+// Bound by the issue of vector instructions (65536 poses of a 320x240 frame: 1.84e9 of them, one
+// every 3.2 cycles and SIMD, every cycle of the launch).  A multiply-add of vector registers takes
+// 2.5 cycles, a comparison, select, minimum, conversion, FP64 or DPP instruction or one with a scalar
+// operand 4.1, a transcendental 8 to 19, so the code around the tests counts those: boxes compared by
 // distance from their centre (2 subtractions and 2 comparisons for 4), the nearest entry and the
 // background plane by integer minimum, one comparison per match term.  65536 poses 2600 to 2440
 // us, 1024 two-hand poses 128.0 to 120.7 us.  Fewer scalar instructions alone do not help: culling
