@@ -144,8 +144,7 @@ struct ht_ctx {
   int* r_sel = nullptr;       // [cap_ref]
   int* r_active = nullptr;    // [cap_ref]
   int cap_ref = 0;
-  int* pso_flags = nullptr;   // [cap_flags] per-particle improved / mutated flags
-  int cap_flags = 0;
+  int* pso_flags = nullptr;   // [cap_particles] per-particle improved / mutated flags
   int* seg_partial = nullptr; // [cap_seg] per-block minima of the preprocessing
   int cap_seg = 0;
   std::map<GraphKey, hipGraphExec_t> graphs;
@@ -201,6 +200,7 @@ void free_workspace(ht_ctx* c) {
   dfree(c->ws.item_map);
   dfree(c->ws.list);
   dfree(c->ws.counters);
+  dfree(c->pso_flags);
   c->cap_particles = c->cap_tiles = 0;
   c->cap_wrench = false;
 }
@@ -259,6 +259,7 @@ ht_status ensure_workspace(ht_ctx* c, int n_total, int max_tiles, bool grad, hip
     HT_HIP(hipMalloc(&w.wrench, ni * c->n_seg * 6 * sizeof(float)));
   }
   HT_HIP(hipMalloc(&w.counters, 2 * ht::kCounterInts * sizeof(int)));
+  HT_HIP(hipMalloc(&c->pso_flags, (size_t)np * sizeof(int)));
   c->cap_tiles = nt;
   c->cap_particles = np;
   c->cap_wrench = wr;
@@ -530,6 +531,8 @@ ht_status ht_create(ht_ctx** out, int hip_device) {
   if (e == hipSuccess) e = hipMemset(c->d_done, 0, (size_t)kDoneSets * c->done_ints() * sizeof(int));
   if (e == hipSuccess) e = hipMalloc(&c->d_errors, sizeof(unsigned int));
   if (e == hipSuccess) e = hipMemset(c->d_errors, 0, sizeof(unsigned int));
+  // (the caller's streams need not wait for the one that these clear on)
+  if (e == hipSuccess) e = hipStreamSynchronize(nullptr);
   if (e != hipSuccess) {
     ht_destroy(c);
     return fail(HT_ERR_OOM, "context allocation failed: %s", hipGetErrorString(e));
@@ -567,7 +570,6 @@ void ht_destroy(ht_ctx* c) {
   dfree(c->r_cgrad);
   dfree(c->r_sel);
   dfree(c->r_active);
-  dfree(c->pso_flags);
   dfree(c->seg_partial);
   dfree(c->d_slots);
   dfree(c->d_model);
@@ -1017,14 +1019,6 @@ ht_status pso_step_impl(ht_ctx* c, const ht_swarm& sw, const ht_pso_params& p, h
       prev_grad = g;
     }
   }
-  if (F * P > c->cap_flags) {
-    if (capturing(s)) return fail(HT_ERR_STATE, "swarm flags too small during capture");
-    HT_HIP(hipDeviceSynchronize());
-    invalidate_graphs(c);   // captured graphs hold the old buffers
-    dfree(c->pso_flags);
-    HT_HIP(hipMalloc(&c->pso_flags, (size_t)F * P * sizeof(int)));
-    c->cap_flags = F * P;
-  }
   HT_HIP(traced(c, HT_K_PSO, F * P, s,
                 [&] { return ht::launch_pso_update(c->d_model, sw, p, D, c->pso_flags, s); }));
   return HT_OK;
@@ -1158,14 +1152,6 @@ ht_status ht_pso_run_graph(ht_ctx* c, const ht_swarm* sw, const ht_pso_params* p
     const int most = std::max(F * P, refine ? F * 4 * K : 0);
     if ((st = ensure_workspace(c, most, c->max_tiles(), refine, s)) != HT_OK) return st;
     if (refine && (st = ensure_refine(c, F * K, s)) != HT_OK) return st;
-    // (the one-launch update of a small plain swarm needs no flags)
-    if ((refine || !ht::pso_update_is_small(*sw, c->n_dof)) && F * P > c->cap_flags) {
-      HT_HIP(hipDeviceSynchronize());
-      invalidate_graphs(c);   // captured graphs hold the old buffers
-      dfree(c->pso_flags);
-      HT_HIP(hipMalloc(&c->pso_flags, (size_t)F * P * sizeof(int)));
-      c->cap_flags = F * P;
-    }
     hipStream_t cs;
     HT_HIP(hipStreamCreateWithFlags(&cs, hipStreamNonBlocking));
     hipError_t e = hipStreamBeginCapture(cs, hipStreamCaptureModeThreadLocal);
