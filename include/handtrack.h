@@ -22,6 +22,8 @@
  *     the legacy default stream) and never synchronise, so they can be captured in a HIP
  *     graph once the context's workspace is reserved (ht_reserve); without a reservation a
  *     call may grow the workspace with hipMalloc, which is refused during capture.
+ *     A recorded call keeps the workspace it was recorded with: after a call beyond the
+ *     reservation, which reallocates it, or a new model, record again before replaying.
  *   - Order: the calls of a context share its workspace, so their work must not overlap: enqueue
  *     them on one stream, or order the streams with events, replays of recorded calls included.
  *     Calls that overlap all the same give undefined results; calls after them are not affected.
